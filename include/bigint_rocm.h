@@ -57,7 +57,7 @@ extern "C" {
                                result is not valid (not expected to occur) */
 
 /* multiplication algorithms */
-#define BIGINT_MUL_AUTO 0  /* MFMA-split where supported, else plain        */
+#define BIGINT_MUL_AUTO 0  /* the fastest of the transform, MFMA-split, plain */
 #define BIGINT_MUL_PLAIN 1 /* u64-digit schoolbook convolution               */
 #define BIGINT_MUL_MFMA 2  /* 7- or 8-bit digits, int8 MFMA Toeplitz tiles   */
 #define BIGINT_MUL_KARATSUBA 3 /* one Karatsuba level over BIGINT_MUL_MFMA  */
@@ -144,19 +144,25 @@ int bigint_sub(uint32_t* out, uint32_t* borrow_out, const uint32_t* a,
  * `stream` (stream-ordered); a second launch resolves each instance's strip
  * carries.  Same bytes as one work-group per instance
  * (bigint_mfma_split_parts reports the split).
+ * AUTO multiplies large operands (from about 640 limbs each in large batches,
+ * 2560 limbs in small ones, na + nb <= 32768) by number-theoretic transforms
+ * of the limbs modulo three 27-bit primes, whose residues determine every
+ * C_k < 2^78 exactly (integers only, no workspace, same bytes), unless a
+ * configuration is forced on the thread.
  * a: batch*na limbs, b: batch*nb limbs, out: batch*(na+nb) limbs.
  * na, nb >= 1.  MFMA needs na, nb <= BIGINT_MFMA_MAX_LIMBS (else
- * BIGINT_EUNSUPPORTED); PLAIN needs na+nb <= 32768; AUTO picks MFMA when it
- * fits and na,nb >= 64, otherwise PLAIN. */
+ * BIGINT_EUNSUPPORTED); PLAIN needs na+nb <= 32768; AUTO picks the transform
+ * as above, else MFMA when it fits and na,nb >= 64, otherwise PLAIN. */
 int bigint_mul(uint32_t* out, const uint32_t* a, int64_t na, const uint32_t* b,
                int64_t nb, int64_t batch, int algo, void* stream);
 
 /* ---- fixed-precision product and the evaluation's fused workloads (Section 6) ---
  * bigint_mullo: out[i] = a[i] * b[i] mod B^n (B = 2^32), the paper's
  *   multiplication, whose quadratic formula keeps only digits k < n
- *   (Section 5.2).  MFMA-split, computing only the strips below limb n.
- *   Small batches split each product's bands over work-groups as
- *   bigint_mul's do (same condition, workspace and bytes).
+ *   (Section 5.2).  MFMA-split, computing only the strips below limb n, or
+ *   the transform multiply where it is faster (as bigint_mul's AUTO).
+ *   Small batches on the MFMA multiply split each product's bands over
+ *   work-groups as bigint_mul's do (same condition, workspace and bytes).
  *   a, b, out: batch*n limbs; 1 <= n <= BIGINT_MFMA_MAX_LIMBS; out must not
  *   overlap a or b.
  * bigint_add6: the 6-Add benchmark (Table tab-add): six dependent additions

@@ -1,0 +1,99 @@
+"""GPU parity of the transform multiply (bigint_mul AUTO and bigint_mullo pick
+it): at the edges of its transform sizes (M = 4 q T points), on operands of
+all ones (the largest coefficients, carries through every block), zeros and
+single limbs, against the MFMA-split multiply on every instance and the oracle
+on the first rows; integers throughout, so the bytes are equal."""
+import numpy as np
+import pytest
+
+from gpu_util import dev, host, oracle_map, rand_limbs
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def bi():
+    import paper_2607_28897_amd as m
+    m.lib()
+    yield m
+    m.set_mfma_config(0, 0, 0)
+
+
+def operands(seed, batch, na, nb):
+    g = np.random.default_rng(100000 + seed)
+    a, b = rand_limbs(g, batch, na), rand_limbs(g, batch, nb)
+    a[0], b[0] = 0xFFFFFFFF, 0xFFFFFFFF
+    a[1], b[1] = 0xFFFFFFFF, 0
+    b[1, 0] = 1                                   # all ones, unchanged
+    a[2] = 0
+    a[2, -1] = 0xFFFFFFFF
+    b[2] = 0xFFFFFFFF
+    a[3, na // 2:] = 0xFFFFFFFF                   # long runs against random limbs
+    b[3, : nb // 3] = 0
+    return a, b
+
+
+# every transform size: the largest operands that fit, one limb more (the next
+# size), odd and unequal ones
+EDGES = [(64, 640), (64, 768), (64, 896), (64, 1024), (128, 1280), (128, 1536), (128, 1792), (128, 2048),
+         (256, 2560), (256, 3072), (256, 3584), (256, 4096), (512, 5120), (512, 6144), (512, 7168),
+         (512, 8192), (1024, 10240), (1024, 12288), (1024, 14336), (1024, 16384)]
+
+
+@pytest.mark.parametrize("T,n", EDGES)
+@pytest.mark.parametrize("da,db", [(0, 0), (-1, 0), (1, 0), (-3, -200)])
+def test_full_products(bi, orc, T, n, da, db):
+    na, nb = n + da, n + db
+    if na + nb > 32768:
+        na = 16384
+    batch = max(5, 4096 * 64 // T) if T < 256 else 5
+    a, b = operands(n + da + 5 * db, batch, na, nb)
+    ta, tb = dev(a), dev(b)
+    p = bi.mul(ta, tb)
+    want = bi.mul(ta, tb, bi.MUL_MFMA)
+    assert bool((p == want).all())
+    exp = oracle_map(lambda i: orc.mul1(a[i], b[i]), range(4))
+    got = host(p[:4])
+    assert all(np.array_equal(got[i], exp[i]) for i in range(4))
+
+
+@pytest.mark.parametrize("n,batch", [(2048, 2048), (2559, 6), (4096, 5), (5000, 5), (8192, 5), (9999, 4),
+                                     (16383, 4), (16384, 5)])
+def test_products_mod_bn(bi, orc, n, batch):
+    a, b = operands(n, batch, n, n)
+    ta, tb = dev(a), dev(b)
+    p = bi.mullo(ta, tb)
+    bi.set_mfma_config(0, 8, 0)                   # a forced configuration keeps the MFMA multiply
+    want = bi.mullo(ta, tb)
+    bi.set_mfma_config(0, 0, 0)
+    assert bool((p == want).all())
+    got = host(p[:4])
+    assert all(np.array_equal(got[i], orc.mul1(a[i], b[i])[:n]) for i in range(4))
+
+
+@pytest.mark.parametrize("na,nb", [(16384, 5000), (12000, 2500), (7000, 16384)])
+def test_unequal_operands(bi, orc, na, nb):
+    a, b = operands(na + nb, 4, na, nb)
+    p = bi.mul(dev(a), dev(b))
+    exp = oracle_map(lambda i: orc.mul1(a[i], b[i]), range(4))
+    got = host(p)
+    assert all(np.array_equal(got[i], exp[i]) for i in range(4))
+
+
+def test_graph_capture(bi):
+    """A call with no workspace: captured and replayed, eager work between."""
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(5)
+    a = torch.randint(-2**31, 2**31, (8, 4096), dtype=torch.int32, device="cuda", generator=g)
+    b = torch.randint(-2**31, 2**31, (8, 4096), dtype=torch.int32, device="cuda", generator=g)
+    want = bi.mul(a, b, bi.MUL_MFMA)
+    bi.mul(a, b)
+    gr = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(gr):
+        p = bi.mul(a, b)
+    for _ in range(3):
+        p.zero_()
+        gr.replay()
+        torch.cuda.synchronize()
+        assert bool((p == want).all())
+        bi.add(a, b)
