@@ -264,25 +264,23 @@ static bool mfma_fits(int64_t na, int64_t nb, MfmaCfg cfg) {
 // a configuration forced on this thread keeps one work-group per instance
 static bool split_forced() { return t_cfg_P || t_cfg_waves || t_cfg_dw || t_cfg_tile; }
 
-// Whether a uniform batch of na x nb products (mod B^n with low) runs on the
-// transform multiply.  Times per product and CU at full load, in ns, fitted to
-// batches of 4096 products of 640 .. 2048 limbs and 1024 of 4096 .. 16384
-// (measured transform / MFMA, us per CU: 640 limbs 4.5 / 5.2, 1024 6.7 / 7.2,
-// 2048 13.5 / 16.8, 4096 28 / 56, 8192 54 / 191, 16384 124 / 640; products
-// mod B^n take half the MFMA work and the whole transform): the MFMA
-// multiply takes 2.4e-3 na nb + 2.7 (na + nb), a transform of M points
-// 3.4 M.  A small batch is bound by one product's latency instead, which on
-// few waves is longer for the transform below 5120 points (64 x 2048 limbs
-// 37 against 26 us), so those sizes take it only where the batch gives every
-// CU its 16 waves.
-static bool ntt_rule(int64_t na, int64_t nb, int64_t batch, bool low) {
-  int T, q;
-  if (split_forced() || na > BIGINT_MFMA_MAX_LIMBS || nb > BIGINT_MFMA_MAX_LIMBS || !ntt_size(na, nb, &T, &q))
-    return false;
-  const int64_t M = 4 * (int64_t)q * T;
-  if (M < 5120 && batch * T < 1024 * (int64_t)num_cus()) return false;
-  const int64_t mfma = 24 * na * nb / (low ? 2 : 1) / 10000 + 27 * (na + nb) / 10;
-  return mfma > 34 * M / 10;
+// The transform kernel for a uniform batch of na x nb products (mod B^n with
+// low), or -1 where the MFMA multiply is faster.  The MFMA multiply takes
+// about 2.4e-6 na nb + 2.7e-3 (na + nb) us of a CU per product in a large
+// batch (640 limbs 5.2, 1024 7.2, 2048 17, 4096 56, 8192 190, 16384 640; the
+// transform takes 3.9, 5.8, 10, 26, 53 and 122 there), and one product alone
+// 9 us plus 0.7 of that up to 50 us, where its bands start to be split over
+// the CUs, and a sixth of the rest (measured 12, 14, 24, 41, 69 and 127 us
+// for those sizes; the transform 12, 12, 15, 25, 60 and 108).
+static int ntt_choice(int64_t na, int64_t nb, int64_t batch, bool low) {
+  if (split_forced() || na > BIGINT_MFMA_MAX_LIMBS || nb > BIGINT_MFMA_MAX_LIMBS || std::min(na, nb) < 64)
+    return -1;
+  double us;
+  const int pick = ntt_pick(na, nb, batch, &us);
+  if (pick < 0) return -1;
+  const double load = 2.4e-6 * (low ? 0.5 : 1.0) * (double)na * (double)nb + 2.7e-3 * (double)(na + nb);
+  const double lat = 9.0 + 0.7 * std::min(load, 50.0) + std::max(load - 50.0, 0.0) / 6.0;
+  return us <= std::max(lat, load * (double)batch / num_cus()) ? pick : -1;
 }
 
 // products of a small batch with each product's bands split over `parts`
@@ -331,11 +329,12 @@ int bigint_mul(uint32_t* out, const uint32_t* a, int64_t na, const uint32_t* b, 
     if (e != hipSuccess) { set_hip_error(e); return BIGINT_EHIP; }
     return BIGINT_OK;
   }
-  if (algo == BIGINT_MUL_AUTO && ntt_rule(na, nb, batch, false)) {
+  const int ntt = algo == BIGINT_MUL_AUTO ? ntt_choice(na, nb, batch, false) : -1;
+  if (ntt >= 0) {
     if (batch == 0) return BIGINT_OK;
     BI_DEBUG("bigint: mul %lld x (%lld x %lld limbs): transforms modulo three primes\n", (long long)batch,
              (long long)na, (long long)nb);
-    return launch_mul_ntt(out, a, na, b, nb, batch, (int)(na + nb), (hipStream_t)stream);
+    return launch_mul_ntt(out, a, na, b, nb, batch, (int)(na + nb), ntt, (hipStream_t)stream);
   }
   const MfmaCfg cfg = uniform_mfma_cfg((int)na, (int)nb, batch, false);
   int use = algo;
@@ -381,9 +380,10 @@ int bigint_mullo(uint32_t* out, const uint32_t* a, const uint32_t* b, int64_t n,
   if (batch > 0x7fffffff || n > BIGINT_MFMA_MAX_LIMBS) return BIGINT_EUNSUPPORTED;
   const size_t bytes = (size_t)n * batch * 4;
   if (overlap(out, bytes, a, bytes) || overlap(out, bytes, b, bytes)) return BIGINT_EINVAL;
-  if (ntt_rule(n, n, batch, true)) {
+  const int ntt = ntt_choice(n, n, batch, true);
+  if (ntt >= 0) {
     if (batch == 0) return BIGINT_OK;
-    return launch_mul_ntt(out, a, n, b, n, batch, (int)n, (hipStream_t)stream);
+    return launch_mul_ntt(out, a, n, b, n, batch, (int)n, ntt, (hipStream_t)stream);
   }
   const MfmaCfg cfg = uniform_mfma_cfg((int)n, (int)n, batch, true);
   if (!mfma_fits(n, n, cfg)) return BIGINT_EUNSUPPORTED;

@@ -91,7 +91,7 @@ constexpr uint64_t root4096(uint64_t p) {
   }
 }
 
-struct Roots {
+struct alignas(64) Roots {
   int32_t f[kTab];    // s of node i (any level), Montgomery form, centred
   int32_t fv[kTab];   // s(i / 2) s(i), negated for odd i (see fwd_net)
   int32_t b[kTab];    // inverses of f and fv
@@ -280,7 +280,8 @@ constexpr InvPlan<R> inv_plan(int start, int free_levels) {
 // three reductions, 20 instructions for four points where two separate
 // levels take 24.  s(l, i) and v(l, i): the root of node i of level l, and
 // that root times its parent's (negated for odd i).
-template <int R, int FREE, class S, class V>
+// HALF: the points of the upper half are 0 on entry.
+template <int R, int FREE, bool HALF = false, class S, class V>
 __host__ __device__ __forceinline__ void fwd_net(int32_t (&x)[R], S s, V v, int32_t p, uint32_t pinv) {
   constexpr int L = log2i(R);
 #pragma unroll
@@ -293,7 +294,11 @@ __host__ __device__ __forceinline__ void fwd_net(int32_t (&x)[R], S s, V v, int3
         const int k = i * 4 * h + j;
         const int32_t a = x[k], b = x[k + h], c = x[k + 2 * h], d = x[k + 3 * h];
         int32_t t, q0, q1;
-        if (l < FREE && i == 0) {
+        if (HALF && l == 0) {
+          t = 0;
+          q0 = b;
+          q1 = mont(b, s(1, 1), p, pinv);
+        } else if (l < FREE && i == 0) {
           t = c;
           q0 = b + d;
           q1 = mont(b - d, s(l + 1, 1), p, pinv);
@@ -402,6 +407,16 @@ struct Size {
 // Each takes the thread's place in the pass explicitly, so that the same code
 // runs on the host for one thread after another.
 
+// root first + i, addressed by a 32-bit offset from the table's uniform base
+__host__ __device__ __forceinline__ int32_t at(Tab f, int first, int i) {
+#ifdef __HIP_DEVICE_COMPILE__
+  typedef const __attribute__((address_space(4))) char* Bytes;
+  return *(Tab)((Bytes)f + (uint32_t)(4 * first) + 4 * i);
+#else
+  return f[first + i];
+#endif
+}
+
 struct Prime {
   int32_t p;
   uint32_t pinv;
@@ -424,16 +439,19 @@ __host__ __device__ __forceinline__ Prime local(const Prime& P) {
 }
 
 // pass 1 of set s: limbs src(s + S1 c) (0 past the operand's end) to LDS
-template <class Z, class Src>
+// HALF: the operand has at most M / 2 limbs, so the upper half of every set
+// is zero: no loads, no reductions and no sums with it.
+template <class Z, bool HALF, class Src>
 __host__ __device__ __forceinline__ void fwd1(const Src& src, int s, int32_t* lds, const Prime& P_) {
   const Prime P = local(P_);
+  constexpr int N = HALF ? Z::R1 / 2 : Z::R1;
   int32_t x[Z::R1];
-  uint32_t raw[Z::R1];
+  uint32_t raw[N];
 #pragma unroll
-  for (int c = 0; c < Z::R1; ++c) raw[c] = src(s + Z::S1 * c);
+  for (int c = 0; c < N; ++c) raw[c] = src(s + Z::S1 * c);
 #pragma unroll
-  for (int c = 0; c < Z::R1; ++c) x[c] = mont_u(raw[c], P.load, P.p, P.pinv);
-  fwd_net<Z::R1, kFwdFree>(x, [&](int, int i) { return P.f[i]; }, [&](int, int i) { return P.fv[i]; }, P.p, P.pinv);
+  for (int c = 0; c < Z::R1; ++c) x[c] = c < N ? mont_u(raw[c], P.load, P.p, P.pinv) : 0;
+  fwd_net<Z::R1, kFwdFree, HALF>(x, [&](int, int i) { return P.f[i]; }, [&](int, int i) { return P.fv[i]; }, P.p, P.pinv);
 #pragma unroll
   for (int c = 0; c < Z::R1; ++c) lds[Z::pos1(s, c)] = x[c];
 }
@@ -447,7 +465,7 @@ __host__ __device__ __forceinline__ void fwd2(int s, int32_t* lds, const Prime& 
 #pragma unroll
   for (int c = 0; c < Z::R2; ++c) x[c] = lds[Z::pos2(s, c)];
   fwd_net<Z::R2, 0>(
-      x, [&](int l, int i) { return P.f[(b << l) + i]; }, [&](int l, int i) { return P.fv[(b << l) + i]; }, P.p,
+      x, [&](int l, int i) { return at(P.f, b << l, i); }, [&](int l, int i) { return at(P.fv, b << l, i); }, P.p,
       P.pinv);
 #pragma unroll
   for (int c = 0; c < Z::R2; ++c) lds[Z::pos2(s, c)] = x[c];
@@ -471,17 +489,26 @@ __host__ __device__ __forceinline__ void block_put(int t, int32_t* lds, const in
 }
 
 // pass 3 of thread t: the last two levels, leaf k in x[k]
+// the roots of thread t's two levels
+struct Roots3 {
+  int32_t s0, s1, s2, v1, v2;
+};
+__host__ __device__ __forceinline__ Roots3 load3(int t, Tab f, Tab fv) {
+  return Roots3{at(f, t, 0), at(f, 2 * t, 0), at(f, 2 * t, 1), at(fv, 2 * t, 0), at(fv, 2 * t, 1)};
+}
+
 template <class Z>
-__host__ __device__ __forceinline__ void fwd3(int t, const int32_t* lds, int32_t (&x)[4][Z::Q], const Prime& P_) {
+__host__ __device__ __forceinline__ void fwd3(int t, const int32_t* lds, int32_t (&x)[4][Z::Q], const Roots3& w,
+                                              const Prime& P_) {
   const Prime P = local(P_);
   int32_t raw[Z::S2];
   block_get<Z>(t, lds, raw);
-  const int32_t s0 = P.f[t], s1 = P.f[2 * t], s2 = P.f[2 * t + 1], v1 = P.fv[2 * t], v2 = P.fv[2 * t + 1];
 #pragma unroll
   for (int j = 0; j < Z::Q; ++j) {
     int32_t y[4] = {raw[j], raw[Z::Q + j], raw[2 * Z::Q + j], raw[3 * Z::Q + j]};
     fwd_net<4, 0>(
-        y, [&](int l, int i) { return l == 0 ? s0 : (i == 0 ? s1 : s2); }, [&](int, int i) { return i == 0 ? v1 : v2; },
+        y, [&](int l, int i) { return l == 0 ? w.s0 : (i == 0 ? w.s1 : w.s2); },
+        [&](int, int i) { return i == 0 ? w.v1 : w.v2; },
         P.p, P.pinv);
 #pragma unroll
     for (int k = 0; k < 4; ++k) x[k][j] = y[k];
@@ -490,14 +517,13 @@ __host__ __device__ __forceinline__ void fwd3(int t, const int32_t* lds, int32_t
 
 // the leaf products of thread t: b[k] = a[k] b[k] mod x^Q - r_k (a reduced)
 template <class Z>
-__host__ __device__ __forceinline__ void leaves(int t, const int32_t (&a)[4][Z::Q], int32_t (&b)[4][Z::Q],
+__host__ __device__ __forceinline__ void leaves(const int32_t (&a)[4][Z::Q], int32_t (&b)[4][Z::Q], const Roots3& w,
                                                 const Prime& P_) {
   const Prime P = local(P_);
   constexpr int Q = Z::Q;
-  const int32_t s1 = P.f[2 * t], s2 = P.f[2 * t + 1];
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
-    const int32_t r = k == 0 ? s1 : (k == 1 ? -s1 : (k == 2 ? s2 : -s2));
+    const int32_t r = k == 0 ? w.s1 : (k == 1 ? -w.s1 : (k == 2 ? w.s2 : -w.s2));
     int32_t c[Q];
 #pragma unroll
     for (int j = 0; j < Q; ++j) {
@@ -528,16 +554,17 @@ constexpr int leaf_bound(int q, int bound) {
 
 // inverse pass 3 of thread t: two levels, points to LDS
 template <class Z>
-__host__ __device__ __forceinline__ void inv3(int t, const int32_t (&x)[4][Z::Q], int32_t* lds, const Prime& P_) {
+__host__ __device__ __forceinline__ void inv3(int t, const int32_t (&x)[4][Z::Q], int32_t* lds, const Roots3& w,
+                                              const Prime& P_) {
   const Prime P = local(P_);
   int32_t raw[Z::S2];
-  const int32_t s0 = P.b[t], s1 = P.b[2 * t], s2 = P.b[2 * t + 1], v1 = P.bv[2 * t], v2 = P.bv[2 * t + 1];
   constexpr int start = leaf_bound(Z::Q, Z::FWD);
 #pragma unroll
   for (int j = 0; j < Z::Q; ++j) {
     int32_t y[4] = {x[0][j], x[1][j], x[2][j], x[3][j]};
     inv_net<4, start, 0, false>(
-        y, [&](int l, int i) { return l == 0 ? s0 : (i == 0 ? s1 : s2); }, [&](int, int i) { return i == 0 ? v1 : v2; },
+        y, [&](int l, int i) { return l == 0 ? w.s0 : (i == 0 ? w.s1 : w.s2); },
+        [&](int, int i) { return i == 0 ? w.v1 : w.v2; },
         P.p, P.pinv, P.one);
 #pragma unroll
     for (int k = 0; k < 4; ++k) raw[k * Z::Q + j] = y[k];
@@ -553,7 +580,7 @@ __host__ __device__ __forceinline__ void inv2(int s, int32_t* lds, const Prime& 
 #pragma unroll
   for (int c = 0; c < Z::R2; ++c) x[c] = lds[Z::pos2(s, c)];
   inv_net<Z::R2, kPassEnd, 0, false>(
-      x, [&](int l, int i) { return P.b[(b << l) + i]; }, [&](int l, int i) { return P.bv[(b << l) + i]; }, P.p,
+      x, [&](int l, int i) { return at(P.b, b << l, i); }, [&](int l, int i) { return at(P.bv, b << l, i); }, P.p,
       P.pinv, P.one);
 #pragma unroll
   for (int c = 0; c < Z::R2; ++c) lds[Z::pos2(s, c)] = x[c];
@@ -612,8 +639,9 @@ __host__ __device__ __forceinline__ uint32_t crt_limb(uint32_t r0, int32_t r1, i
 // there are dropped, with no compare or mask
 struct Limbs {
   __amdgpu_buffer_rsrc_t d;
-  __device__ __forceinline__ Limbs(const uint32_t* p, int n)
-      : d(__builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(p), 0, 4 * n, 0x00020000)) {}
+  int n;
+  __device__ __forceinline__ Limbs(const uint32_t* p, int n_)
+      : d(__builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(p), 0, 4 * n_, 0x00020000)), n(n_) {}
   __device__ __forceinline__ uint32_t operator()(int i) const {
     return __builtin_amdgcn_raw_buffer_load_b32(d, 4 * i, 0, 0);
   }
@@ -622,14 +650,105 @@ struct Limbs {
   }
 };
 
+// The cyclic convolution of a and b modulo the prime of P on the T threads
+// t = 0 .. T - 1 (waves wv = 0 .. NW - 1 of a work-group whose other waves do
+// the same for other primes); the residues of the coefficients stay in lds,
+// in natural order, complete after the closing barrier.
+template <class Z>
+__device__ __forceinline__ void conv_prime(const Limbs& a, const Limbs& b, int t, int wv, int32_t* lds,
+                                           const Prime& P, int32_t scale) {
+  const int lane = t & 63;
+  int32_t xa[4][Z::Q], xb[4][Z::Q];
+  // (loops, also where they run once: unrolled or with their loads moved
+  // ahead of the barriers, the kernel spills a hundred registers)
+  auto fwd12 = [&](const Limbs& src) __attribute__((always_inline)) {
+    if (src.n <= Z::M / 2) {
+#pragma unroll 1
+      for (int ch = wv; ch < Z::NC1; ch += Z::NW) fwd1<Z, true>(src, 64 * ch + lane, lds, P);
+    } else {
+#pragma unroll 1
+      for (int ch = wv; ch < Z::NC1; ch += Z::NW) fwd1<Z, false>(src, 64 * ch + lane, lds, P);
+    }
+    __syncthreads();
+#pragma unroll 1
+    for (int s = t; s < Z::N2; s += Z::T) fwd2<Z>(s, lds, P);
+    __syncthreads();
+  };
+  fwd12(a);
+  fwd3<Z>(t, lds, xa, load3(t, P.f, P.fv), P);
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+#pragma unroll
+    for (int j = 0; j < Z::Q; ++j) xa[k][j] = mont(xa[k][j], scale, P.p, P.pinv);
+  }
+  __syncthreads();
+  fwd12(b);
+  const Roots3 w = load3(t, P.f, P.fv);
+  fwd3<Z>(t, lds, xb, w, P);
+  leaves<Z>(xa, xb, w, P);
+  inv3<Z>(t, xb, lds, load3(t, P.b, P.bv), P);
+  __syncthreads();
+#pragma unroll 1
+  for (int s = t; s < Z::N2; s += Z::T) inv2<Z>(s, lds, P);
+  __syncthreads();
+#pragma unroll 1
+  for (int ch = wv; ch < Z::NC1; ch += Z::NW) {
+    int32_t r[Z::R1];
+    inv1<Z>(64 * ch + lane, lds, r, P);
+#pragma unroll
+    for (int c = 0; c < Z::R1; ++c) lds[Z::pos1(64 * ch + lane, c)] = r[c];
+  }
+  __syncthreads();
+}
+
+__device__ __forceinline__ Prime prime_of(int pr) {
+  const Field& F = d_fields.f[pr];
+  return Prime{F.p, F.pinv, F.one, F.load, (Tab)F.roots.f, (Tab)F.roots.fv, (Tab)F.roots.b, (Tab)F.roots.bv};
+}
+
+// Carries between the threads' runs of E limbs (thread order = limb order):
+// the word above a run goes to limbs 0-1 of the next one, a carry out of
+// limb 1 runs on through runs of all ones, one work-group scan.  over: one
+// word of LDS per wave; scratch: 16 words.
+template <int E>
+__device__ __forceinline__ void close_runs(uint32_t (&x)[E], uint64_t acc, bool live, uint64_t* over,
+                                           uint32_t* scratch) {
+  const int lane = lane_id(), wv = wave_id();
+  uint64_t d = ((uint64_t)(uint32_t)__builtin_amdgcn_update_dpp(0, (int)(acc >> 32), 0x138, 0xf, 0xf, false) << 32) |
+               (uint32_t)__builtin_amdgcn_update_dpp(0, (int)acc, 0x138, 0xf, 0xf, false);
+  if (num_waves() > 1) {
+    if (lane == 63) over[wv] = acc;
+    __syncthreads();
+    if (lane == 0 && wv > 0) d = over[wv - 1];
+  }
+  uint32_t ones = 0xffffffffu;
+#pragma unroll
+  for (int e = 2; e < E; ++e) ones &= x[e];
+  const uint64_t x0 = ((uint64_t)x[1] << 32) | x[0], y0 = x0 + d;
+  const bool h = y0 < x0, full = live && ones == 0xffffffffu;
+  const uint32_t c = wg_carry_scan(h && full, !h && full && y0 == ~0ull, 0u, scratch, nullptr);
+  const uint64_t y = y0 + c;
+  x[0] = (uint32_t)y;
+  x[1] = (uint32_t)(y >> 32);
+  if (h || y < y0) {
+    bool on = true;
+#pragma unroll
+    for (int e = 2; e < E; ++e) {
+      x[e] += on ? 1u : 0u;
+      on = on && x[e] == 0u;
+    }
+  }
+}
+
 // out[0 .. nout) = a * b mod B^nout (nout <= na + nb <= M, the smaller operand
-// at most 16,384 limbs); lds: Z::LDS_BYTES.
+// at most 16,384 limbs) on T threads, one prime after another; lds:
+// Z::LDS_BYTES.
 template <class Z>
 __device__ __forceinline__ void wg_mul_ntt(uint32_t* __restrict__ out, const uint32_t* __restrict__ a, int na,
                                            const uint32_t* __restrict__ b, int nb, int nout, int32_t* lds) {
-  uint64_t* over = reinterpret_cast<uint64_t*>(lds + Z::LDS_WORDS);   // carry words across waves
+  uint64_t* over = reinterpret_cast<uint64_t*>(lds + Z::LDS_WORDS);
   uint32_t* scratch = reinterpret_cast<uint32_t*>(over + Z::NW);
-  const Limbs la(a, na), lb(b, nb), lo_(out, nout);
+  const Limbs la(a, na), lb(b, nb), lo(out, nout);
   // residues of the first two primes: kept in private memory (the opaque
   // index keeps them there), the registers are needed for the next prime
   int32_t keep[2 * Z::S2];
@@ -642,44 +761,8 @@ __device__ __forceinline__ void wg_mul_ntt(uint32_t* __restrict__ out, const uin
     int t = threadIdx.x, wv = __builtin_amdgcn_readfirstlane(wave_id());
     asm volatile("" : "+v"(t));
     asm volatile("" : "+s"(wv));
-    const int lane = t & 63;
-    const Field& F = d_fields.f[pr];
-    const Prime P{F.p, F.pinv, F.one, F.load, (Tab)F.roots.f, (Tab)F.roots.fv, (Tab)F.roots.b, (Tab)F.roots.bv};
-    const int32_t scale = F.scale[Z::K];
-    int32_t xa[4][Z::Q], xb[4][Z::Q];
-    auto fwd12 = [&](const Limbs& src) __attribute__((always_inline)) {
-#pragma unroll 1
-      for (int ch = wv; ch < Z::NC1; ch += Z::NW) fwd1<Z>(src, 64 * ch + lane, lds, P);
-      __syncthreads();
-#pragma unroll 1
-      for (int s = t; s < Z::N2; s += Z::T) fwd2<Z>(s, lds, P);
-      __syncthreads();
-    };
-    fwd12(la);
-    fwd3<Z>(t, lds, xa, P);
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-#pragma unroll
-      for (int j = 0; j < Z::Q; ++j) xa[k][j] = mont(xa[k][j], scale, P.p, P.pinv);
-    }
-    __syncthreads();
-    fwd12(lb);
-    fwd3<Z>(t, lds, xb, P);
-    leaves<Z>(t, xa, xb, P);
-    inv3<Z>(t, xb, lds, P);
-    __syncthreads();
-#pragma unroll 1
-    for (int s = t; s < Z::N2; s += Z::T) inv2<Z>(s, lds, P);
-    __syncthreads();
-#pragma unroll 1
-    for (int ch = wv; ch < Z::NC1; ch += Z::NW) {
-      int32_t r[Z::R1];
-      inv1<Z>(64 * ch + lane, lds, r, P);
-#pragma unroll
-      for (int c = 0; c < Z::R1; ++c) lds[Z::pos1(64 * ch + lane, c)] = r[c];
-    }
-    __syncthreads();
-    // thread t: the residues of coefficients S2 t ..
+    const Prime P = prime_of(pr);
+    conv_prime<Z>(la, lb, t, wv, lds, P, d_fields.f[pr].scale[Z::K]);
     int32_t r[Z::S2];
     block_get<Z>(t, lds, r);
     __syncthreads();
@@ -691,46 +774,71 @@ __device__ __forceinline__ void wg_mul_ntt(uint32_t* __restrict__ out, const uin
       for (int e = 0; e < Z::S2; ++e) keep[Z::S2 + e + zero] = r[e];
     } else {
       uint64_t acc = 0;
-      uint32_t* x = reinterpret_cast<uint32_t*>(r);
+      uint32_t x[Z::S2];
 #pragma unroll
       for (int e = 0; e < Z::S2; ++e)
         x[e] = crt_limb((uint32_t)keep[e + zero], keep[Z::S2 + e + zero], r[e], &acc, d_crt);
-      // the word above this block goes to limbs 0-1 of the next one, a carry
-      // out of limb 1 runs on through blocks of all ones: one carry scan
-      uint64_t d = ((uint64_t)(uint32_t)__builtin_amdgcn_update_dpp(0, (int)(acc >> 32), 0x138, 0xf, 0xf, false) << 32) |
-                   (uint32_t)__builtin_amdgcn_update_dpp(0, (int)acc, 0x138, 0xf, 0xf, false);
-      if (Z::NW > 1) {
-        if (lane == 63) over[wv] = acc;
-        __syncthreads();
-        if (lane == 0 && wv > 0) d = over[wv - 1];
-      }
-      uint32_t ones = 0xffffffffu;
-#pragma unroll
-      for (int e = 2; e < Z::S2; ++e) ones &= x[e];
-      const uint64_t x0 = ((uint64_t)x[1] << 32) | x[0], y0 = x0 + d;
-      const bool h = y0 < x0, full = ones == 0xffffffffu;
-      const uint32_t c = wg_carry_scan(h && full, !h && full && y0 == ~0ull, 0u, scratch, nullptr);
-      const uint64_t y = y0 + c;
-      x[0] = (uint32_t)y;
-      x[1] = (uint32_t)(y >> 32);
-      if (h || y < y0) {
-        bool on = true;
-#pragma unroll
-        for (int e = 2; e < Z::S2; ++e) {
-          x[e] += on ? 1u : 0u;
-          on = on && x[e] == 0u;
-        }
-      }
-      block_put<Z>(t, lds, r);
+      close_runs<Z::S2>(x, acc, true, over, scratch);
+      block_put<Z>(t, lds, reinterpret_cast<int32_t(&)[Z::S2]>(x));
       __syncthreads();
 #pragma unroll 1
       for (int ch = wv; ch < Z::NC1; ch += Z::NW) {
-        const int s = 64 * ch + lane;
+        const int s = 64 * ch + (t & 63);
 #pragma unroll
-        for (int c2 = 0; c2 < Z::R1; ++c2) lo_.put(s + Z::S1 * c2, (uint32_t)lds[Z::pos1(s, c2)]);
+        for (int c2 = 0; c2 < Z::R1; ++c2) lo.put(s + Z::S1 * c2, (uint32_t)lds[Z::pos1(s, c2)]);
       }
     }
   }
+}
+
+// LDS of wg_mul_ntt3
+template <class Z>
+constexpr size_t ntt3_lds_bytes() { return (size_t)3 * Z::LDS_WORDS * 4 + 3 * Z::NW * 8 + 128; }
+
+// The same on 3T threads, the three primes side by side: a third of the
+// latency, for batches that leave waves of the chip idle.  2T threads then
+// recombine 2Q coefficients each.
+template <class Z>
+__device__ __forceinline__ void wg_mul_ntt3(uint32_t* __restrict__ out, const uint32_t* __restrict__ a, int na,
+                                            const uint32_t* __restrict__ b, int nb, int nout, int32_t* lds) {
+  constexpr int E = 2 * Z::Q;
+  uint64_t* over = reinterpret_cast<uint64_t*>(lds + 3 * Z::LDS_WORDS);
+  uint32_t* scratch = reinterpret_cast<uint32_t*>(over + 3 * Z::NW);
+  const Limbs la(a, na), lb(b, nb), lo(out, nout);
+  const int wv = __builtin_amdgcn_readfirstlane(wave_id()), pr = wv / Z::NW;
+  const Prime P = prime_of(pr);
+  conv_prime<Z>(la, lb, threadIdx.x - pr * Z::T, wv - pr * Z::NW, lds + pr * Z::LDS_WORDS, P,
+                d_fields.f[pr].scale[Z::K]);
+  const int t = threadIdx.x, at = (t >> 1) * Z::PS2 + (t & 1) * E;   // this thread's run of E points
+  uint32_t x[E];
+  uint64_t acc = 0;
+  const bool live = t < 2 * Z::T;
+  if (live) {
+    const Field& F = d_fields.f[0];
+    int32_t r[3][E];
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      const int2* src = reinterpret_cast<const int2*>(lds + q * Z::LDS_WORDS + at);
+#pragma unroll
+      for (int e = 0; e < E / 2; ++e) {
+        const int2 v = src[e];
+        r[q][2 * e] = v.x;
+        r[q][2 * e + 1] = v.y;
+      }
+    }
+#pragma unroll
+    for (int e = 0; e < E; ++e)
+      x[e] = crt_limb(canon(mont(r[0][e], F.one, F.p, F.pinv), F.p), r[1][e], r[2][e], &acc, d_crt);
+  }
+  close_runs<E>(x, acc, live, over, scratch);
+  if (live) {
+    int2* dst = reinterpret_cast<int2*>(lds + at);
+#pragma unroll
+    for (int e = 0; e < E / 2; ++e) dst[e] = int2{(int)x[2 * e], (int)x[2 * e + 1]};
+  }
+  __syncthreads();
+#pragma unroll 4
+  for (int i = t; i < nout; i += 3 * Z::T) out[i] = (uint32_t)lds[(i / Z::S2) * Z::PS2 + i % Z::S2];
 }
 
 #endif

@@ -36,11 +36,11 @@ int launch_mul_mfma_split(uint32_t* out, const uint32_t* a, int64_t na, const ui
 int launch_mul_mfma(uint32_t* out, int32_t* coef, const uint32_t* a, int64_t na,
                     const uint32_t* b, int64_t nb, int64_t batch, MfmaCfg cfg, hipStream_t s,
                     int nout = -1);
-// transform multiply: out = a * b mod B^nout, nout <= na + nb (ntt_size: its
-// work-group threads and leaf size for these operands, false: too large)
-bool ntt_size(int64_t na, int64_t nb, int* T, int* q);
+// transform multiply: out = a * b mod B^nout, nout <= na + nb.  ntt_pick: the
+// kernel for this batch and its estimated time, -1 if the operands are too large
+int ntt_pick(int64_t na, int64_t nb, int64_t batch, double* us);
 int launch_mul_ntt(uint32_t* out, const uint32_t* a, int64_t na, const uint32_t* b, int64_t nb, int64_t batch,
-                   int nout, hipStream_t s);
+                   int nout, int pick, hipStream_t s);
 size_t kara_ws_bytes(int n, int64_t batch);
 int launch_mul_kara(uint32_t* out, const uint32_t* a, const uint32_t* b, int64_t n, int64_t batch,
                     void* ws, MfmaCfg cfg, hipStream_t s);

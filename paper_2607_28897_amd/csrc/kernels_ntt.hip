@@ -1,4 +1,6 @@
 // kernels_ntt.hip -- the transform multiply: kernels and launchers.
+#include <algorithm>
+
 #include "internal.hpp"
 #include "dev_mul_ntt.hpp"
 
@@ -14,6 +16,27 @@ __global__ __launch_bounds__(Z::T, 4) void k_mul_ntt(uint32_t* out, const uint32
                      reinterpret_cast<int32_t*>(smem));
 }
 
+// the three primes side by side (3T threads), for batches that leave waves idle
+template <class Z>
+__global__ __launch_bounds__(3 * Z::T) void k_mul_ntt3(uint32_t* out, const uint32_t* a, int na, const uint32_t* b,
+                                                       int nb, int nout) {
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  const int64_t inst = blockIdx.x;
+  ntt::wg_mul_ntt3<Z>(out + inst * (int64_t)nout, a + inst * (int64_t)na, na, b + inst * (int64_t)nb, nb, nout,
+                      reinterpret_cast<int32_t*>(smem));
+}
+
+template <int T, int Q, int R1, int R2>
+static int launch_ntt3_size(uint32_t* out, const uint32_t* a, int64_t na, const uint32_t* b, int64_t nb,
+                            int64_t batch, int nout, hipStream_t s) {
+  typedef ntt::Size<T, Q, R1, R2> Z;
+  constexpr size_t lds = ntt::ntt3_lds_bytes<Z>();
+  BI_HIP(hipFuncSetAttribute((const void*)k_mul_ntt3<Z>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+  hipLaunchKernelGGL(k_mul_ntt3<Z>, dim3((unsigned)batch), dim3(3 * T), lds, s, out, a, (int)na, b, (int)nb, nout);
+  BI_LAUNCH_CHECK();
+  return BIGINT_OK;
+}
+
 template <int T, int Q, int R1, int R2>
 static int launch_ntt_size(uint32_t* out, const uint32_t* a, int64_t na, const uint32_t* b, int64_t nb,
                            int64_t batch, int nout, hipStream_t s) {
@@ -26,42 +49,83 @@ static int launch_ntt_size(uint32_t* out, const uint32_t* a, int64_t na, const u
   return BIGINT_OK;
 }
 
-template <int T, int R1, int R2>
-static int launch_ntt_t(uint32_t* out, const uint32_t* a, int64_t na, const uint32_t* b, int64_t nb,
-                        int64_t batch, int nout, int q, hipStream_t s) {
-  switch (q) {
-    case 5: return launch_ntt_size<T, 5, R1, R2>(out, a, na, b, nb, batch, nout, s);
-    case 6: return launch_ntt_size<T, 6, R1, R2>(out, a, na, b, nb, batch, nout, s);
-    case 7: return launch_ntt_size<T, 7, R1, R2>(out, a, na, b, nb, batch, nout, s);
-    default: return launch_ntt_size<T, 8, R1, R2>(out, a, na, b, nb, batch, nout, s);
-  }
-}
+// ---- which kernel ------------------------------------------------------------------
+// The sizes built: serial (one prime after another) and the three primes side
+// by side, with what one product takes alone on an idle CU and what it takes
+// of a CU in a large batch (us, measured on batches of 1 to 8192; in between,
+// 0.4 of the first and the second add up).  Side by
+// side wins wherever waves are idle, and above 3072 points also in large
+// batches except at 5120 and 6144 points, whose serial kernels fit four
+// work-groups a CU against one (2560-limb products, batch 1024: 73 against
+// 88 us; batch 256: 35 against 25 us).
+struct NttKernel {
+  int M;
+  bool side;     // three primes side by side
+  float lat, load;
+};
+constexpr NttKernel kNtt[] = {
+    {1280, false, 25.f, 3.9f},    {1536, false, 28.f, 4.4f},   {1792, false, 34.f, 5.8f},
+    {2048, false, 34.f, 5.8f},    {2048, true, 12.f, 8.2f},    {2560, false, 27.f, 7.9f},
+    {3072, false, 28.f, 8.9f},    {3072, true, 14.f, 9.5f},    {4096, true, 15.f, 10.4f},
+    {5120, false, 31.f, 18.f},    {5120, true, 22.f, 22.f},    {6144, false, 33.f, 20.f},
+    {6144, true, 23.f, 23.f},     {7168, true, 26.f, 27.f},    {8192, true, 25.f, 26.f},
+    {10240, false, 45.f, 36.f},   {12288, false, 48.f, 41.f},  {14336, false, 57.f, 53.f},
+    {16384, false, 60.f, 53.f},   {20480, false, 80.f, 79.f},  {24576, false, 84.f, 86.f},
+    {28672, false, 107.f, 123.f}, {32768, false, 108.f, 122.f}};
 
-// smallest transform of at least na + nb points: M = 4 q T, T = 64 .. 1024,
-// q = 5 .. 8
-bool ntt_size(int64_t na, int64_t nb, int* T, int* q) {
-  if (na + nb > 32768) return false;
-  for (int t = 64; t <= 1024; t *= 2)
-    for (int k = 5; k <= 8; ++k)
-      if (4 * (int64_t)k * t >= na + nb) {
-        *T = t;
-        *q = k;
-        return true;
-      }
-  return false;
+int ntt_pick(int64_t na, int64_t nb, int64_t batch, double* us) {
+  int best = -1;
+  *us = 0.0;
+  for (int i = 0; i < (int)(sizeof(kNtt) / sizeof(kNtt[0])); ++i) {
+    if (kNtt[i].M < na + nb) continue;
+    if (best >= 0 && kNtt[i].M > 2 * kNtt[best].M) break;
+    const double t = std::max<double>(kNtt[i].lat, 0.4 * kNtt[i].lat + kNtt[i].load * (double)batch / num_cus());
+    if (best < 0 || t < *us) {
+      best = i;
+      *us = t;
+    }
+  }
+  return best;
 }
 
 int launch_mul_ntt(uint32_t* out, const uint32_t* a, int64_t na, const uint32_t* b, int64_t nb, int64_t batch,
-                   int nout, hipStream_t s) {
-  int T, q;
-  if (!ntt_size(na, nb, &T, &q)) return BIGINT_EUNSUPPORTED;
-  switch (T) {
-    case 64: return launch_ntt_t<64, 4, 16>(out, a, na, b, nb, batch, nout, q, s);
-    case 128: return launch_ntt_t<128, 8, 16>(out, a, na, b, nb, batch, nout, q, s);
-    case 256: return launch_ntt_t<256, 16, 16>(out, a, na, b, nb, batch, nout, q, s);
-    case 512: return launch_ntt_t<512, 32, 16>(out, a, na, b, nb, batch, nout, q, s);
-    default: return launch_ntt_t<1024, 32, 32>(out, a, na, b, nb, batch, nout, q, s);
+                   int nout, int pick, hipStream_t s) {
+#define NTT(T, Q, R1, R2) return launch_ntt_size<T, Q, R1, R2>(out, a, na, b, nb, batch, nout, s)
+#define NTT3(Q) return launch_ntt3_size<256, Q, 16, 16>(out, a, na, b, nb, batch, nout, s)
+  if (pick < 0 || pick >= (int)(sizeof(kNtt) / sizeof(kNtt[0])) || na + nb > kNtt[pick].M) return BIGINT_EINVAL;
+  if (kNtt[pick].side) {
+    switch (kNtt[pick].M) {
+      case 2048: NTT3(2);
+      case 3072: NTT3(3);
+      case 4096: NTT3(4);
+      case 5120: NTT3(5);
+      case 6144: NTT3(6);
+      case 7168: NTT3(7);
+      case 8192: NTT3(8);
+    }
+  } else {
+    switch (kNtt[pick].M) {
+      case 1280: NTT(64, 5, 4, 16);
+      case 1536: NTT(64, 6, 4, 16);
+      case 1792: NTT(64, 7, 4, 16);
+      case 2048: NTT(64, 8, 4, 16);
+      case 2560: NTT(128, 5, 8, 16);
+      case 3072: NTT(128, 6, 8, 16);
+      case 5120: NTT(256, 5, 16, 16);
+      case 6144: NTT(256, 6, 16, 16);
+      case 10240: NTT(512, 5, 32, 16);
+      case 12288: NTT(512, 6, 32, 16);
+      case 14336: NTT(512, 7, 32, 16);
+      case 16384: NTT(512, 8, 32, 16);
+      case 20480: NTT(1024, 5, 32, 32);
+      case 24576: NTT(1024, 6, 32, 32);
+      case 28672: NTT(1024, 7, 32, 32);
+      case 32768: NTT(1024, 8, 32, 32);
+    }
   }
+#undef NTT
+#undef NTT3
+  return BIGINT_EUNSUPPORTED;
 }
 
 }  // namespace bi

@@ -57,6 +57,18 @@ def test_full_products(bi, orc, T, n, da, db):
     assert all(np.array_equal(got[i], exp[i]) for i in range(4))
 
 
+@pytest.mark.parametrize("na,nb,batch", [(1280, 1280, 2048), (1536, 1535, 2500), (2560, 2560, 1024), (3072, 3071, 900),
+                                         (2561, 2561, 1024), (1024, 1025, 4096)])
+def test_large_batches(bi, na, nb, batch):
+    """The sizes whose large batches run one prime after another and whose
+    small ones run the primes side by side: the same bytes."""
+    a, b = operands(na * 3 + nb, batch, na, nb)
+    ta, tb = dev(a), dev(b)
+    p = bi.mul(ta, tb)
+    assert bool((p == bi.mul(ta, tb, bi.MUL_MFMA)).all())
+    assert bool((p[:9] == bi.mul(ta[:9].contiguous(), tb[:9].contiguous())).all())
+
+
 @pytest.mark.parametrize("n,batch", [(2048, 2048), (2559, 6), (4096, 5), (5000, 5), (8192, 5), (9999, 4),
                                      (16383, 4), (16384, 5)])
 def test_products_mod_bn(bi, orc, n, batch):
