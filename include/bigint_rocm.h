@@ -251,8 +251,10 @@ int bigint_plan_info(bigint_plan_t plan, int64_t* info, int n);
  * out_off[i+1]-out_off[i] == (a_off[i+1]-a_off[i]) + (b_off[i+1]-b_off[i]);
  * the limb counts must equal those given to bigint_plan_create (not checked
  * on the device).  The instances run largest first, one work-group each, in
- * a few launches (one per run of instances sharing a tile configuration,
- * each also taking some smaller instances to fill its end); the launches are
+ * a few launches (products faster on the transform multiply first, one launch
+ * per family of its kernels; the others one per run of instances sharing a
+ * tile configuration, each also taking some smaller instances to fill its
+ * end); the launches are
  * captured into a hipGraph and replayed on later calls with the same
  * pointers (unless BIGINT_PLAN_NO_GRAPH).  Offsets are DEVICE int64 arrays
  * of length batch+1. */
@@ -273,7 +275,9 @@ int bigint_mul_ragged(uint32_t* out, const int64_t* out_off, const uint32_t* a,
  * first list schedule, [8] work-groups per instance: 1, or the parts of a
  * segment of few instances whose bands are split as bigint_mul splits a
  * small batch (then 4 strips per band and 4 waves, and two launches).  The
- * plan's load-balance figure per launch. */
+ * plan's load-balance figure per launch.  A segment on the transform multiply
+ * reports its own [4], [5], [7] and as [2], [3], [6] what its first instance's
+ * MFMA configuration would be and the digit products that would compute. */
 int bigint_plan_segments(bigint_plan_t plan, int64_t* seg, int max_segments,
                          int* n_segments);
 

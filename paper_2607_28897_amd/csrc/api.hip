@@ -272,13 +272,17 @@ static bool split_forced() { return t_cfg_P || t_cfg_waves || t_cfg_dw || t_cfg_
 // 9 us plus 0.7 of that up to 50 us, where its bands start to be split over
 // the CUs, and a sixth of the rest (measured 12, 14, 24, 41, 69 and 127 us
 // for those sizes; the transform 12, 12, 15, 25, 60 and 108).
+static double mfma_load(int64_t na, int64_t nb, bool low) {
+  return 2.4e-6 * (low ? 0.5 : 1.0) * (double)na * (double)nb + 2.7e-3 * (double)(na + nb);
+}
+
 static int ntt_choice(int64_t na, int64_t nb, int64_t batch, bool low) {
   if (split_forced() || na > BIGINT_MFMA_MAX_LIMBS || nb > BIGINT_MFMA_MAX_LIMBS || std::min(na, nb) < 64)
     return -1;
   double us;
   const int pick = ntt_pick(na, nb, batch, &us);
   if (pick < 0) return -1;
-  const double load = 2.4e-6 * (low ? 0.5 : 1.0) * (double)na * (double)nb + 2.7e-3 * (double)(na + nb);
+  const double load = mfma_load(na, nb, low);
   const double lat = 9.0 + 0.7 * std::min(load, 50.0) + std::max(load - 50.0, 0.0) / 6.0;
   return us <= std::max(lat, load * (double)batch / num_cus()) ? pick : -1;
 }
@@ -539,6 +543,57 @@ static int plan_graph_call(bigint_plan_s* plan, const void* const* key, int nkey
   return BIGINT_OK;
 }
 
+// A ragged plan of fewer products keeps the MFMA multiply, which spreads the
+// bands of each over the CUs.
+constexpr int64_t kNttPlanMin = 16;
+
+// The transform families a ragged plan uses (bit k: kind k), by estimated
+// time over all 16 choices: every family taken is one launch, lasting at
+// least one of its products; the products left to the MFMA multiply run
+// together, lasting at least their largest one, whose bands are split where
+// few are left (measured: 17, 30 and 64 products of 1024 to 16384 limbs 129,
+// 224 and 360 us, of 2000 to 8000 limbs 67, 67 and 132; the four families
+// together 217 and 94 at any of these counts).
+static int ntt_families(const bigint_plan_s* p, const std::vector<NttRagged>& ntt) {
+  struct Sum { double count = 0, load = 0, lat = 0, mfma = 0, mfma_max = 0; } f[kNttFamilies + 1];
+  const double cus = num_cus();
+  for (int64_t i = 0; i < p->batch; ++i) {
+    const double m = mfma_load(p->la[i], p->lb[i], false);
+    Sum& s = f[ntt[i].kind];
+    s.count += 1;
+    s.load += ntt[i].load;
+    s.lat = std::max(s.lat, ntt[i].lat);
+    s.mfma += m;
+    s.mfma_max = std::max(s.mfma_max, m);
+  }
+  int best = 0;
+  double best_us = 0.0;
+  for (int use = 0; use < 1 << kNttFamilies; ++use) {
+    double us = 0.0, count = 0.0, load = 0.0, top = 0.0;
+    for (int k = 0; k <= kNttFamilies; ++k) {
+      if (f[k].count == 0) continue;
+      if (k && (use >> (k - 1) & 1)) {
+        us += std::max(f[k].lat, 0.4 * f[k].lat + f[k].load / cus);
+      } else {
+        count += f[k].count;
+        load += f[k].mfma;
+        top = std::max(top, f[k].mfma_max);
+      }
+    }
+    if (count > 0) {
+      double lat = 0.8 * top;
+      if (top < 50.0) lat = 9.0 + 0.7 * top;
+      else if (4 * count <= cus) lat = std::min(lat, 44.0 + 1.6 * top / std::min(32.0, cus / count));
+      us += std::max(lat, 0.3 * lat + load / cus);
+    }
+    if (use == 0 || us < best_us) {
+      best = use;
+      best_us = us;
+    }
+  }
+  return best << 1;
+}
+
 static int plan_build_mul(bigint_plan_s* p) {
   const int64_t B = p->batch;
   bool plain = (p->flags & BIGINT_PLAN_PLAIN) != 0;
@@ -554,6 +609,24 @@ static int plan_build_mul(bigint_plan_s* p) {
   std::vector<int64_t> idx(B);
   std::iota(idx.begin(), idx.end(), 0);
   std::stable_sort(idx.begin(), idx.end(), [&](int64_t x, int64_t y) { return cost(x) > cost(y); });
+  // Products on the transform multiply come first, by kernel family (largest
+  // transforms first) and then by estimated time.
+  std::vector<NttRagged> ntt(plain ? 0 : B);
+  for (int64_t i = 0; i < B && !plain; ++i)
+    if (std::min(p->la[i], p->lb[i]) >= 64) ntt[i] = ntt_ragged(p->la[i], p->lb[i]);
+  const int use = plain || B < kNttPlanMin ? 0 : ntt_families(p, ntt);
+  int64_t n_ntt = 0;
+  for (auto& r : ntt) {
+    if (!(use >> r.kind & 1)) r.kind = 0;
+    n_ntt += r.kind != 0;
+  }
+  if (n_ntt > 0) {
+    auto rank = [&](int64_t i) { return ntt[i].kind ? ntt[i].kind : 100; };
+    std::stable_sort(idx.begin(), idx.end(), [&](int64_t x, int64_t y) {
+      if (rank(x) != rank(y)) return rank(x) < rank(y);
+      return ntt[x].kind && ntt[x].load > ntt[y].load;
+    });
+  }
   std::vector<QueueItem> q(B);
   if (plain) {
     size_t lds = 0;
@@ -590,7 +663,7 @@ static int plan_build_mul(bigint_plan_s* p) {
       return v;
     };
     std::vector<It> it(B);
-    for (int64_t t = 0; t < B; ++t) {
+    for (int64_t t = n_ntt; t < B; ++t) {
       const int64_t i = idx[t];
       const MfmaCfg c = ragged_mfma_cfg((int)p->la[i], (int)p->lb[i]);
       const size_t l = mfma_lds((int)p->la[i], (int)p->lb[i], c);
@@ -599,6 +672,40 @@ static int plan_build_mul(bigint_plan_s* p) {
     }
     std::vector<RaggedClass> cls;
     int64_t pos = 0;
+    while (pos < n_ntt) {   // one segment per kernel family
+      const int kind = ntt[idx[pos]].kind;
+      const MfmaCfg c0 = ragged_mfma_cfg((int)p->la[idx[pos]], (int)p->lb[idx[pos]]);
+      RaggedClass k{ragged_cfg_id(c0), ntt_ragged_waves(kind), (int)pos, 0, 0};
+      k.ntt = kind;
+      int64_t end = pos, prod = 0;
+      double work = 0.0, span = 0.0;
+      for (; end < n_ntt && ntt[idx[end]].kind == kind; ++end) {
+        const int64_t i = idx[end];
+        q[end] = QueueItem{(int32_t)i, ntt[i].q};
+        k.lds = std::max(k.lds, ntt[i].lds);
+        prod += (c0.dw == 8 ? 4 * p->la[i] : (32 * p->la[i] + 6) / 7) *
+                (c0.dw == 8 ? 4 * p->lb[i] : (32 * p->lb[i] + 6) / 7);
+      }
+      k.count = (int)(end - pos);
+      const int slots = ntt_ragged_slots(kind, k.lds);
+      std::priority_queue<double, std::vector<double>, std::greater<double>> fin;
+      for (int m = 0; m < slots; ++m) fin.push(0.0);
+      for (int64_t t = pos; t < end; ++t) {
+        const double f = fin.top() + ntt[idx[t]].load;
+        fin.pop();
+        fin.push(f);
+        work += ntt[idx[t]].load;
+        span = std::max(span, f);
+      }
+      p->seg_products.push_back(prod);
+      p->seg_busy.push_back(span > 0.0 ? work / ((double)slots * span) : 0.0);
+      p->seg_slots.push_back(slots);
+      BI_DEBUG("bigint: plan segment %zu: %d products from queue position %d by transforms, %d waves, %zu bytes "
+               "of LDS, %d resident work-groups, modelled busy %.3f\n",
+               cls.size(), k.count, k.first, k.waves, k.lds, slots, p->seg_busy.back());
+      cls.push_back(k);
+      pos = end;
+    }
     while (pos < B) {
       const It& h = it[pos];
       RaggedClass k{ragged_cfg_id(h.c), h.c.waves, (int)pos, 0, 0};
@@ -662,7 +769,7 @@ static int plan_build_mul(bigint_plan_s* p) {
     const int R = num_cus();
     int64_t ws_words = 0;
     for (RaggedClass& k : cls) {
-      if ((int64_t)k.count * 4 > R) continue;
+      if (k.ntt || (int64_t)k.count * 4 > R) continue;
       const int dw = k.cfg >= 3 ? 8 : 7;
       int wmax = 0, w0 = 0;
       size_t lmax = 0;

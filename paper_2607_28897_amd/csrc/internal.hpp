@@ -67,7 +67,7 @@ size_t plain_lds(int na, int nb);
 // plain plan is one launch.
 struct QueueItem {
   int32_t inst;
-  int32_t cfg;   // MFMA: strips per band (4, 8, 16) of the instance; plain: 0
+  int32_t cfg;   // MFMA: strips per band (4, 8, 16) of the instance; transform: leaf size; plain: 0
 };
 
 // One launch of a ragged MFMA plan: queue entries [first, first + count), one
@@ -87,7 +87,23 @@ struct RaggedClass {
   int64_t ws_off = 0;
   int wstride = 0;
   size_t split_lds = 0;
+  int ntt = 0;    // kernel family of a transform segment (0: MFMA; cfg then only reports)
 };
+
+// The transform kernel family and leaf size of a ragged instance (kind 0: its
+// operands are too large), what it takes of a CU in a large batch and alone (us).
+struct NttRagged {
+  int kind = 0, q = 0;
+  size_t lds = 0;
+  double load = 0.0, lat = 0.0;
+};
+constexpr int kNttFamilies = 4;   // kinds 1 .. 4
+NttRagged ntt_ragged(int64_t na, int64_t nb);
+int ntt_ragged_slots(int kind, size_t lds);   // work-groups resident on the device at once
+int ntt_ragged_waves(int kind);
+int launch_mul_ntt_ragged(uint32_t* out, const int64_t* out_off, const uint32_t* a, const int64_t* a_off,
+                          const uint32_t* b, const int64_t* b_off, const QueueItem* queue, const RaggedClass& c,
+                          hipStream_t s);
 // strips and part-kernel LDS of one instance of a split ragged segment
 void ragged_split_geo(int na, int nb, int dw, int* strips, size_t* lds);
 

@@ -1051,6 +1051,11 @@ int launch_mul_ragged(uint32_t* out, const int64_t* out_off, const uint32_t* a,
   uint64_t* ws = reinterpret_cast<uint64_t*>(ws_v);
   for (int k = 0; k < ncls; ++k) {
     const RaggedClass& c = cls[k];
+    if (c.ntt) {
+      const int rc = launch_mul_ntt_ragged(out, out_off, a, a_off, b, b_off, queue, c, s);
+      if (rc != BIGINT_OK) return rc;
+      continue;
+    }
     if (c.parts > 1) {
       if (!ws || c.split_lds > 163840) return BIGINT_EINVAL;
       const int rc = c.cfg >= 3 ? launch_ragged_split<8>(c, out, out_off, a, a_off, b, b_off, queue, ws, s)

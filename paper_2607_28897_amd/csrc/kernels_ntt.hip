@@ -128,4 +128,146 @@ int launch_mul_ntt(uint32_t* out, const uint32_t* a, int64_t na, const uint32_t*
   return BIGINT_EUNSUPPORTED;
 }
 
+// ============================================================================
+// ragged batches: one launch per kernel family, its instances in queue order
+// (largest first), one work-group each; the leaf size comes with the queue
+// entry.  The families follow what fits a CU: T = 1024 (one work-group), T =
+// 512 (two), the side-by-side kernels of 5120 to 8192 points (one) and of up
+// to 4096 points (two).
+// ============================================================================
+enum { kRagged1024 = 1, kRagged512, kRaggedSide, kRaggedSideSmall };
+
+template <int KIND>
+struct RaggedFamily;
+template <>
+struct RaggedFamily<kRagged1024> {
+  static constexpr int T = 1024, THREADS = 1024, Q0 = 5, Q1 = 8, R1 = 32, R2 = 32;
+  static constexpr bool SIDE = false;
+};
+template <>
+struct RaggedFamily<kRagged512> {
+  static constexpr int T = 512, THREADS = 512, Q0 = 5, Q1 = 8, R1 = 32, R2 = 16;
+  static constexpr bool SIDE = false;
+};
+template <>
+struct RaggedFamily<kRaggedSide> {
+  static constexpr int T = 256, THREADS = 768, Q0 = 5, Q1 = 8, R1 = 16, R2 = 16;
+  static constexpr bool SIDE = true;
+};
+template <>
+struct RaggedFamily<kRaggedSideSmall> {
+  static constexpr int T = 256, THREADS = 768, Q0 = 2, Q1 = 4, R1 = 16, R2 = 16;
+  static constexpr bool SIDE = true;
+};
+
+template <class F, int Q>
+__device__ __forceinline__ void ragged_one(int q, uint32_t* po, const uint32_t* pa, int na, const uint32_t* pb,
+                                           int nb, int32_t* lds) {
+  if constexpr (Q <= F::Q1) {
+    if (q != Q) {
+      ragged_one<F, Q + 1>(q, po, pa, na, pb, nb, lds);
+    } else {
+      typedef ntt::Size<F::T, Q, F::R1, F::R2> Z;
+      if constexpr (F::SIDE) ntt::wg_mul_ntt3<Z>(po, pa, na, pb, nb, na + nb, lds);
+      else ntt::wg_mul_ntt<Z>(po, pa, na, pb, nb, na + nb, lds);
+    }
+  }
+}
+
+template <int KIND>
+__global__ __launch_bounds__(RaggedFamily<KIND>::THREADS, RaggedFamily<KIND>::SIDE ? 1 : 4) void k_mul_ntt_ragged(
+    uint32_t* out, const int64_t* out_off, const uint32_t* a, const int64_t* a_off, const uint32_t* b,
+    const int64_t* b_off, const QueueItem* queue) {
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  const int64_t i = __builtin_amdgcn_readfirstlane(queue[blockIdx.x].inst);
+  const int q = __builtin_amdgcn_readfirstlane(queue[blockIdx.x].cfg);
+  ragged_one<RaggedFamily<KIND>, RaggedFamily<KIND>::Q0>(
+      q, out + out_off[i], a + a_off[i], (int)(a_off[i + 1] - a_off[i]), b + b_off[i],
+      (int)(b_off[i + 1] - b_off[i]), reinterpret_cast<int32_t*>(smem));
+}
+
+template <class F, int Q>
+static size_t family_lds(int q) {
+  if constexpr (Q > F::Q1) return 0;
+  else if (q != Q) return family_lds<F, Q + 1>(q);
+  else {
+    typedef ntt::Size<F::T, Q, F::R1, F::R2> Z;
+    return F::SIDE ? ntt::ntt3_lds_bytes<Z>() : Z::LDS_BYTES;
+  }
+}
+
+static size_t ragged_lds(int kind, int q) {
+  switch (kind) {
+    case kRagged1024: return family_lds<RaggedFamily<kRagged1024>, 5>(q);
+    case kRagged512: return family_lds<RaggedFamily<kRagged512>, 5>(q);
+    case kRaggedSide: return family_lds<RaggedFamily<kRaggedSide>, 5>(q);
+    default: return family_lds<RaggedFamily<kRaggedSideSmall>, 2>(q);
+  }
+}
+
+static const void* ragged_kernel_ntt(int kind) {
+  switch (kind) {
+    case kRagged1024: return (const void*)k_mul_ntt_ragged<kRagged1024>;
+    case kRagged512: return (const void*)k_mul_ntt_ragged<kRagged512>;
+    case kRaggedSide: return (const void*)k_mul_ntt_ragged<kRaggedSide>;
+    default: return (const void*)k_mul_ntt_ragged<kRaggedSideSmall>;
+  }
+}
+
+static int ragged_threads(int kind) { return kind == kRagged1024 ? 1024 : (kind == kRagged512 ? 512 : 768); }
+
+NttRagged ntt_ragged(int64_t na, int64_t nb) {
+  NttRagged r;
+  const int64_t need = na + nb;
+  if (need > 32768) return r;
+  if (need > 16384) r.kind = kRagged1024, r.q = (int)cdiv(need, 4096);
+  else if (need > 8192) r.kind = kRagged512, r.q = (int)cdiv(need, 2048);
+  else if (need > 4096) r.kind = kRaggedSide, r.q = (int)cdiv(need, 1024);
+  else r.kind = kRaggedSideSmall, r.q = std::max(2, (int)cdiv(need, 1024));
+  r.lds = ragged_lds(r.kind, r.q);
+  const int M = r.q * (r.kind == kRagged1024 ? 4096 : (r.kind == kRagged512 ? 2048 : 1024));
+  for (const NttKernel& k : kNtt)
+    if (k.M == M && k.side == (r.kind >= kRaggedSide)) {
+      r.load = k.load;
+      r.lat = k.lat;
+    }
+  return r;
+}
+
+int ntt_ragged_slots(int kind, size_t lds) {
+  int per_cu = 1;
+  const void* k = ragged_kernel_ntt(kind);
+  if (hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess ||
+      hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k, ragged_threads(kind), lds) != hipSuccess || per_cu < 1)
+    per_cu = 1;
+  return num_cus() * per_cu;
+}
+
+int ntt_ragged_waves(int kind) { return ragged_threads(kind) / 64; }
+
+int launch_mul_ntt_ragged(uint32_t* out, const int64_t* out_off, const uint32_t* a, const int64_t* a_off,
+                          const uint32_t* b, const int64_t* b_off, const QueueItem* queue, const RaggedClass& c,
+                          hipStream_t s) {
+  if (c.count < 1) return BIGINT_OK;
+  const dim3 gd((unsigned)c.count), bd(ragged_threads(c.ntt));
+  BI_HIP(hipFuncSetAttribute(ragged_kernel_ntt(c.ntt), hipFuncAttributeMaxDynamicSharedMemorySize, (int)c.lds));
+  queue += c.first;
+  switch (c.ntt) {
+    case kRagged1024:
+      hipLaunchKernelGGL(k_mul_ntt_ragged<kRagged1024>, gd, bd, c.lds, s, out, out_off, a, a_off, b, b_off, queue);
+      break;
+    case kRagged512:
+      hipLaunchKernelGGL(k_mul_ntt_ragged<kRagged512>, gd, bd, c.lds, s, out, out_off, a, a_off, b, b_off, queue);
+      break;
+    case kRaggedSide:
+      hipLaunchKernelGGL(k_mul_ntt_ragged<kRaggedSide>, gd, bd, c.lds, s, out, out_off, a, a_off, b, b_off, queue);
+      break;
+    default:
+      hipLaunchKernelGGL(k_mul_ntt_ragged<kRaggedSideSmall>, gd, bd, c.lds, s, out, out_off, a, a_off, b, b_off,
+                         queue);
+  }
+  BI_LAUNCH_CHECK();
+  return BIGINT_OK;
+}
+
 }  // namespace bi

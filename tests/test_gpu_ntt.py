@@ -92,6 +92,39 @@ def test_unequal_operands(bi, orc, na, nb):
     assert all(np.array_equal(got[i], exp[i]) for i in range(4))
 
 
+@pytest.mark.parametrize("flags", [0, 2])
+def test_ragged_unequal(bi, flags):
+    """A plan over every transform family and leaf size, operands of unequal
+    lengths at odd offsets, against the plain kernel's plan; graph replays and
+    direct launches."""
+    import torch
+    g = np.random.default_rng(17)
+    la = np.exp(g.uniform(np.log(600), np.log(16384), 700)).astype(np.int64)
+    lb = np.maximum(64, (la * g.uniform(0.5, 1.0, 700)).astype(np.int64))
+    edges = [1024, 1536, 2048, 2560, 3072, 3584, 4096, 5120, 6144, 7168, 8192, 10240, 12288, 14336, 16384]
+    for k, n in enumerate(edges):
+        la[2 * k:2 * k + 2] = n
+        lb[2 * k:2 * k + 2] = [n, n - 1]
+    off = [np.zeros(701, np.int64) for _ in range(2)]
+    for o, n in zip(off, (la, lb)):
+        np.cumsum(n, out=o[1:])
+    a, b = (rand_limbs(g, int(o[-1])) for o in off)
+    a[: off[0][20]] = 0xFFFFFFFF
+    b[: off[1][20]] = 0xFFFFFFFF
+    ta, tb = dev(a), dev(b)
+    oa, ob = (torch.from_numpy(o).cuda() for o in off)
+    plan, plain = bi.MulPlan(la, lb, flags), bi.MulPlan(la, lb, bi.PLAN_PLAIN)
+    assert len(plan.segments()) >= 4
+    want, oo = plain(ta, oa, tb, ob)
+    out = torch.empty_like(want)
+    for _ in range(3):
+        out.fill_(-1)
+        plan(ta, oa, tb, ob, out=out, out_off=oo)
+        assert bool((out == want).all())
+    plan.close()
+    plain.close()
+
+
 def test_graph_capture(bi):
     """A call with no workspace: captured and replayed, eager work between."""
     import torch
