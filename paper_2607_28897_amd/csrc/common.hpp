@@ -44,6 +44,16 @@ __device__ __forceinline__ int lane_id() { return threadIdx.x & 63; }
 __device__ __forceinline__ int wave_id() { return threadIdx.x >> 6; }
 __device__ __forceinline__ int num_waves() { return blockDim.x >> 6; }
 
+// Four limbs at any limb address: one 16-byte access (gfx950 takes 4-byte
+// aligned ones; rows of odd length need it on three rows of four)
+struct __attribute__((packed, aligned(4))) Limb4 {
+  uint32_t x, y, z, w;
+};
+__device__ __forceinline__ Limb4 load4(const uint32_t* p) { return *reinterpret_cast<const Limb4*>(p); }
+__device__ __forceinline__ void store4(uint32_t* p, uint32_t x, uint32_t y, uint32_t z, uint32_t w) {
+  *reinterpret_cast<Limb4*>(p) = Limb4{x, y, z, w};
+}
+
 // Floor / ceiling division of a (possibly negative) int by a positive int.
 __device__ __forceinline__ int floor_div(int a, int b) {
   int q = a / b;

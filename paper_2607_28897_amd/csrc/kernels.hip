@@ -9,10 +9,13 @@ namespace bi {
 
 // ============================================================================
 // add / sub: one work-group per instance, Q consecutive limbs per thread
-// loaded with 16-byte vector loads (Section 5.1: badd copies the operands
-// from global memory into registers, baddReg scans the per-thread carries).
+// read and written with 16-byte accesses at any limb address (Section 5.1:
+// badd copies the operands from global memory into registers, baddReg scans
+// the per-thread carries).  Bound: HBM.  Rows of odd length used to go limb by
+// limb, Q limbs apart in each access: 4096 x 8191 limbs 187 us, 2.1 TB/s; now
+// 78 us, 5.1 TB/s, what a plain copy reaches.
 // ============================================================================
-template <int Q, bool SUB, bool VEC>
+template <int Q, bool SUB>
 __global__ __launch_bounds__(1024) void k_addsub(uint32_t* out, uint32_t* cout, const uint32_t* a,
                                                  const uint32_t* b, int n) {
   __shared__ uint32_t scratch[32];
@@ -24,11 +27,10 @@ __global__ __launch_bounds__(1024) void k_addsub(uint32_t* out, uint32_t* cout, 
   const int valid = min(Q, max(0, n - j0));
   LimbRun<Q, SUB> run;
   run.start();
-  if (VEC && valid == Q) {
+  if (valid == Q) {
 #pragma unroll
     for (int i = 0; i < Q; i += 4) {
-      const uint4 va = *reinterpret_cast<const uint4*>(pa + j0 + i);
-      const uint4 vb = *reinterpret_cast<const uint4*>(pb + j0 + i);
+      const Limb4 va = load4(pa + j0 + i), vb = load4(pb + j0 + i);
       run.set(i, va.x, vb.x, true);
       run.set(i + 1, va.y, vb.y, true);
       run.set(i + 2, va.z, vb.z, true);
@@ -45,11 +47,9 @@ __global__ __launch_bounds__(1024) void k_addsub(uint32_t* out, uint32_t* cout, 
   uint32_t total;
   const uint32_t c = wg_carry_scan(run.G, run.P, 0u, scratch, &total);
   run.apply(c);
-  if (VEC && valid == Q) {
+  if (valid == Q) {
 #pragma unroll
-    for (int i = 0; i < Q; i += 4)
-      *reinterpret_cast<uint4*>(po + j0 + i) =
-          make_uint4(run.s[i], run.s[i + 1], run.s[i + 2], run.s[i + 3]);
+    for (int i = 0; i < Q; i += 4) store4(po + j0 + i, run.s[i], run.s[i + 1], run.s[i + 2], run.s[i + 3]);
   } else {
 #pragma unroll
     for (int i = 0; i < Q; ++i)
@@ -58,31 +58,57 @@ __global__ __launch_bounds__(1024) void k_addsub(uint32_t* out, uint32_t* cout, 
   if (cout && threadIdx.x == 0) cout[inst] = total;
 }
 
-template <bool SUB>
-__global__ __launch_bounds__(1024) void k_addsub_rounds(uint32_t* out, uint32_t* cout,
-                                                        const uint32_t* a, const uint32_t* b, int n) {
+// Instances of more than 16 limbs per thread: rounds of 1024 Q limbs, the
+// carry chained, each read and written as above (40,001 limbs: 1.2 -> 4.1
+// TB/s against limb-by-limb accesses).
+template <int Q, bool SUB>
+__global__ __launch_bounds__(1024) void k_addsub_rounds(uint32_t* out, uint32_t* cout, const uint32_t* a,
+                                                        const uint32_t* b, int n) {
   __shared__ uint32_t scratch[32];
   const int64_t inst = blockIdx.x;
   const uint32_t* pa = a + inst * n;
   const uint32_t* pb = b + inst * n;
-  auto X = [&](int j) -> uint32_t { return pa[j]; };
-  auto Y = [&](int j) -> uint32_t { return pb[j]; };
-  const uint32_t c = wg_addsub<16, SUB>(out + inst * n, n, X, Y, 0u, scratch);
-  if (cout && threadIdx.x == 0) cout[inst] = c;
+  uint32_t* po = out + inst * n;
+  uint32_t carry = 0u;
+  for (int base = 0; base < n; base += 1024 * Q) {
+    const int j0 = base + threadIdx.x * Q;
+    const int valid = min(Q, max(0, n - j0));
+    LimbRun<Q, SUB> run;
+    run.start();
+    if (valid == Q) {
+#pragma unroll
+      for (int i = 0; i < Q; i += 4) {
+        const Limb4 va = load4(pa + j0 + i), vb = load4(pb + j0 + i);
+        run.set(i, va.x, vb.x, true);
+        run.set(i + 1, va.y, vb.y, true);
+        run.set(i + 2, va.z, vb.z, true);
+        run.set(i + 3, va.w, vb.w, true);
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < Q; ++i) run.set(i, i < valid ? pa[j0 + i] : 0u, i < valid ? pb[j0 + i] : 0u, i < valid);
+    }
+    run.finish();
+    uint32_t next;
+    run.apply(wg_carry_scan(run.G, run.P, carry, scratch, &next));
+    carry = next;
+    if (valid == Q) {
+#pragma unroll
+      for (int i = 0; i < Q; i += 4) store4(po + j0 + i, run.s[i], run.s[i + 1], run.s[i + 2], run.s[i + 3]);
+    } else {
+#pragma unroll
+      for (int i = 0; i < Q; ++i)
+        if (i < valid) po[j0 + i] = run.s[i];
+    }
+  }
+  if (cout && threadIdx.x == 0) cout[inst] = carry;
 }
 
 template <int Q, bool SUB>
 static int launch_addsub_q(uint32_t* out, uint32_t* cout, const uint32_t* a, const uint32_t* b,
                            int64_t n, int64_t batch, hipStream_t s) {
   const int T = (int)((cdiv(n, Q) + 63) / 64 * 64);
-  const bool vec = (n % 4 == 0) && ((uintptr_t)a % 16 == 0) && ((uintptr_t)b % 16 == 0) &&
-                   ((uintptr_t)out % 16 == 0);
-  if (vec)
-    hipLaunchKernelGGL((k_addsub<Q, SUB, true>), dim3((unsigned)batch), dim3(T), 0, s, out, cout, a,
-                       b, (int)n);
-  else
-    hipLaunchKernelGGL((k_addsub<Q, SUB, false>), dim3((unsigned)batch), dim3(T), 0, s, out, cout,
-                       a, b, (int)n);
+  hipLaunchKernelGGL((k_addsub<Q, SUB>), dim3((unsigned)batch), dim3(T), 0, s, out, cout, a, b, (int)n);
   BI_LAUNCH_CHECK();
   return BIGINT_OK;
 }
@@ -96,7 +122,7 @@ static int launch_addsub_q(uint32_t* out, uint32_t* cout, const uint32_t* a, con
 // instance's) comes from its run summary and its carry in.  STEPS = 1: one
 // addition (or subtraction); STEPS = 6: the 6-Add chain a+b+a+b+a+b+a with
 // the carries out counted.
-template <int Q, bool SUB, int STEPS, bool VEC>
+template <int Q, bool SUB, int STEPS>
 __global__ __launch_bounds__(256) void k_addsub_ipb(uint32_t* out, uint32_t* cout, const uint32_t* a,
                                                     const uint32_t* b, int n, int L, int ipw,
                                                     int64_t batch) {
@@ -108,11 +134,10 @@ __global__ __launch_bounds__(256) void k_addsub_ipb(uint32_t* out, uint32_t* cou
   const int valid = live ? min(Q, max(0, n - j0)) : 0;
   const int64_t base = live ? inst * (int64_t)n : 0;
   uint32_t av[Q], bv[Q], x[Q];
-  if (VEC && valid == Q) {
+  if (valid == Q) {
 #pragma unroll
     for (int i = 0; i < Q; i += 4) {
-      const uint4 va = *reinterpret_cast<const uint4*>(a + base + j0 + i);
-      const uint4 vb = *reinterpret_cast<const uint4*>(b + base + j0 + i);
+      const Limb4 va = load4(a + base + j0 + i), vb = load4(b + base + j0 + i);
       av[i] = va.x; av[i + 1] = va.y; av[i + 2] = va.z; av[i + 3] = va.w;
       bv[i] = vb.x; bv[i + 1] = vb.y; bv[i + 2] = vb.z; bv[i + 3] = vb.w;
     }
@@ -139,10 +164,9 @@ __global__ __launch_bounds__(256) void k_addsub_ipb(uint32_t* out, uint32_t* cou
     for (int i = 0; i < Q; ++i) x[i] = run.s[i];
     total += (uint32_t)(run.G | (run.P & (c != 0u)));
   }
-  if (VEC && valid == Q) {
+  if (valid == Q) {
 #pragma unroll
-    for (int i = 0; i < Q; i += 4)
-      *reinterpret_cast<uint4*>(out + base + j0 + i) = make_uint4(x[i], x[i + 1], x[i + 2], x[i + 3]);
+    for (int i = 0; i < Q; i += 4) store4(out + base + j0 + i, x[i], x[i + 1], x[i + 2], x[i + 3]);
   } else {
 #pragma unroll
     for (int i = 0; i < Q; ++i)
@@ -161,14 +185,7 @@ static int launch_addsub_ipb(uint32_t* out, uint32_t* cout, const uint32_t* a, c
   const int ipw = 64 / L;
   const int64_t per_wg = 4 * (int64_t)ipw;
   const dim3 gd((unsigned)((batch + per_wg - 1) / per_wg)), bd(256);
-  const bool vec = (n % 4 == 0) && ((uintptr_t)a % 16 == 0) && ((uintptr_t)b % 16 == 0) &&
-                   ((uintptr_t)out % 16 == 0);
-  if (vec)
-    hipLaunchKernelGGL((k_addsub_ipb<kIpbQ, SUB, STEPS, true>), gd, bd, 0, s, out, cout, a, b,
-                       (int)n, L, ipw, batch);
-  else
-    hipLaunchKernelGGL((k_addsub_ipb<kIpbQ, SUB, STEPS, false>), gd, bd, 0, s, out, cout, a, b,
-                       (int)n, L, ipw, batch);
+  hipLaunchKernelGGL((k_addsub_ipb<kIpbQ, SUB, STEPS>), gd, bd, 0, s, out, cout, a, b, (int)n, L, ipw, batch);
   BI_LAUNCH_CHECK();
   return BIGINT_OK;
 }
@@ -193,10 +210,9 @@ static int launch_addsub_t(uint32_t* out, uint32_t* cout, const uint32_t* a, con
   }
   if (n <= 8192) return launch_addsub_q<8, SUB>(out, cout, a, b, n, batch, s);
   if (n <= 16384) return launch_addsub_q<16, SUB>(out, cout, a, b, n, batch, s);
-  if (n <= 32768) return launch_addsub_q<32, SUB>(out, cout, a, b, n, batch, s);
-  // beyond 1024 threads x 32 limbs: rounds of the work-group add, carry chained
-  hipLaunchKernelGGL((k_addsub_rounds<SUB>), dim3((unsigned)batch), dim3(1024), 0, s, out, cout, a,
-                     b, (int)n);
+  // beyond 1024 threads x 16 limbs: rounds, carry chained (32 limbs a thread
+  // instead measured 3.4 TB/s at 20,001 and 32,768 limbs)
+  hipLaunchKernelGGL((k_addsub_rounds<16, SUB>), dim3((unsigned)batch), dim3(1024), 0, s, out, cout, a, b, (int)n);
   BI_LAUNCH_CHECK();
   return BIGINT_OK;
 }
@@ -512,7 +528,7 @@ int launch_mul_mfma(uint32_t* out, int32_t* coef, const uint32_t* a, int64_t na,
 // 6-Add: ((((((a+b)+a)+b)+a)+b)+a) mod B^n with the operands and the running
 // sum in registers: one HBM pass (read a, b; write the result), six
 // work-group carry scans.  ovf[i] = how many of the six additions carried out.
-template <int Q, bool VEC>
+template <int Q>
 __global__ __launch_bounds__(1024) void k_add6(uint32_t* out, uint32_t* ovf, const uint32_t* a,
                                                const uint32_t* b, int n) {
   __shared__ uint32_t scratch[32];
@@ -523,11 +539,10 @@ __global__ __launch_bounds__(1024) void k_add6(uint32_t* out, uint32_t* ovf, con
   const int j0 = threadIdx.x * Q;
   const int valid = min(Q, max(0, n - j0));
   uint32_t av[Q], bv[Q], x[Q];
-  if (VEC && valid == Q) {
+  if (valid == Q) {
 #pragma unroll
     for (int i = 0; i < Q; i += 4) {
-      const uint4 va = *reinterpret_cast<const uint4*>(pa + j0 + i);
-      const uint4 vb = *reinterpret_cast<const uint4*>(pb + j0 + i);
+      const Limb4 va = load4(pa + j0 + i), vb = load4(pb + j0 + i);
       av[i] = va.x; av[i + 1] = va.y; av[i + 2] = va.z; av[i + 3] = va.w;
       bv[i] = vb.x; bv[i + 1] = vb.y; bv[i + 2] = vb.z; bv[i + 3] = vb.w;
     }
@@ -553,10 +568,9 @@ __global__ __launch_bounds__(1024) void k_add6(uint32_t* out, uint32_t* ovf, con
     for (int i = 0; i < Q; ++i) x[i] = run.s[i];
     total += cout;
   }
-  if (VEC && valid == Q) {
+  if (valid == Q) {
 #pragma unroll
-    for (int i = 0; i < Q; i += 4)
-      *reinterpret_cast<uint4*>(po + j0 + i) = make_uint4(x[i], x[i + 1], x[i + 2], x[i + 3]);
+    for (int i = 0; i < Q; i += 4) store4(po + j0 + i, x[i], x[i + 1], x[i + 2], x[i + 3]);
   } else {
 #pragma unroll
     for (int i = 0; i < Q; ++i)
@@ -569,14 +583,7 @@ template <int Q>
 static int launch_add6_q(uint32_t* out, uint32_t* ovf, const uint32_t* a, const uint32_t* b,
                          int64_t n, int64_t batch, hipStream_t s) {
   const int T = (int)((cdiv(n, Q) + 63) / 64 * 64);
-  const bool vec = (n % 4 == 0) && ((uintptr_t)a % 16 == 0) && ((uintptr_t)b % 16 == 0) &&
-                   ((uintptr_t)out % 16 == 0);
-  if (vec)
-    hipLaunchKernelGGL((k_add6<Q, true>), dim3((unsigned)batch), dim3(T), 0, s, out, ovf, a, b,
-                       (int)n);
-  else
-    hipLaunchKernelGGL((k_add6<Q, false>), dim3((unsigned)batch), dim3(T), 0, s, out, ovf, a, b,
-                       (int)n);
+  hipLaunchKernelGGL(k_add6<Q>, dim3((unsigned)batch), dim3(T), 0, s, out, ovf, a, b, (int)n);
   BI_LAUNCH_CHECK();
   return BIGINT_OK;
 }

@@ -142,3 +142,29 @@ def test_batches_of_two_to_four_groups_per_cu(bi, orc, n):
     b[1::5] = 0
     b[1::5, 0] = 1
     _check(bi, orc, a, b)
+
+
+@pytest.mark.parametrize("n", [5, 255, 257, 1023, 2049, 4095, 8191, 16381, 32769, 49153])
+@pytest.mark.parametrize("shift", [0, 1, 3])
+def test_rows_at_any_limb_address(bi, orc, n, shift):
+    """Operands, results and rows that start at addresses not a multiple of 16
+    bytes (16-byte accesses at every limb address), in place as well; the
+    limbs before and after the result stay as they were."""
+    import torch
+    g = np.random.default_rng(n + shift)
+    a, b = rand_limbs(g, 3, n), rand_limbs(g, 3, n)
+    a[1], b[1] = 0xFFFFFFFF, 0
+    b[1, 0] = 1
+    def at(x, k):
+        t = torch.full((3 * n + 8,), 77, dtype=torch.int32, device="cuda")
+        t[k:k + 3 * n] = dev(x).view(-1)
+        return t, t[k:k + 3 * n].view(3, n)
+    _, ta = at(a, shift)
+    _, tb = at(b, (shift + 2) % 4)
+    whole, to = at(a, (shift + 1) % 4)
+    bi.sub(ta, tb, out=to)
+    assert np.array_equal(host(to), orc.sub(a, b)[0])
+    k = (shift + 1) % 4
+    assert bool((whole[:k] == 77).all()) and bool((whole[k + 3 * n:] == 77).all())
+    bi.add(ta, tb, out=ta)
+    assert np.array_equal(host(ta), orc.add(a, b)[0])
