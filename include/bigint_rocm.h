@@ -156,6 +156,17 @@ int bigint_sub(uint32_t* out, uint32_t* borrow_out, const uint32_t* a,
 int bigint_mul(uint32_t* out, const uint32_t* a, int64_t na, const uint32_t* b,
                int64_t nb, int64_t batch, int algo, void* stream);
 
+/* bigint_mul_ws: bigint_mul (same arguments, results and errors) with a
+ * workspace the caller provides, which lets AUTO spread each of a few large
+ * products over many work-groups.  bigint_mul_workspace_size reports the bytes
+ * that a batch can use (0: none); with fewer the call runs as bigint_mul.
+ * ws: device memory, 16-byte aligned, not overlapping the operands or the
+ * product, free again once the stream has passed the call. */
+int bigint_mul_workspace_size(int64_t na, int64_t nb, int64_t batch, size_t* bytes);
+int bigint_mul_ws(uint32_t* out, const uint32_t* a, int64_t na, const uint32_t* b,
+                  int64_t nb, int64_t batch, int algo, void* ws, size_t ws_bytes,
+                  void* stream);
+
 /* ---- fixed-precision product and the evaluation's fused workloads (Section 6) ---
  * bigint_mullo: out[i] = a[i] * b[i] mod B^n (B = 2^32), the paper's
  *   multiplication, whose quadratic formula keeps only digits k < n
@@ -182,6 +193,10 @@ int bigint_mul(uint32_t* out, const uint32_t* a, int64_t na, const uint32_t* b,
  *   BIGINT_MFMA_MAX_LIMBS; out must not overlap a or b. */
 int bigint_mullo(uint32_t* out, const uint32_t* a, const uint32_t* b, int64_t n,
                  int64_t batch, void* stream);
+/* bigint_mullo with a caller's workspace, as bigint_mul_ws (its size: that of
+ * an n x n product). */
+int bigint_mullo_ws(uint32_t* out, const uint32_t* a, const uint32_t* b, int64_t n,
+                    int64_t batch, void* ws, size_t ws_bytes, void* stream);
 int bigint_add6(uint32_t* out, uint32_t* overflow, const uint32_t* a,
                 const uint32_t* b, int64_t n, int64_t batch, void* stream);
 int bigint_poly(uint32_t* out, const uint32_t* a, const uint32_t* b, int64_t n,

@@ -73,6 +73,9 @@ def lib() -> ctypes.CDLL:
             "bigint_add": ([_vp, _vp, _vp, _vp, _i64, _i64, _vp], _int),
             "bigint_sub": ([_vp, _vp, _vp, _vp, _i64, _i64, _vp], _int),
             "bigint_mul": ([_vp, _vp, _i64, _vp, _i64, _i64, _int, _vp], _int),
+            "bigint_mul_ws": ([_vp, _vp, _i64, _vp, _i64, _i64, _int, _vp, ctypes.c_size_t, _vp], _int),
+            "bigint_mul_workspace_size": ([_i64, _i64, _i64, ctypes.POINTER(ctypes.c_size_t)], _int),
+            "bigint_mullo_ws": ([_vp, _vp, _vp, _i64, _i64, _vp, ctypes.c_size_t, _vp], _int),
             "bigint_divmod": ([_vp, _vp, _vp, _vp, _i64, _vp, _i64, _i64, _vp], _int),
             "bigint_divmod_noalloc": ([_vp, _vp, _vp, _vp, _i64, _vp, _i64, _i64, _vp], _int),
             "bigint_plan_create": ([ctypes.POINTER(_vp), _int, _vp, _vp, _i64, _int], _int),
@@ -185,6 +188,23 @@ def _addsub(fn, a, b, out, what):
     return _back(out, wd), carry
 
 
+def _mul_ws(na, nb, batch, device):
+    """A workspace from torch's allocator for products that take one (ordered
+    on the current stream like every tensor), else None, and its size.  With
+    no memory left for it the product runs without."""
+    if na + nb <= 8192:
+        return None, 0
+    n = ctypes.c_size_t()
+    _check(lib().bigint_mul_workspace_size(na, nb, batch, ctypes.byref(n)), "bigint_mul_workspace_size")
+    if n.value == 0:
+        return None, 0
+    torch = _torch()
+    try:
+        return torch.empty(n.value, dtype=torch.uint8, device=device), n.value
+    except torch.cuda.OutOfMemoryError:
+        return None, 0
+
+
 def mul(a, b, algo: int = MUL_AUTO):
     """Full products a * b row by row: [batch, na] x [batch, nb] -> [batch, na+nb]."""
     torch = _torch()
@@ -195,7 +215,11 @@ def mul(a, b, algo: int = MUL_AUTO):
     if ba != bb:
         raise ValueError("batch mismatch")
     out = torch.empty((ba, na + nb), dtype=a.dtype, device=a.device)
-    _check(lib().bigint_mul(_p(out), _p(a), na, _p(b), nb, ba, algo, _stream()), "bigint_mul")
+    ws, size = _mul_ws(na, nb, ba, a.device) if algo == MUL_AUTO else (None, 0)
+    if ws is not None:
+        _check(lib().bigint_mul_ws(_p(out), _p(a), na, _p(b), nb, ba, algo, _p(ws), size, _stream()), "bigint_mul")
+    else:
+        _check(lib().bigint_mul(_p(out), _p(a), na, _p(b), nb, ba, algo, _stream()), "bigint_mul")
     return _back(out if a.dim() == 2 else out.view(-1), wd)
 
 
@@ -264,7 +288,11 @@ def mullo(a, b):
     if ba != bb or n != nb:
         raise ValueError("shape mismatch")
     out = torch.empty((ba, n), dtype=a.dtype, device=a.device)
-    _check(lib().bigint_mullo(_p(out), _p(a), _p(b), n, ba, _stream()), "bigint_mullo")
+    ws, size = _mul_ws(n, n, ba, a.device)
+    if ws is not None:
+        _check(lib().bigint_mullo_ws(_p(out), _p(a), _p(b), n, ba, _p(ws), size, _stream()), "bigint_mullo")
+    else:
+        _check(lib().bigint_mullo(_p(out), _p(a), _p(b), n, ba, _stream()), "bigint_mullo")
     return _back(out if a.dim() == 2 else out.view(-1), wd)
 
 

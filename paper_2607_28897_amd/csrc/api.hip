@@ -271,20 +271,37 @@ static bool split_forced() { return t_cfg_P || t_cfg_waves || t_cfg_dw || t_cfg_
 // transform takes 3.9, 5.8, 10, 26, 53 and 122 there), and one product alone
 // 9 us plus 0.7 of that up to 50 us, where its bands start to be split over
 // the CUs, and a sixth of the rest (measured 12, 14, 24, 41, 69 and 127 us
-// for those sizes; the transform 12, 12, 15, 25, 60 and 108).
+// for those sizes; the transform 12, 12, 15, 25, 60 and 108, with its
+// quarters apart 18 and 24 for the last two).  The estimates are good to some
+// 10 %, so the transform is taken where it is ahead by more than that.
 static double mfma_load(int64_t na, int64_t nb, bool low) {
   return 2.4e-6 * (low ? 0.5 : 1.0) * (double)na * (double)nb + 2.7e-3 * (double)(na + nb);
 }
 
-static int ntt_choice(int64_t na, int64_t nb, int64_t batch, bool low) {
+constexpr int kNttQuarters = 1000;   // ntt_choice: the quarters apart
+
+static int ntt_choice(int64_t na, int64_t nb, int64_t batch, bool low, size_t ws_bytes) {
   if (split_forced() || na > BIGINT_MFMA_MAX_LIMBS || nb > BIGINT_MFMA_MAX_LIMBS || std::min(na, nb) < 64)
     return -1;
   double us;
-  const int pick = ntt_pick(na, nb, batch, &us);
+  int pick = ntt_pick(na, nb, batch, &us);
   if (pick < 0) return -1;
+  const double quarters = ntt_quarters_us(na, nb, batch);
+  if (quarters < us && ws_bytes >= ntt_quarters_ws(na, nb, batch)) {
+    pick = kNttQuarters;
+    us = quarters;
+  }
   const double load = mfma_load(na, nb, low);
   const double lat = 9.0 + 0.7 * std::min(load, 50.0) + std::max(load - 50.0, 0.0) / 6.0;
-  return us <= std::max(lat, load * (double)batch / num_cus()) ? pick : -1;
+  return us <= 0.92 * std::max(lat, load * (double)batch / num_cus()) ? pick : -1;
+}
+
+static int mul_ntt(uint32_t* out, const uint32_t* a, int64_t na, const uint32_t* b, int64_t nb, int nout,
+                   int64_t batch, int pick, void* ws, hipStream_t s) {
+  BI_DEBUG("bigint: mul %lld x (%lld x %lld limbs): transforms modulo three primes%s\n", (long long)batch,
+           (long long)na, (long long)nb, pick == kNttQuarters ? ", quarters apart" : "");
+  return pick == kNttQuarters ? launch_mul_ntt_quarters(out, a, na, b, nb, batch, nout, ws, s)
+                              : launch_mul_ntt(out, a, na, b, nb, batch, nout, pick, s);
 }
 
 // products of a small batch with each product's bands split over `parts`
@@ -302,8 +319,8 @@ static int mul_split(uint32_t* out, const uint32_t* a, int64_t na, const uint32_
   return BIGINT_OK;
 }
 
-int bigint_mul(uint32_t* out, const uint32_t* a, int64_t na, const uint32_t* b, int64_t nb,
-               int64_t batch, int algo, void* stream) {
+static int mul_any(uint32_t* out, const uint32_t* a, int64_t na, const uint32_t* b, int64_t nb, int64_t batch,
+                   int algo, void* ws, size_t ws_bytes, void* stream) {
   if (!out || !a || !b || na <= 0 || nb <= 0 || batch < 0) return BIGINT_EINVAL;
   if (algo != BIGINT_MUL_AUTO && algo != BIGINT_MUL_PLAIN && algo != BIGINT_MUL_MFMA &&
       algo != BIGINT_MUL_KARATSUBA)
@@ -333,12 +350,10 @@ int bigint_mul(uint32_t* out, const uint32_t* a, int64_t na, const uint32_t* b, 
     if (e != hipSuccess) { set_hip_error(e); return BIGINT_EHIP; }
     return BIGINT_OK;
   }
-  const int ntt = algo == BIGINT_MUL_AUTO ? ntt_choice(na, nb, batch, false) : -1;
+  const int ntt = algo == BIGINT_MUL_AUTO ? ntt_choice(na, nb, batch, false, ws_bytes) : -1;
   if (ntt >= 0) {
     if (batch == 0) return BIGINT_OK;
-    BI_DEBUG("bigint: mul %lld x (%lld x %lld limbs): transforms modulo three primes\n", (long long)batch,
-             (long long)na, (long long)nb);
-    return launch_mul_ntt(out, a, na, b, nb, batch, (int)(na + nb), ntt, (hipStream_t)stream);
+    return mul_ntt(out, a, na, b, nb, (int)(na + nb), batch, ntt, ws, (hipStream_t)stream);
   }
   const MfmaCfg cfg = uniform_mfma_cfg((int)na, (int)nb, batch, false);
   int use = algo;
@@ -367,6 +382,29 @@ int bigint_mul(uint32_t* out, const uint32_t* a, int64_t na, const uint32_t* b, 
   return launch_mul_plain(out, a, na, b, nb, batch, (hipStream_t)stream);
 }
 
+int bigint_mul(uint32_t* out, const uint32_t* a, int64_t na, const uint32_t* b, int64_t nb, int64_t batch,
+               int algo, void* stream) {
+  return mul_any(out, a, na, b, nb, batch, algo, nullptr, 0, stream);
+}
+
+int bigint_mul_ws(uint32_t* out, const uint32_t* a, int64_t na, const uint32_t* b, int64_t nb, int64_t batch,
+                  int algo, void* ws, size_t ws_bytes, void* stream) {
+  if ((!ws && ws_bytes) || ((uintptr_t)ws & 15)) return BIGINT_EINVAL;
+  if (na > 0 && nb > 0 && batch > 0 && na <= (1 << 20) && nb <= (1 << 20) && batch <= 0x7fffffff &&
+      (overlap(ws, ws_bytes, out, (size_t)(na + nb) * batch * 4) || overlap(ws, ws_bytes, a, (size_t)na * batch * 4) ||
+       overlap(ws, ws_bytes, b, (size_t)nb * batch * 4)))
+    return BIGINT_EINVAL;
+  return mul_any(out, a, na, b, nb, batch, algo, ws, ws_bytes, stream);
+}
+
+int bigint_mul_workspace_size(int64_t na, int64_t nb, int64_t batch, size_t* bytes) {
+  if (na <= 0 || nb <= 0 || batch < 0 || !bytes) return BIGINT_EINVAL;
+  *bytes = 0;
+  if (batch > 0 && batch <= 0x7fffffff && ntt_choice(na, nb, batch, false, SIZE_MAX) == kNttQuarters)
+    *bytes = ntt_quarters_ws(na, nb, batch);
+  return BIGINT_OK;
+}
+
 int bigint_mfma_split_parts(int64_t na, int64_t nb, int64_t batch, int* parts) {
   if (na <= 0 || nb <= 0 || batch < 1 || !parts) return BIGINT_EINVAL;
   *parts = 1;
@@ -378,16 +416,16 @@ int bigint_mfma_split_parts(int64_t na, int64_t nb, int64_t batch, int* parts) {
   return BIGINT_OK;
 }
 
-int bigint_mullo(uint32_t* out, const uint32_t* a, const uint32_t* b, int64_t n, int64_t batch,
-                 void* stream) {
+static int mullo_any(uint32_t* out, const uint32_t* a, const uint32_t* b, int64_t n, int64_t batch, void* ws,
+                     size_t ws_bytes, void* stream) {
   if (!out || !a || !b || n <= 0 || batch < 0) return BIGINT_EINVAL;
   if (batch > 0x7fffffff || n > BIGINT_MFMA_MAX_LIMBS) return BIGINT_EUNSUPPORTED;
   const size_t bytes = (size_t)n * batch * 4;
   if (overlap(out, bytes, a, bytes) || overlap(out, bytes, b, bytes)) return BIGINT_EINVAL;
-  const int ntt = ntt_choice(n, n, batch, true);
+  const int ntt = ntt_choice(n, n, batch, true, ws_bytes);
   if (ntt >= 0) {
     if (batch == 0) return BIGINT_OK;
-    return launch_mul_ntt(out, a, n, b, n, batch, (int)n, ntt, (hipStream_t)stream);
+    return mul_ntt(out, a, n, b, n, (int)n, batch, ntt, ws, (hipStream_t)stream);
   }
   const MfmaCfg cfg = uniform_mfma_cfg((int)n, (int)n, batch, true);
   if (!mfma_fits(n, n, cfg)) return BIGINT_EUNSUPPORTED;
@@ -396,6 +434,21 @@ int bigint_mullo(uint32_t* out, const uint32_t* a, const uint32_t* b, int64_t n,
   const int parts = split_forced() ? 1 : mul_mfma_split_parts((int)n, (int)n, (int)n, batch, cfg.dw, &wstride);
   if (parts > 1) return mul_split(out, a, n, b, n, (int)n, batch, cfg.dw, parts, wstride, (hipStream_t)stream);
   return launch_mul_mfma(out, nullptr, a, n, b, n, batch, cfg, (hipStream_t)stream, (int)n);
+}
+
+int bigint_mullo(uint32_t* out, const uint32_t* a, const uint32_t* b, int64_t n, int64_t batch, void* stream) {
+  return mullo_any(out, a, b, n, batch, nullptr, 0, stream);
+}
+
+int bigint_mullo_ws(uint32_t* out, const uint32_t* a, const uint32_t* b, int64_t n, int64_t batch, void* ws,
+                    size_t ws_bytes, void* stream) {
+  if ((!ws && ws_bytes) || ((uintptr_t)ws & 15)) return BIGINT_EINVAL;
+  if (n > 0 && batch > 0 && n <= (1 << 20) && batch <= 0x7fffffff) {
+    const size_t bytes = (size_t)n * batch * 4;
+    if (overlap(ws, ws_bytes, out, bytes) || overlap(ws, ws_bytes, a, bytes) || overlap(ws, ws_bytes, b, bytes))
+      return BIGINT_EINVAL;
+  }
+  return mullo_any(out, a, b, n, batch, ws, ws_bytes, stream);
 }
 
 int bigint_add6(uint32_t* out, uint32_t* overflow, const uint32_t* a, const uint32_t* b,

@@ -456,12 +456,13 @@ __host__ __device__ __forceinline__ void fwd1(const Src& src, int s, int32_t* ld
   for (int c = 0; c < Z::R1; ++c) lds[Z::pos1(s, c)] = x[c];
 }
 
-// pass 2 of set s, in place
+// pass 2 of set s, in place; node: the transform's root is node `node` of its
+// level in a larger one (a factor of it), else 0
 template <class Z>
-__host__ __device__ __forceinline__ void fwd2(int s, int32_t* lds, const Prime& P_) {
+__host__ __device__ __forceinline__ void fwd2(int s, int32_t* lds, const Prime& P_, int node = 0) {
   const Prime P = local(P_);
   int32_t x[Z::R2];
-  const int b = s / Z::S2;
+  const int b = node * Z::R1 + s / Z::S2;
 #pragma unroll
   for (int c = 0; c < Z::R2; ++c) x[c] = lds[Z::pos2(s, c)];
   fwd_net<Z::R2, 0>(
@@ -573,10 +574,10 @@ __host__ __device__ __forceinline__ void inv3(int t, const int32_t (&x)[4][Z::Q]
 }
 
 template <class Z>
-__host__ __device__ __forceinline__ void inv2(int s, int32_t* lds, const Prime& P_) {
+__host__ __device__ __forceinline__ void inv2(int s, int32_t* lds, const Prime& P_, int node = 0) {
   const Prime P = local(P_);
   int32_t x[Z::R2];
-  const int b = s / Z::S2;
+  const int b = node * Z::R1 + s / Z::S2;
 #pragma unroll
   for (int c = 0; c < Z::R2; ++c) x[c] = lds[Z::pos2(s, c)];
   inv_net<Z::R2, kPassEnd, 0, false>(
@@ -595,6 +596,73 @@ __host__ __device__ __forceinline__ void inv1(int s, const int32_t* lds, int32_t
   for (int c = 0; c < Z::R1; ++c) x[c] = lds[Z::pos1(s, c)];
   inv_net<Z::R1, kPassEnd, kInvFree, true>(
       x, [&](int, int i) { return P.b[i]; }, [&](int, int i) { return P.bv[i]; }, P.p, P.pinv, P.one);
+}
+
+// ---- a factor of a larger transform ---------------------------------------------------
+// A product of 4 M points splits by its first two levels into the factors
+// x^M - r with r = 1, -1, i, -i (nodes 0..3 of level 2).  Operand x is
+// x_0 + x_1 r + x_2 r^2 + x_3 r^3 there, x_k its k-th run of M limbs.
+
+// c[node][k] = r^k, Montgomery form in [0, p)
+struct Quarters { uint32_t c[kPrimes][4][4]; };
+constexpr Quarters make_quarters() {
+  Quarters q{};
+  for (int pr = 0; pr < kPrimes; ++pr) {
+    const uint64_t p = (uint64_t)kP[pr], w = root4096(p), i = powmod(w, kTab / 2, p);
+    const uint64_t r[4] = {1, p - 1, i, p - i};
+    for (int f = 0; f < 4; ++f)
+      for (int k = 0; k < 4; ++k) q.c[pr][f][k] = (uint32_t)to_mont(powmod(r[f], (uint64_t)k, p), p);
+  }
+  return q;
+}
+constexpr Quarters kQuarters = make_quarters();
+__device__ const Quarters d_quarters = kQuarters;
+constexpr int kLoad4 = 18;   // a loaded point: a sum of four limbs times roots, redc in (-p/2, 9p/2)
+
+// pass 1 of set s of factor `node`: runs > 2: all four runs of the operand
+// (else its first two; the others are 0)
+template <class Z, bool HALF, class Src>
+__host__ __device__ __forceinline__ void fwd1_quarter(const Src& src, int s, int node, const uint32_t (&c)[4],
+                                                      int32_t* lds, const Prime& P_) {
+  const Prime P = local(P_);
+  constexpr int N = HALF ? 2 : 4;
+  static_assert(fwd_bound(4, fwd_bound(Z::R2, fwd_bound(Z::R1, kLoad4, 0), 0), 0) <= Z::FWD, "leaf bound");
+  int32_t x[Z::R1];
+#pragma unroll
+  for (int e = 0; e < Z::R1; ++e) {
+    uint64_t m = 0;
+#pragma unroll
+    for (int k = 0; k < N; ++k) m += (uint64_t)src(s + Z::S1 * e + Z::M * k) * c[k];
+    x[e] = redc((int64_t)m, P.p, P.pinv);
+  }
+  fwd_net<Z::R1, 0>(
+      x, [&](int l, int i) { return P.f[(node << l) + i]; }, [&](int l, int i) { return P.fv[(node << l) + i]; }, P.p,
+      P.pinv);
+#pragma unroll
+  for (int e = 0; e < Z::R1; ++e) lds[Z::pos1(s, e)] = x[e];
+}
+
+// inverse pass 1 of set s of factor `node`: x[c] reduced, |x| < p
+template <class Z>
+__host__ __device__ __forceinline__ void inv1_quarter(int s, int node, const int32_t* lds, int32_t (&x)[Z::R1],
+                                                      const Prime& P_) {
+  const Prime P = local(P_);
+#pragma unroll
+  for (int c = 0; c < Z::R1; ++c) x[c] = lds[Z::pos1(s, c)];
+  inv_net<Z::R1, kPassEnd, 0, false>(
+      x, [&](int l, int i) { return P.b[(node << l) + i]; }, [&](int l, int i) { return P.bv[(node << l) + i]; }, P.p,
+      P.pinv, P.one);
+}
+
+// the last two inverse levels: y[f] = a point of factor f (bound kPassEnd);
+// y[k] = the residue of the coefficient of run k, bound 4 kPassEnd
+__host__ __device__ __forceinline__ void join_quarters(int32_t (&y)[4], int32_t i_inv, const Prime& P) {
+  const int32_t e0 = y[0] + y[1], d0 = y[0] - y[1], e1 = y[2] + y[3];
+  const int32_t q = mont(y[2] - y[3], i_inv, P.p, P.pinv);
+  y[0] = e0 + e1;
+  y[2] = e0 - e1;
+  y[1] = d0 + q;
+  y[3] = d0 - q;
 }
 
 // ---- Chinese remainders ------------------------------------------------------------
@@ -788,6 +856,174 @@ __device__ __forceinline__ void wg_mul_ntt(uint32_t* __restrict__ out, const uin
         for (int c2 = 0; c2 < Z::R1; ++c2) lo.put(s + Z::S1 * c2, (uint32_t)lds[Z::pos1(s, c2)]);
       }
     }
+  }
+}
+
+// One prime and one factor of a product of 4 Z::M points, on T threads: the
+// residues of the factor's points (bound kPassEnd) to y[0 .. Z::M).
+template <class Z>
+__device__ __forceinline__ void wg_ntt_quarter(int32_t* __restrict__ y, const uint32_t* __restrict__ a, int na,
+                                               const uint32_t* __restrict__ b, int nb, int pr, int node,
+                                               int32_t* lds) {
+  const Limbs la(a, na), lb(b, nb);
+  const Prime P = prime_of(pr);
+  const int t = threadIdx.x, lane = t & 63, wv = __builtin_amdgcn_readfirstlane(wave_id());
+  int32_t xa[4][Z::Q], xb[4][Z::Q];
+  auto fwd12 = [&](const Limbs& src) __attribute__((always_inline)) {
+    if (src.n <= 2 * Z::M) {
+#pragma unroll 1
+      for (int ch = wv; ch < Z::NC1; ch += Z::NW)
+        fwd1_quarter<Z, true>(src, 64 * ch + lane, node, d_quarters.c[pr][node], lds, P);
+    } else {
+#pragma unroll 1
+      for (int ch = wv; ch < Z::NC1; ch += Z::NW)
+        fwd1_quarter<Z, false>(src, 64 * ch + lane, node, d_quarters.c[pr][node], lds, P);
+    }
+    __syncthreads();
+#pragma unroll 1
+    for (int s = t; s < Z::N2; s += Z::T) fwd2<Z>(s, lds, P, node);
+    __syncthreads();
+  };
+  const Roots3 w = load3(node * Z::T + t, P.f, P.fv);
+  const int32_t scale = d_fields.f[pr].scale[Z::K + 2];
+  fwd12(la);
+  fwd3<Z>(t, lds, xa, w, P);
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+#pragma unroll
+    for (int j = 0; j < Z::Q; ++j) xa[k][j] = mont(xa[k][j], scale, P.p, P.pinv);
+  }
+  __syncthreads();
+  fwd12(lb);
+  fwd3<Z>(t, lds, xb, w, P);
+  leaves<Z>(xa, xb, w, P);
+  inv3<Z>(t, xb, lds, load3(node * Z::T + t, P.b, P.bv), P);
+  __syncthreads();
+#pragma unroll 1
+  for (int s = t; s < Z::N2; s += Z::T) inv2<Z>(s, lds, P, node);
+  __syncthreads();
+#pragma unroll 1
+  for (int ch = wv; ch < Z::NC1; ch += Z::NW) {
+    int32_t r[Z::R1];
+    inv1_quarter<Z>(64 * ch + lane, node, lds, r, P);
+#pragma unroll
+    for (int c = 0; c < Z::R1; ++c) y[64 * ch + lane + Z::S1 * c] = r[c];
+  }
+}
+
+// Joins the factors of a product (y[prime][node][m]) into limbs.  Thread j
+// takes points 8 j .. 8 j + 7 of every factor, that is 8 limbs in each of the
+// product's four runs of m limbs; a wave's 512 limbs in each run form a strip,
+// resolved here but for what enters it from below: strip[2 w] = its carry word
+// with "limbs 2..511 all ones" in bit 63, strip[2 w + 1] = its limbs 0-1.
+constexpr int kRun = 8, kStripLimbs = 64 * kRun;
+__device__ __forceinline__ void join_strip(uint32_t* __restrict__ out, int nout, const int32_t* __restrict__ y,
+                                           int m, int j, uint64_t* strip) {
+  const int lane = lane_id();
+  int32_t r[kPrimes][4][kRun];
+#pragma unroll
+  for (int pr = 0; pr < kPrimes; ++pr) {
+    const Prime P = prime_of(pr);
+    const int32_t i_inv = P.b[1];
+#pragma unroll
+    for (int f = 0; f < 4; ++f) {
+      const v4i* src = reinterpret_cast<const v4i*>(y + ((int64_t)(pr * 4 + f) * m + kRun * j));
+#pragma unroll
+      for (int e = 0; e < kRun; e += 4) {
+        const v4i v = src[e / 4];
+        r[pr][f][e] = v.x; r[pr][f][e + 1] = v.y; r[pr][f][e + 2] = v.z; r[pr][f][e + 3] = v.w;
+      }
+    }
+#pragma unroll
+    for (int e = 0; e < kRun; ++e) {
+      int32_t v[4] = {r[pr][0][e], r[pr][1][e], r[pr][2][e], r[pr][3][e]};
+      join_quarters(v, i_inv, P);
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        r[pr][k][e] = pr == 0 ? (int32_t)canon(mont(v[k], P.one, P.p, P.pinv), P.p) : v[k];
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const int base = k * m + kRun * j;   // this run's first limb
+    uint64_t acc = 0;
+    uint32_t x[kRun];
+#pragma unroll
+    for (int e = 0; e < kRun; ++e) x[e] = crt_limb((uint32_t)r[0][k][e], r[1][k][e], r[2][k][e], &acc, d_crt);
+    const uint64_t d = ((uint64_t)(uint32_t)__builtin_amdgcn_update_dpp(0, (int)(acc >> 32), 0x138, 0xf, 0xf, false) << 32) |
+                       (uint32_t)__builtin_amdgcn_update_dpp(0, (int)acc, 0x138, 0xf, 0xf, false);
+    uint32_t ones = 0xffffffffu;
+#pragma unroll
+    for (int e = 2; e < kRun; ++e) ones &= x[e];
+    const uint64_t x0 = ((uint64_t)x[1] << 32) | x[0], y0 = x0 + d;
+    const bool h = y0 < x0, full = ones == 0xffffffffu;
+    const bool g = h && full, pp = !h && full && y0 == ~0ull;
+    const WaveCarry wc = wave_carry_masks(g, pp);
+    const uint32_t c = wave_carry_in(wc, 0u);
+    const uint64_t yy = y0 + c;
+    x[0] = (uint32_t)yy;
+    x[1] = (uint32_t)(yy >> 32);
+    if (h || yy < y0) {
+      bool on = true;
+#pragma unroll
+      for (int e = 2; e < kRun; ++e) {
+        x[e] += on ? 1u : 0u;
+        on = on && x[e] == 0u;
+      }
+    }
+    if (base + kRun <= nout) {
+      store4(out + base, x[0], x[1], x[2], x[3]);
+      store4(out + base + 4, x[4], x[5], x[6], x[7]);
+    } else {
+#pragma unroll
+      for (int e = 0; e < kRun; ++e)
+        if (base + e < nout) out[base + e] = x[e];
+    }
+    // limbs of the strip from limb 2 up (limbs past the product count as ones)
+    bool all = true;
+#pragma unroll
+    for (int e = 0; e < kRun; ++e) all = all && (x[e] == 0xffffffffu || base + e >= nout || (lane == 0 && e < 2));
+    const bool tail = __ballot(all) == ~0ull;
+    uint64_t* st = strip + 2 * (base / kStripLimbs);
+    if (lane == 63) st[0] = (acc + wave_carry_out(wc, 0u)) | ((uint64_t)tail << 63);
+    if (lane == 0) st[1] = yy;
+  }
+}
+
+// The closing scan over the W <= 64 strips of a product, on one wave for its
+// strip `mine` (every wave repeats the scan): strip w takes carry word w - 1
+// at its limbs 0-1, one-bit carries run on through strips of all ones; a
+// carry into strip `mine`'s tail runs up to its first limb not all ones.
+__device__ __forceinline__ void close_joined(uint32_t* out, int nout, int W, const uint64_t* strip, int mine) {
+  const int w = lane_id();
+  const bool valid = w < W;
+  const uint64_t kC = (1ull << 63) - 1;
+  const uint64_t x0 = valid ? strip[2 * w + 1] : 0ull;
+  const uint64_t x = x0 + ((valid && w > 0) ? (strip[2 * (w - 1)] & kC) : 0ull);
+  const bool ones = valid && (strip[2 * w] >> 63), h = x < x0;
+  const WaveCarry wc = wave_carry_masks(valid && h && ones, valid && !h && x == ~0ull && ones);
+  const uint64_t y = x + wave_carry_in(wc, 0u);
+  const int j0 = kStripLimbs * mine;
+  if (w == mine && y != x0) {
+    if (j0 < nout) out[j0] = (uint32_t)y;
+    if (j0 + 1 < nout) out[j0 + 1] = (uint32_t)(y >> 32);
+  }
+  if (!(__ballot(h || y < x) >> mine & 1)) return;
+  uint32_t v[kRun];
+#pragma unroll
+  for (int c = 0; c < kRun; ++c) {
+    const int j = j0 + 64 * c + w;
+    v[c] = j < nout ? out[j] : 0u;
+  }
+  bool on = true;
+#pragma unroll
+  for (int c = 0; c < kRun; ++c) {
+    const int j = j0 + 64 * c + w;
+    uint64_t stop = __ballot(v[c] != 0xffffffffu);
+    if (c == 0) stop &= ~3ull;
+    const int at = stop ? __ffsll((long long)stop) - 1 : 64;
+    if (on && j < nout && w <= at && j >= j0 + 2) out[j] = v[c] + 1u;
+    on = on && !stop;
   }
 }
 

@@ -1,5 +1,6 @@
 // kernels_ntt.hip -- the transform multiply: kernels and launchers.
 #include <algorithm>
+#include <cmath>
 
 #include "internal.hpp"
 #include "dev_mul_ntt.hpp"
@@ -49,11 +50,98 @@ static int launch_ntt_size(uint32_t* out, const uint32_t* a, int64_t na, const u
   return BIGINT_OK;
 }
 
+// ---- few large products: every prime and factor of a product its own work-group ------
+template <class Z>
+__global__ __launch_bounds__(Z::T) void k_ntt_quarter(int32_t* y, const uint32_t* a, int na, const uint32_t* b,
+                                                      int nb) {
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  const int64_t inst = blockIdx.y;
+  const int pr = blockIdx.x >> 2, node = blockIdx.x & 3;
+  ntt::wg_ntt_quarter<Z>(y + (inst * 12 + blockIdx.x) * Z::M, a + inst * na, na, b + inst * nb, nb, pr, node,
+                         reinterpret_cast<int32_t*>(smem));
+}
+
+// 1024 points of every factor per work-group of two waves
+__global__ __launch_bounds__(128) void k_ntt_join(uint32_t* out, int nout, const int32_t* y, int m,
+                                                  uint64_t* strip) {
+  const int64_t inst = blockIdx.y;
+  ntt::join_strip(out + inst * nout, nout, y + inst * 12 * m, m, (int)(blockIdx.x * 128 + threadIdx.x),
+                  strip + inst * (8 * m / ntt::kStripLimbs));
+}
+
+// four strips per work-group
+__global__ __launch_bounds__(256) void k_ntt_close(uint32_t* out, int nout, int m, const uint64_t* strip) {
+  const int64_t inst = blockIdx.y;
+  const int W = 4 * m / ntt::kStripLimbs;
+  ntt::close_joined(out + inst * nout, nout, W, strip + inst * 2 * W,
+                    __builtin_amdgcn_readfirstlane((int)blockIdx.x * 4 + wave_id()));
+}
+
+// At most kQuarterChunk products at a time share the workspace.
+constexpr int64_t kQuarterChunk = 256;
+
+template <int Q>
+static int launch_ntt_quarters(uint32_t* out, const uint32_t* a, int64_t na, const uint32_t* b, int64_t nb,
+                               int64_t batch, int nout, void* ws, hipStream_t s) {
+  typedef ntt::Size<256, Q, 16, 16> Z;
+  BI_HIP(hipFuncSetAttribute((const void*)k_ntt_quarter<Z>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                             (int)Z::LDS_BYTES));
+  for (int64_t first = 0; first < batch; first += kQuarterChunk) {
+    const unsigned n = (unsigned)std::min(kQuarterChunk, batch - first);
+    int32_t* y = reinterpret_cast<int32_t*>(ws);
+    uint64_t* strip = reinterpret_cast<uint64_t*>(y + (int64_t)n * 12 * Z::M);
+    uint32_t* o = out + first * nout;
+    hipLaunchKernelGGL(k_ntt_quarter<Z>, dim3(12, n), dim3(Z::T), Z::LDS_BYTES, s, y, a + first * na, (int)na,
+                       b + first * nb, (int)nb);
+    BI_LAUNCH_CHECK();
+    hipLaunchKernelGGL(k_ntt_join, dim3(Q, n), dim3(128), 0, s, o, nout, y, Z::M, strip);
+    BI_LAUNCH_CHECK();
+    hipLaunchKernelGGL(k_ntt_close, dim3(2 * Q, n), dim3(256), 0, s, o, nout, Z::M, strip);
+    BI_LAUNCH_CHECK();
+  }
+  return BIGINT_OK;
+}
+
+static int quarter_q(int64_t need) { return (int)std::max<int64_t>(3, cdiv(need, 4096)); }
+
+size_t ntt_quarters_ws(int64_t na, int64_t nb, int64_t batch) {
+  return (size_t)std::min(batch, kQuarterChunk) * quarter_q(na + nb) * (12 * 1024 * 4 + 8 * 16);
+}
+
+// Estimated time (us) with the quarters apart: 15 us for one product's three
+// launches, then what a product takes of a CU, and 8 us for every further
+// chunk.  Against one work-group per product (us, one / quarters): 16384 limbs
+// batch 3 106 / 23, 64 113 / 48, 256 135 / 134, 300 230 / 153, 512 241 / 252;
+// 8192 limbs 58 / 18, 60 / 29, 72 / 68, 106 / 78, 114 / 120; 5120 limbs
+// 43 / 18, 44 / 29, 49 / 58.  The gain is the chip filled by few products
+// and the last round of work-groups filled; the price is the trip of the 12
+// transforms through memory.
+double ntt_quarters_us(int64_t na, int64_t nb, int64_t batch) {
+  static const double load[9] = {0, 0, 0, 43, 54, 72, 83, 112, 118};
+  if (na + nb <= 8192 || na + nb > 32768) return 1e30;
+  return 15.0 + load[quarter_q(na + nb)] * (double)batch / num_cus() + 8.0 * (double)((batch - 1) / kQuarterChunk);
+}
+
+int launch_mul_ntt_quarters(uint32_t* out, const uint32_t* a, int64_t na, const uint32_t* b, int64_t nb,
+                            int64_t batch, int nout, void* ws, hipStream_t s) {
+  switch (quarter_q(na + nb)) {
+    case 3: return launch_ntt_quarters<3>(out, a, na, b, nb, batch, nout, ws, s);
+    case 4: return launch_ntt_quarters<4>(out, a, na, b, nb, batch, nout, ws, s);
+    case 5: return launch_ntt_quarters<5>(out, a, na, b, nb, batch, nout, ws, s);
+    case 6: return launch_ntt_quarters<6>(out, a, na, b, nb, batch, nout, ws, s);
+    case 7: return launch_ntt_quarters<7>(out, a, na, b, nb, batch, nout, ws, s);
+    case 8: return launch_ntt_quarters<8>(out, a, na, b, nb, batch, nout, ws, s);
+    default: return BIGINT_EUNSUPPORTED;
+  }
+}
+
 // ---- which kernel ------------------------------------------------------------------
 // The sizes built: serial (one prime after another) and the three primes side
 // by side, with what one product takes alone on an idle CU and what it takes
-// of a CU in a large batch (us, measured on batches of 1 to 8192; in between,
-// 0.4 of the first and the second add up).  Side by
+// of a CU in a large batch (us, measured on batches of 1 to 8192).  In
+// between, work-groups that fill a CU by themselves go in whole rounds, and of
+// the small ones several overlap (1024 limbs: batch 2048 66 us, 4096 94, 8192
+// 181; 1536 limbs side by side: 256 14 us, 512 23, 1024 40).  Side by
 // side wins wherever waves are idle, and above 3072 points also in large
 // batches except at 5120 and 6144 points, whose serial kernels fit four
 // work-groups a CU against one (2560-limb products, batch 1024: 73 against
@@ -79,7 +167,11 @@ int ntt_pick(int64_t na, int64_t nb, int64_t batch, double* us) {
   for (int i = 0; i < (int)(sizeof(kNtt) / sizeof(kNtt[0])); ++i) {
     if (kNtt[i].M < na + nb) continue;
     if (best >= 0 && kNtt[i].M > 2 * kNtt[best].M) break;
-    const double t = std::max<double>(kNtt[i].lat, 0.4 * kNtt[i].lat + kNtt[i].load * (double)batch / num_cus());
+    const NttKernel& k = kNtt[i];
+    const double x = (double)batch / num_cus();
+    const double t = k.M > (k.side ? 4096 : 8192) ? 1.1 * k.lat + k.load * std::max(0.0, std::ceil(x) - 1.0)
+                     : k.side                     ? std::max<double>(k.lat, 0.4 * k.lat + k.load * x)
+                                                  : std::max(k.load * x, k.lat + 0.7 * k.load * x);
     if (best < 0 || t < *us) {
       best = i;
       *us = t;

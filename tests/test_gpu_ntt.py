@@ -142,3 +142,42 @@ def test_graph_capture(bi):
         torch.cuda.synchronize()
         assert bool((p == want).all())
         bi.add(a, b)
+
+
+@pytest.mark.parametrize("na,nb", [(4097, 4096), (6144, 6144), (6145, 6144), (8192, 8192), (8193, 8192), (10240, 10240),
+                                   (12288, 12287), (14336, 14336), (16384, 16384), (16384, 256), (16000, 4000),
+                                   (9000, 700)])
+def test_few_large_products(bi, orc, na, nb):
+    """Few large products, every prime and quarter of each its own work-group:
+    every transform size, unequal operands (one run of limbs only), all-ones
+    and zero operands (carries through whole strips)."""
+    a, b = operands(na + 2 * nb, 5, na, nb)
+    p = bi.mul(dev(a), dev(b))
+    exp = oracle_map(lambda i: orc.mul1(a[i], b[i]), range(5))
+    got = host(p)
+    assert [i for i in range(5) if not np.array_equal(got[i], exp[i])] == []
+    if na == nb:
+        got = host(bi.mullo(dev(a), dev(b)))
+        assert [i for i in range(5) if not np.array_equal(got[i], exp[i][:na])] == []
+
+
+def test_few_large_products_in_chunks(bi):
+    """More products than share the workspace at once, and the C entry with a
+    workspace too small for them (which then uses none)."""
+    import ctypes
+    import torch
+    L = bi.lib()
+    a, b = operands(9, 300, 10000, 9000)
+    ta, tb = dev(a), dev(b)
+    want = bi.mul(ta, tb, bi.MUL_MFMA)
+    size = ctypes.c_size_t()
+    assert L.bigint_mul_workspace_size(10000, 9000, 300, ctypes.byref(size)) == 0 and size.value > 0
+    assert bool((bi.mul(ta, tb) == want).all())
+    ws = torch.empty(size.value, dtype=torch.uint8, device="cuda")
+    out = torch.empty_like(want)
+    args = (out.data_ptr(), ta.data_ptr(), 10000, tb.data_ptr(), 9000, 300, bi.MUL_AUTO, ws.data_ptr())
+    s = torch.cuda.current_stream().cuda_stream
+    assert L.bigint_mul_ws(*args, size.value // 2, s) == 0
+    assert bool((out == want).all())
+    assert L.bigint_mul_ws(out.data_ptr(), ta.data_ptr(), 10000, tb.data_ptr(), 9000, 300, bi.MUL_AUTO,
+                           out.data_ptr(), 1 << 20, s) == bi.EINVAL
