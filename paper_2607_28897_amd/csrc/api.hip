@@ -552,7 +552,7 @@ struct bigint_plan_s {
   size_t lds = 0;                    // plain multiply
   bool plain = false;
   int grid = 0;               // division: work-groups (workspace slots) per launch
-  int cap_u = 0, cap_v = 0;   // division: largest dividend / divisor
+  DivCfg div = {};            // division: sizes and how it runs
   // workspace
   void* ws = nullptr;
   size_t ws_bytes = 0, ws_need = 0;
@@ -862,14 +862,14 @@ static int plan_build_mul(bigint_plan_s* p) {
 
 static int plan_build_div(bigint_plan_s* p) {
   const int64_t B = p->batch;
-  int64_t cu = 1, cv = 1;
+  int64_t cu = 1, cv = 1, prod = div_product_limbs(1, 1);
   for (int64_t i = 0; i < B; ++i) {
     if (p->la[i] > BIGINT_DIV_MAX_LIMBS || p->lb[i] > BIGINT_DIV_MAX_LIMBS) return BIGINT_EUNSUPPORTED;
     cu = std::max(cu, p->la[i]);
     cv = std::max(cv, p->lb[i]);
+    prod = std::max(prod, div_product_limbs(p->la[i], p->lb[i]));
   }
-  p->cap_u = (int)cu;
-  p->cap_v = (int)cv;
+  p->div = div_cfg((int)cu, (int)cv, prod, B);
   // largest first: the cost grows like (nu - nv) (nu + 4 nv) limb products
   std::vector<int64_t> idx(B);
   std::iota(idx.begin(), idx.end(), 0);
@@ -888,22 +888,21 @@ static int plan_build_div(bigint_plan_s* p) {
   // 0.380 ms; pairing neighbours in the order instead: 0.45 ms).
   {
     const int64_t R = num_cus();
-    const int64_t e = std::min<int64_t>(B, R * div_groups_per_cu(p->cap_u, p->cap_v));
+    const int64_t e = std::min<int64_t>(B, R * p->div.per_cu);
     for (int64_t row = 1; row * R < e; row += 2)
       std::reverse(q.begin() + row * R, q.begin() + std::min(e, (row + 1) * R));
   }
-  p->grid = div_chunk(p->cap_u, p->cap_v, B);
+  p->grid = div_chunk(p->div, B);
   p->n_launches = B > 0 ? (B + p->grid - 1) / p->grid : 0;
   BI_DEBUG("bigint: plan of %lld divisions: dividends up to %d limbs, divisors up to %d, %d threads per "
            "division, %d per CU, %d per launch\n",
-           (long long)B, p->cap_u, p->cap_v, div_threads(p->cap_u), div_groups_per_cu(p->cap_u, p->cap_v),
-           p->grid);
+           (long long)B, p->div.cap_u, p->div.cap_v, p->div.threads, p->div.per_cu, p->grid);
   if (B > 0) {
     BI_HIP(hipMalloc(&p->d_queue, sizeof(int32_t) * B));
     BI_HIP(hipMemcpy(p->d_queue, q.data(), sizeof(int32_t) * B, hipMemcpyHostToDevice));
   }
-  p->ws_need = div_ws_bytes(p->cap_u, p->cap_v, p->grid);
-  if (div_lds_bytes(p->cap_u, p->cap_v) > 163840 - 256) return BIGINT_EUNSUPPORTED;
+  p->ws_need = div_ws_bytes(p->div.cap_u, p->div.cap_v, p->grid);
+  if (p->div.per_cu < 1) return BIGINT_EUNSUPPORTED;
   return BIGINT_OK;
 }
 
@@ -1052,13 +1051,15 @@ static int divmod_launch_alloc(uint32_t* q, uint32_t* r, int32_t* status, const 
                                hipStream_t s) {
   const int cap_u = h_inv >= 0 ? h_inv + 2 : (int)nu;
   const int cap_v = (int)nv;
-  const int grid = div_chunk(cap_u, cap_v, batch);
+  // (the inverse's fix-up takes a product of v and all of w)
+  const DivCfg cfg = div_cfg(cap_u, cap_v, h_inv >= 0 ? h_inv + 24 : div_product_limbs(nu, nv), batch);
+  const int grid = div_chunk(cfg, batch);
   const size_t bytes = div_ws_bytes(cap_u, cap_v, grid);
   void* ws = nullptr;
   hipError_t e = hipMallocAsync(&ws, bytes, s);
   if (e != hipSuccess) { set_hip_error(e); return BIGINT_ENOMEM; }
   const int rc = launch_divmod(q, nullptr, r, nullptr, status, u, nullptr, (int)nu, v, nullptr,
-                               (int)nv, nullptr, batch, ws, cap_u, cap_v, grid, h_inv, nullptr, s);
+                               (int)nv, nullptr, batch, ws, cfg, grid, h_inv, nullptr, s);
   e = hipFreeAsync(ws, s);
   if (rc != BIGINT_OK) return rc;
   if (e != hipSuccess) { set_hip_error(e); return BIGINT_EHIP; }
@@ -1103,10 +1104,11 @@ int bigint_divmod_noalloc(uint32_t* q, uint32_t* r, int32_t* status, const uint3
   // work-groups per launch: as bigint_divmod, but no more workspace slots
   // than the scratch array holds (the launches run one after another)
   const size_t slot = div_ws_bytes((int)nu, (int)nv, 1);
-  const int64_t grid = std::min<int64_t>(div_chunk((int)nu, (int)nv, batch), (int64_t)(cap / slot));
+  const DivCfg cfg = div_cfg((int)nu, (int)nv, div_product_limbs(nu, nv), batch);
+  const int64_t grid = std::min<int64_t>(div_chunk(cfg, batch), (int64_t)(cap / slot));
   if (grid < 1) return BIGINT_EUNSUPPORTED;
   return launch_divmod(q, nullptr, r, nullptr, status, u, nullptr, (int)nu, v, nullptr, (int)nv,
-                       nullptr, batch, ws, (int)nu, (int)nv, (int)grid, -1, nullptr,
+                       nullptr, batch, ws, cfg, (int)grid, -1, nullptr,
                        (hipStream_t)stream);
 }
 
@@ -1143,7 +1145,7 @@ static int divmod_ragged(uint32_t* q, const int64_t* q_off, uint32_t* r, const i
   auto launch = [&](hipStream_t ls) {
     return launch_divmod(q, q_off, r, r_off, status, u, u_off, 0, v, v_off, 0,
                          reinterpret_cast<const int32_t*>(plan->d_queue), batch, plan->ws,
-                         plan->cap_u, plan->cap_v, plan->grid, -1, counts, ls);
+                         plan->div, plan->grid, -1, counts, ls);
   };
   // the counting variant is a diagnostic: launched directly
   if (counts || (plan->flags & BIGINT_PLAN_NO_GRAPH)) return launch(s);

@@ -4,7 +4,8 @@
 // h significant limbs, the quotient is read off w ~ B^h / v:
 // q~ = floor(u w / B^h) is within a few units of floor(u / v), and the signed
 // remainder u - q~ v, reduced into [0, v) by adding or subtracting v, fixes
-// it.  w is grown by Newton steps in the integral domain, the paper's `step`
+// it.  Long quotients are taken so in pieces from the top, from an inverse of
+// one piece's precision (see kHalves).  w is grown by Newton steps in the integral domain, the paper's `step`
 // (Section 5.3, Fig. bdiv-F-code) with both of its branches: with
 // e = B^c - V w (the signed powDiff, V the divisor's top limbs),
 //     w' = w B^m + floor(w e / B^(c-m))      if e > 0
@@ -257,6 +258,14 @@ __device__ __forceinline__ uint32_t wg_arith1(uint32_t* dst, int n, const uint32
   auto X = [&](int j) -> uint32_t { return (j < nx) ? x[min(j, nx - 1)] : 0u; };
   auto Y = [&](int j) -> uint32_t { return j == 0 ? small : 0u; };
   return div_addsub<SUB>(dst, n, X, Y, sh);
+}
+
+// a pointer that is the same in every lane, in scalar registers
+template <class T>
+__device__ __forceinline__ T* uniform_ptr(T* p) {
+  const uint64_t v = (uint64_t)p;
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+  return (T*)(((uint64_t)hi << 32) | lo);
 }
 
 constexpr int kSmallMul = 64;  // operands up to this many limbs: column-sum product
@@ -625,6 +634,36 @@ __device__ inline unsigned __int128 seed_inverse(const uint32_t* v, int k1) {
   return seed_div<2>(v, k1);
 }
 
+// ---- the quotient in pieces --------------------------------------------------------
+// A quotient of kHalves limbs and more is taken in two halves from an inverse
+// of half its precision (Karp and Markstein's last step): against the last
+// Newton step and one quotient of full length, two thirds of the digit
+// products, and no product longer than (nu + nv) / 2 limbs.  The LDS of a
+// division thus holds 0.4 of what a product of two dividends would take, and
+// the registers alone decide how many share a CU (4096 divisions of 2048 by
+// 1024 limbs: 7 per CU and 802 us in one piece, 16 per CU and 501 us in two;
+// 512 of 8192 by 4096: 536 and 490).  Shorter quotients gain nothing by it.
+constexpr int kHalves = 300;
+constexpr int kProdSlack = 8;   // limbs of a division's products beyond its pieces
+
+// limbs of a piece of a quotient of P + 1 limbs whose products, 2 s and
+// k1 + s limbs and the slack, fit prod limbs (more than two pieces only where
+// the divisor has fewer limbs than prod was sized for)
+__host__ __device__ inline int piece_limbs(int P, int k1, int prod) {
+  const int s = P >= kHalves ? P / 2 + 1 : P;
+  const int fit = min((prod - kProdSlack) / 2, prod - kProdSlack - k1);
+  if (P <= 0) return 0;
+  return s <= fit ? s : max(1, min(P / 2 + 1, fit));
+}
+
+// limbs of the longest product (both factors) of nu / nv divisions whose
+// divisors use all their limbs
+__host__ __device__ inline int64_t product_limbs(int64_t nu, int64_t nv) {
+  const int64_t P = nu > nv ? nu - nv : 0;
+  const int64_t s = P >= kHalves ? P / 2 + 1 : P;
+  return (2 * s > nv + s ? 2 * s : nv + s) + kProdSlack;
+}
+
 // ---- the division of one instance ----------------------------------------------
 
 struct Bufs {
@@ -636,13 +675,13 @@ struct Bufs {
 };
 
 __host__ __device__ inline size_t div_ws_limbs(int nu, int nv) {
-  const int cw = nu + 8, ce = nv + 8, ct = 2 * nu + nv + 16;
+  const int cw = nu + 8, ce = nv + 8, ct = 2 * nu + nv + 32;
   return (size_t)2 * cw + ce + ct;
 }
 
 __host__ __device__ inline Bufs carve_bufs(uint32_t* ws, int nu, int nv) {
   Bufs b;
-  b.cw = nu + 8; b.ce = nv + 8; b.ct = 2 * nu + nv + 16;
+  b.cw = nu + 8; b.ce = nv + 8; b.ct = 2 * nu + nv + 32;
   b.W = ws; b.U2 = b.W + b.cw; b.E = b.U2 + b.cw; b.T = b.E + b.ce;
   return b;
 }
@@ -869,9 +908,10 @@ __device__ inline int shifted_inverse(const uint32_t* v, int k1, int h, Bufs& bf
 // With inverse_only, writes floor(B^h_inv / v) into q[0..nq) instead.
 // adjust (nullable, 3 ints): Newton steps, fix-up unit steps, quotient
 // corrections, each added to.
+template <bool inverse_only>
 __device__ inline int wg_divmod(uint32_t* q, int nq, uint32_t* r, int nr, const uint32_t* u, int nu,
                                 const uint32_t* v, int nv, Bufs bf, Shared* sh, char* smem,
-                                bool inverse_only, int h_inv, int64_t* adjust) {
+                                int h_inv, int prod, int64_t* adjust) {
   if (threadIdx.x == 0) sh->failed = 0u;
   __syncthreads();
   int k1, hu;
@@ -917,48 +957,82 @@ __device__ inline int wg_divmod(uint32_t* q, int nq, uint32_t* r, int nr, const 
     __syncthreads();
     return BIGINT_DIV_OK;
   }
-  int lw = shifted_inverse(v, k1, h, bf, sh, smem, adjust);
   if (inverse_only) {
+    int lw = shifted_inverse(v, k1, h, bf, sh, smem, adjust);
     // the diagnostic wants floor(B^h / v) exactly: one exact fix-up at scale h
     lw = fixup(v, k1, h, bf, lw, sh, smem, nullptr);
     wg_shr_copy(q, nq, bf.W, lw, 0);
     return sh->failed ? BIGINT_DIV_FAILED : BIGINT_DIV_OK;
   }
-  // q~ = floor(u w / B^h), from the top limbs of u only: the low su limbs add
-  // less than B^(su+lw) <= B^(h-1) to u w, so they move q~ by at most one
-  // unit; a high product (limbs from h - su up) takes at most one more
-  const int su = max(0, h - 1 - lw);
-  wg_mul(bf.T, u + su, h - su, bf.W, lw, smem, -1, adjust, h - su);
-  const uint32_t* qt = bf.T + (h - su);              // q~: lw limbs
-  const int lq = max(wg_prec(qt, lw, sh), 1);
-  // r~ = u - q~ v; |r~| < 8 v < B^(k1+1), so r~ mod B^(k1+2) holds it with
-  // its sign in the top limb
+  // The quotient's limbs in pieces of s from the top, each from the same
+  // inverse of s limbs' precision (scale h2 = k1 + s): piece by piece the
+  // dividend is the remainder so far with the next s limbs of u below it.
+  const int s = piece_limbs(h - k1, k1, prod);
+  const int pieces = s > 0 ? (h - k1 + s - 1) / s : 1;
+  const int h2 = k1 + s;
+  const int lw = shifted_inverse(v, k1, h2, bf, sh, smem, adjust);
+  if (sh->failed) return BIGINT_DIV_FAILED;
+  uint32_t* buf0 = bf.U2;                 // dividends of the pieces below the first (k1 + 2 + s limbs)
+  uint32_t* buf1 = bf.T + 2 * s + 8;      // (past the product of a piece)
   const int lr = k1 + 2;
-  wg_mul(bf.U2, qt, lq, v, k1, smem, lr, adjust);
-  wg_arith<true>(bf.E, lr, u, h, bf.U2, min(lr, lq + k1), sh);
-  // corrections: while r~ < 0, r~ += v (q~ - 1); while r~ >= v, r~ -= v (q~ + 1)
-  // (each loop is bounded; leaving one at its bound marks the division failed,
-  // which the error analysis rules out: at most 4 corrections are possible)
-  int dq = 0;
-  bool done_neg = false, done_pos = false;
-  for (int rounds = 0; rounds < 8; ++rounds) {
-    const uint32_t top = __builtin_amdgcn_readfirstlane(bf.E[lr - 1]);
-    if (top == 0u) { done_neg = true; break; }
-    wg_arith<false>(bf.E, lr, bf.E, lr, v, k1, sh);
-    --dq;
+  const uint32_t* x = u + (pieces - 1) * s;
+  int hd = h - (pieces - 1) * s;          // its limbs: at most h2
+  int cor = 0;
+  for (int piece = pieces - 1; piece >= 0; --piece) {
+    const int lo = piece * s;             // the piece's lowest limb of q
+    // q~ = floor(x w / B^h2), from the top limbs of x only: the low su limbs
+    // add less than B^(su+lw) <= B^(h2-1) to x w, so they move q~ by at most
+    // one unit; a high product (limbs from h2 - su up) takes at most one more
+    const int su = max(0, h2 - 1 - lw);
+    const int nd = hd - su;
+    wg_mul(bf.T, x + su, nd, bf.W, lw, smem, -1, adjust, h2 - su);
+    const uint32_t* qt = bf.T + (h2 - su);
+    int lq = nd + lw - (h2 - su);
+    // (below the first piece x < v B^s, so q~ is at most a few units above B^s)
+    if (piece < pieces - 1) lq = min(lq, s + 1);
+    // r~ = x - q~ v; |r~| < 8 v < B^(k1+1), so r~ mod B^(k1+2) holds it with
+    // its sign in the top limb.  It is written above the next s limbs of u.
+    wg_mul(bf.E, qt, lq, v, k1, smem, lr, adjust);
+    uint32_t* nx = buf0;
+    uint32_t* rem = nx + (piece > 0 ? s : 0);
+    if (piece > 0)
+      for (int i = threadIdx.x; i < s; i += blockDim.x) nx[i] = u[lo - s + i];
+    wg_arith<true>(rem, lr, x, hd, bf.E, min(lr, lq + k1), sh);
+    // corrections: while r~ < 0, r~ += v (q~ - 1); while r~ >= v, r~ -= v (q~ + 1)
+    // (each loop is bounded; leaving one at its bound marks the division failed,
+    // which the error analysis rules out: at most 4 corrections are possible)
+    int dq = 0;
+    bool done_neg = false, done_pos = false;
+    for (int rounds = 0; rounds < 8; ++rounds) {
+      const uint32_t top = __builtin_amdgcn_readfirstlane(rem[lr - 1]);
+      if (top == 0u) { done_neg = true; break; }
+      wg_arith<false>(rem, lr, rem, lr, v, k1, sh);
+      --dq;
+    }
+    for (int rounds = 0; rounds < 8 && done_neg; ++rounds) {
+      if (wg_cmp(rem, lr, v, k1, lr, sh) < 0) { done_pos = true; break; }
+      wg_arith<true>(rem, lr, rem, lr, v, k1, sh);
+      ++dq;
+    }
+    if (!done_pos && threadIdx.x == 0) sh->failed = 1u;
+    cor += dq < 0 ? -dq : dq;
+    // the piece of q = q~ + dq; with the last one r = r~ over nr limbs (the
+    // copy rides along with the addition's first round)
+    if (piece == 0)
+      for (int i = threadIdx.x; i < nr; i += blockDim.x) r[i] = i < k1 ? rem[i] : 0u;
+    const int nqp = max(0, piece == pieces - 1 ? nq - lo : min(s, nq - lo));
+    if (dq >= 0) wg_arith1<false>(q + lo, nqp, qt, lq, (uint32_t)dq, sh);
+    else wg_arith1<true>(q + lo, nqp, qt, lq, (uint32_t)(-dq), sh);
+    __syncthreads();
+    x = nx;
+    hd = k1 + s;
+    buf0 = buf1;
+    buf1 = nx;
   }
-  for (int rounds = 0; rounds < 8 && done_neg; ++rounds) {
-    if (wg_cmp(bf.E, lr, v, k1, lr, sh) < 0) { done_pos = true; break; }
-    wg_arith<true>(bf.E, lr, bf.E, lr, v, k1, sh);
-    ++dq;
+  if (adjust) {
+    adjust[0] += pieces - 1;   // (a further piece is the Newton step, taken on the quotient)
+    adjust[2] += cor;
   }
-  if (!done_pos && threadIdx.x == 0) sh->failed = 1u;
-  if (adjust) adjust[2] += dq < 0 ? -dq : dq;
-  // q = q~ + dq over all nq limbs and r = r~ over nr limbs, in one pass
-  // (r's copy rides along with the addition's first round)
-  for (int i = threadIdx.x; i < nr; i += blockDim.x) r[i] = i < k1 ? bf.E[i] : 0u;
-  if (dq >= 0) wg_arith1<false>(q, nq, qt, lq, (uint32_t)dq, sh);
-  else wg_arith1<true>(q, nq, qt, lq, (uint32_t)(-dq), sh);
   return sh->failed ? BIGINT_DIV_FAILED : BIGINT_DIV_OK;
 }
 

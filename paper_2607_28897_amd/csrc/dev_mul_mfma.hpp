@@ -123,6 +123,13 @@ __host__ __device__ inline size_t lds_bytes(int na, int nb, int nwaves, int P, b
          (size_t)((2 * NB + 15) & ~15) + 128 + (DW == 8 ? bs_bytes(g) : 0);
 }
 
+// enough for any product of operands of na + nb = n limbs in all (8-bit digits)
+__host__ __device__ inline size_t lds_bytes_sum(int n, int nwaves, int P) {
+  const int W = n / strip_limbs<8>() + 1, NB = (W + P - 1) / P;
+  return (size_t)4 * n + 2 * kPadA + kPadB + kPadBt + 64 + (size_t)nwaves * 1024 + (size_t)8 * W +
+         (size_t)((2 * NB + 15) & ~15) + 128 + (size_t)(4 * (n / 64 + 4) + 16);
+}
+
 struct Lds {
   uint8_t* A;
   uint8_t* B;

@@ -133,17 +133,20 @@ int launch_mad_rate(uint64_t* out, int blocks, int iters, hipStream_t s);
 // slot each, div_ws_bytes(cap_u, cap_v, chunk) bytes in all); larger batches
 // go in consecutive launches.
 size_t div_ws_bytes(int cap_u, int cap_v, int slots);
-size_t div_lds_bytes(int cap_u, int cap_v);
-int div_groups_per_cu(int cap_u, int cap_v);
-int div_threads(int cap_u);   // threads per division work-group
-int div_chunk(int cap_u, int cap_v, int64_t batch);
+// how a batch of divisions runs: the largest dividend and divisor, the limbs
+// (both factors) of the longest product the LDS is sized for, threads per
+// division, divisions resident per CU (0: they do not fit)
+struct DivCfg { int cap_u, cap_v, prod, threads, per_cu; };
+int64_t div_product_limbs(int64_t nu, int64_t nv);
+DivCfg div_cfg(int cap_u, int cap_v, int64_t prod, int64_t batch);
+int div_chunk(const DivCfg& c, int64_t batch);
 // The allocation-free division's device workspace on the current device:
 // its address (from hipGetSymbolAddress, once per device) and size.
 int div_scratch(void** ptr, size_t* bytes);
 int launch_divmod(uint32_t* q, const int64_t* q_off, uint32_t* r, const int64_t* r_off,
                   int32_t* status, const uint32_t* u, const int64_t* u_off, int nu,
                   const uint32_t* v, const int64_t* v_off, int nv, const int32_t* queue,
-                  int64_t nitems, void* ws, int cap_u, int cap_v, int chunk, int h_inv,
+                  int64_t nitems, void* ws, const DivCfg& cfg, int chunk, int h_inv,
                   int64_t* adjust, hipStream_t s);
 
 }  // namespace bi

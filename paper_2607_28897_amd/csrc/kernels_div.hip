@@ -8,18 +8,11 @@
 
 namespace bi {
 
-// threads per division work-group: at most kDivThreads (the register budget
-// is that of 4 waves per SIMD).  A division is mostly a chain of short
-// latency-bound passes, so smaller dividends run on fewer threads and more
-// divisions share a CU: 64 threads up to 1448 dividend limbs, 128 up to
-// 2896, 256 up to 5792 (measured on uniform batches of 2^13..2^18-bit
-// dividends: 6.9x faster at 2^13 bits than with 512 threads, the same at 2^18).
+// Threads of a division work-group: at most kDivThreads (the register budget
+// is that of 4 waves per SIMD).
 constexpr int kDivThreads = 512;
-constexpr int kDivT64 = 1448, kDivT128 = 2896, kDivT256 = 5792;
 
-int div_threads(int cap_u) {
-  return cap_u <= kDivT64 ? 64 : (cap_u <= kDivT128 ? 128 : (cap_u <= kDivT256 ? 256 : kDivThreads));
-}
+int64_t div_product_limbs(int64_t nu, int64_t nv) { return div::product_limbs(nu, nv); }
 
 // Uniform batches pass null offsets and the limb counts nu / nv; ragged
 // batches pass prefix offsets.  queue == nullptr means instance t is item t.
@@ -28,15 +21,16 @@ int div_threads(int cap_u) {
 // in queue order.  (A persistent loop pulling items with an atomic was
 // measured 11% slower on 512 ragged divisions: the loop made the compiler
 // keep loop-invariant values live across the whole division.)
-// h_inv >= 0 selects the shifted-inverse diagnostic: q[i] = floor(B^h_inv / v).
+// INV is the shifted-inverse diagnostic: q[i] = floor(B^h_inv / v).
 // adjust (nullable): 4 int64 per instance, the division's counters (Newton
 // steps, fix-up unit steps, quotient corrections, MFMA multiply-accumulates).
+template <bool INV>
 __global__ __launch_bounds__(kDivThreads, 4) void k_divmod(uint32_t* q, const int64_t* q_off, uint32_t* r,
                                                 const int64_t* r_off, int32_t* status,
                                                 const uint32_t* u, const int64_t* u_off, int nu,
                                                 const uint32_t* v, const int64_t* v_off, int nv,
                                                 const int32_t* queue, int64_t first, int64_t nitems,
-                                                uint32_t* ws, int cap_u, int cap_v, int h_inv,
+                                                uint32_t* ws, int cap_u, int cap_v, int prod, int h_inv,
                                                 int64_t* adjust) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   __shared__ div::Shared sh;
@@ -55,12 +49,12 @@ __global__ __launch_bounds__(kDivThreads, 4) void k_divmod(uint32_t* q, const in
   } else {
     lu = nu; lv = nv;
     uo = i * (int64_t)nu; vo = i * (int64_t)nv;
-    lq = h_inv >= 0 ? h_inv + 1 : nu; qo = i * (int64_t)lq;
+    lq = INV ? h_inv + 1 : nu; qo = i * (int64_t)lq;
     lr = nv; ro = i * (int64_t)nv;
   }
   int64_t cnt[4] = {0, 0, 0, 0};
-  const int st = div::wg_divmod(q + qo, lq, r ? r + ro : nullptr, lr, u ? u + uo : nullptr, lu,
-                                v + vo, lv, bf, &sh, smem, h_inv >= 0, h_inv, cnt);
+  const int st = div::wg_divmod<INV>(q + qo, lq, r ? r + ro : nullptr, lr, u ? u + uo : nullptr, lu, v + vo, lv,
+                                     bf, &sh, smem, h_inv, prod, cnt);
   if (threadIdx.x == 0) {
     if (status) status[i] = st;
     if (adjust) {
@@ -74,26 +68,37 @@ size_t div_ws_bytes(int cap_u, int cap_v, int slots) {
   return (size_t)slots * div::div_ws_limbs(cap_u, cap_v) * 4;
 }
 
-size_t div_lds_bytes(int cap_u, int cap_v) {
-  // the largest product of a division has two factors of at most cap_u + 8 limbs
-  const int m = cap_u + 8;
-  (void)cap_v;
-  // (and at least what the small-operand product and the one-wave steps need)
-  return std::max<size_t>(mfma::lds_bytes<div::kDW>(m, m, div_threads(cap_u) / 64, div::kP),
+static size_t div_lds_bytes(const DivCfg& c) {
+  // (at least what the small-operand product and the one-wave steps need)
+  return std::max<size_t>(mfma::lds_bytes_sum(c.prod, c.threads / 64, div::kP),
                           std::max(div::kSmallMulLds, div::kEarlyLds));
 }
 
-// Work-groups that fit one CU: the kernel is built for 4 waves per SIMD (16
-// per CU), so that many waves (over the work-group's) and then the LDS decide.
-int div_groups_per_cu(int cap_u, int cap_v) {
-  const size_t per = div_lds_bytes(cap_u, cap_v) + sizeof(div::Shared) + 64;
-  const int by_waves = 16 / (div_threads(cap_u) / 64);
-  return std::max(1, std::min<int>(by_waves, (int)(163840 / per)));
+// A division is mostly a chain of short passes that wait on memory and on one
+// another, and more of them on a CU hardly slow one another down (2048 / 1024
+// limbs, 64 threads: one 249 us, 16 per CU 501).  So the work-group is the
+// largest useful one that still lets the whole batch run at once, and where
+// none does, the one with the most divisions resident (2048 / 1024 limbs, us
+// with 64 / 128 / 256 / 512 threads: batch 1 249 / 190 / 168 / 171, 1024
+// 308 / 251 / 261 / 444, 2048 386 / 329 / 533 / 876, 4096 529 / 673 / 979 /
+// 1726; 16384 / 8192 limbs: one 2553 / 1416 / 836 / 623; 512 / 256 limbs: one
+// 113 / 100 / 103 / 110).
+DivCfg div_cfg(int cap_u, int cap_v, int64_t prod, int64_t batch) {
+  DivCfg best{cap_u, cap_v, (int)prod, 0, 0};
+  for (int t = cap_u <= 724 ? 128 : (cap_u <= 2896 ? 256 : kDivThreads); t >= 64; t /= 2) {
+    DivCfg c{cap_u, cap_v, (int)prod, t, 0};
+    // work-groups that fit one CU: the kernel is built for 4 waves per SIMD (16
+    // per CU), so that many waves (over the work-group's) and then the LDS decide
+    const size_t per = div_lds_bytes(c) + sizeof(div::Shared) + 64;
+    c.per_cu = std::min<int>(16 / (t / 64), (int)(163840 / per));
+    if (c.per_cu > best.per_cu) best = c;
+    if ((int64_t)num_cus() * best.per_cu >= batch) break;
+  }
+  return best;
 }
 
-int div_chunk(int cap_u, int cap_v, int64_t batch) {
-  const int64_t resident = (int64_t)num_cus() * div_groups_per_cu(cap_u, cap_v);
-  return (int)std::max<int64_t>(1, std::min<int64_t>(batch, 8 * resident));
+int div_chunk(const DivCfg& c, int64_t batch) {
+  return (int)std::max<int64_t>(1, std::min<int64_t>(batch, (int64_t)8 * num_cus() * c.per_cu));
 }
 
 // ---- workspace of the allocation-free division (bigint_divmod_noalloc) ----------
@@ -130,20 +135,21 @@ int div_scratch(void** ptr, size_t* bytes) {
 int launch_divmod(uint32_t* q, const int64_t* q_off, uint32_t* r, const int64_t* r_off,
                   int32_t* status, const uint32_t* u, const int64_t* u_off, int nu,
                   const uint32_t* v, const int64_t* v_off, int nv, const int32_t* queue,
-                  int64_t nitems, void* ws, int cap_u, int cap_v, int chunk, int h_inv,
+                  int64_t nitems, void* ws, const DivCfg& cfg, int chunk, int h_inv,
                   int64_t* adjust, hipStream_t s) {
-  const size_t lds = div_lds_bytes(cap_u, cap_v);
-  if (lds > 163840 - sizeof(div::Shared) - 64) return BIGINT_EUNSUPPORTED;
+  const size_t lds = div_lds_bytes(cfg);
+  if (cfg.per_cu < 1) return BIGINT_EUNSUPPORTED;
   if (chunk < 1) return BIGINT_EINVAL;
-  BI_HIP(hipFuncSetAttribute((const void*)k_divmod, hipFuncAttributeMaxDynamicSharedMemorySize,
+  const auto kernel = h_inv >= 0 ? k_divmod<true> : k_divmod<false>;
+  BI_HIP(hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
                              (int)lds));
   // chunks run one after another on the stream, so a workspace slot is never
   // held by two live work-groups
   for (int64_t first = 0; first < nitems; first += chunk) {
     const int64_t g = std::min<int64_t>(chunk, nitems - first);
-    hipLaunchKernelGGL(k_divmod, dim3((unsigned)g), dim3(div_threads(cap_u)), lds, s, q, q_off, r, r_off,
+    hipLaunchKernelGGL(kernel, dim3((unsigned)g), dim3((unsigned)cfg.threads), lds, s, q, q_off, r, r_off,
                        status, u, u_off, nu, v, v_off, nv, queue, first, nitems,
-                       reinterpret_cast<uint32_t*>(ws), cap_u, cap_v, h_inv, adjust);
+                       reinterpret_cast<uint32_t*>(ws), cfg.cap_u, cfg.cap_v, cfg.prod, h_inv, adjust);
     BI_LAUNCH_CHECK();
   }
   return BIGINT_OK;

@@ -344,3 +344,48 @@ def test_shifted_inverse_2e19(bi, orc):
         for i in range(2):
             want, _ = orc.shinv1(v[i], h)
             assert np.array_equal(w[i], want), (nv, h, i)
+
+
+@pytest.mark.parametrize("nu,nv,k1", [(600, 300, 300), (601, 301, 301), (599, 300, 300), (900, 600, 600),
+                                      (900, 600, 599), (2048, 1024, 1024), (2048, 1024, 700), (2048, 1024, 130),
+                                      (2048, 1024, 2), (1500, 20, 20), (1500, 1490, 1000), (1500, 1490, 3),
+                                      (400, 1600, 5), (8192, 4096, 4000), (8192, 4096, 60)])
+def test_quotients_in_pieces(bi, orc, nu, nv, k1):
+    """Quotients around the size from which they are taken in two halves, and
+    divisors with leading zero limbs (k1 of nv used), whose longer quotients
+    take more pieces; quotients and remainders of all-ones and zero limbs."""
+    g = np.random.default_rng(nu * 31 + nv + k1)
+    u = rand_limbs(g, 6, nu)
+    v = rand_limbs(g, 6, nv)
+    v[:, k1:] = 0
+    v[:, k1 - 1] |= 1
+    u[1] = 0xFFFFFFFF
+    v[2, :k1] = 0xFFFFFFFF
+    v[3, :k1] = 0
+    v[3, k1 - 1] = 1                       # a power of the base
+    for row, quotient in ((4, (1 << (32 * (nu - k1))) - 1), (5, 1 << (32 * ((nu - k1) // 2)))):
+        V = _to_int(v[row])
+        U = quotient * V + (V - 1 if row == 4 else 0)
+        u[row] = np.frombuffer(U.to_bytes(4 * nu, "little"), np.uint32)
+    q, r, st = bi.divmod(dev(u), dev(v))
+    q, r, st = host(q), host(r), st.cpu().numpy()
+    for i in range(6):
+        wq, wr, ws = orc.divmod1(u[i], v[i])
+        assert st[i] == ws == 0, i
+        assert np.array_equal(q[i], wq) and np.array_equal(r[i], wr), i
+
+
+@pytest.mark.parametrize("nu,nv,batch", [(600, 290, 3000), (1100, 500, 5000), (3000, 1500, 1500), (6000, 3000, 700)])
+def test_threads_by_batch(bi, nu, nv, batch):
+    """Batches that take smaller work-groups than a single division: the same
+    bytes as in calls of 100 divisions."""
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(nu)
+    u = torch.randint(-2**31, 2**31, (batch, nu), dtype=torch.int32, device="cuda", generator=g)
+    v = torch.randint(-2**31, 2**31, (batch, nv), dtype=torch.int32, device="cuda", generator=g)
+    v[:, -1] |= 1
+    q, r, st = bi.divmod(u, v)
+    assert int(st.abs().sum()) == 0
+    for i in range(0, batch, 100):
+        a, b, _ = bi.divmod(u[i:i + 100].contiguous(), v[i:i + 100].contiguous())
+        assert bool((a == q[i:i + 100]).all()) and bool((b == r[i:i + 100]).all()), i
