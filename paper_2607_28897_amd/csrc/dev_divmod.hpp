@@ -40,6 +40,8 @@ struct Shared {
   uint32_t red[4];      // reductions
   uint32_t scan[32];    // carry-scan scratch
   uint32_t w0[4];       // initial estimate (one thread)
+  uint32_t lin[16];     // wg_lin: the waves' carries of two blocks
+  int lin_top[8], lin_cmp[8];  // and what each found
   int early_cur, early_lw;  // scale and length of w after the one-wave steps
   uint32_t failed;      // a bounded loop hit its bound, or an estimate left its error bound (never expected)
 };
@@ -232,15 +234,7 @@ __device__ __forceinline__ int wg_cmp(const uint32_t* x, int nx, const uint32_t*
   return r;
 }
 
-// addition / subtraction for the division on the whole work-group.  (Running
-// short ranges inside every wave instead, with two barriers, raised the
-// kernel's register spills from 180 to 388 bytes per lane and made divisions
-// 9% slower.)
-template <bool SUB, class FX, class FY>
-__device__ __forceinline__ uint32_t div_addsub(uint32_t* out, int n, FX X, FY Y, Shared* sh,
-                                               uint32_t* top = nullptr, uint32_t cin = 0u) {
-  return wg_addsub<16, SUB>(out, n, X, Y, cin, sh->scan, top);
-}
+// ---- additions of the exact fix-up (the inverse diagnostic) ------------------------
 
 // dst[0..n) = x + y (or x - y), operands zero-extended; returns carry/borrow
 template <bool SUB>
@@ -248,7 +242,7 @@ __device__ __forceinline__ uint32_t wg_arith(uint32_t* dst, int n, const uint32_
                                              const uint32_t* y, int ny, Shared* sh) {
   auto X = [&](int j) -> uint32_t { return (j < nx) ? x[min(j, nx - 1)] : 0u; };
   auto Y = [&](int j) -> uint32_t { return (j < ny) ? y[min(j, ny - 1)] : 0u; };
-  return div_addsub<SUB>(dst, n, X, Y, sh);
+  return wg_addsub<16, SUB>(dst, n, X, Y, 0u, sh->scan);
 }
 
 // dst[0..n) = x +/- small (a one-limb value), x zero-extended
@@ -257,7 +251,7 @@ __device__ __forceinline__ uint32_t wg_arith1(uint32_t* dst, int n, const uint32
                                               uint32_t small, Shared* sh) {
   auto X = [&](int j) -> uint32_t { return (j < nx) ? x[min(j, nx - 1)] : 0u; };
   auto Y = [&](int j) -> uint32_t { return j == 0 ? small : 0u; };
-  return div_addsub<SUB>(dst, n, X, Y, sh);
+  return wg_addsub<16, SUB>(dst, n, X, Y, 0u, sh->scan);
 }
 
 // a pointer that is the same in every lane, in scalar registers
@@ -266,6 +260,128 @@ __device__ __forceinline__ T* uniform_ptr(T* p) {
   const uint64_t v = (uint64_t)p;
   const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
   return (T*)(((uint64_t)hi << 32) | lo);
+}
+
+// ---- one pass of additions, with what the next step asks of its result --------------
+// n limbs, zero from there on
+struct Operand {
+  const uint32_t* p;
+  int n;
+};
+struct LinResult {
+  int top;   // significant limbs of the result
+  int cmp;   // sign of the result minus z (both n limbs)
+};
+constexpr int kLinRounds = 16;
+
+// the carry out of bit 63 and the carries into every bit of g + p bits with
+// carry c into bit 0 (p: propagate, g: generate, disjoint)
+__device__ __forceinline__ uint64_t carry_bits(uint64_t g, uint64_t p, uint32_t& c) {
+  const uint64_t a = g | p, s = a + g + c;
+  c = (uint32_t)(g >> 32 | (a >> 32 & ~(s >> 32))) >> 31;
+  return s ^ a ^ g;
+}
+
+// dst[0 .. n) = x B^at + y + c, or x B^at - y - c with sub, modulo B^n (n >= 1;
+// dst may be x's or y's storage, the former with at = 0); with y = {nullptr, 0}
+// its limb 0 is low.
+// A wave takes 64 limbs a round, a limb a lane: the loads are whole lines,
+// the carries of a round are one 64-bit scalar addition of its ballots, and
+// the result's length and its order against z (nullable, nz limbs) fall out of
+// two more ballots, so that no further pass and no second barrier is needed
+// for them.  (Runs of 16 limbs a thread, with a length and a comparison pass
+// of their own, took TIMES.)
+__device__ __noinline__ LinResult wg_lin(uint32_t* dst, int n, Operand x, int at, Operand y, int sub, uint32_t c,
+                                         uint32_t low, const uint32_t* z, int nz, Shared* sh) {
+  n = __builtin_amdgcn_readfirstlane(n);
+  sub = __builtin_amdgcn_readfirstlane(sub);
+  nz = __builtin_amdgcn_readfirstlane(nz);
+  const Limbs D(uniform_ptr(dst), n), X(uniform_ptr(x.p), __builtin_amdgcn_readfirstlane(x.n)),
+      Y(uniform_ptr(y.p), __builtin_amdgcn_readfirstlane(y.n)), Z(uniform_ptr(z), nz);
+  const int lane = lane_id(), xa = lane - __builtin_amdgcn_readfirstlane(at);
+  const int nw = __builtin_amdgcn_readfirstlane(num_waves()), wv = __builtin_amdgcn_readfirstlane(wave_id());
+  uint32_t carry = __builtin_amdgcn_readfirstlane(sub ? 1u - c : c);   // (x + ~y + 1)
+  const uint32_t flip = sub ? ~0u : 0u;
+  low = __builtin_amdgcn_readfirstlane(low);
+  int top = 0, side = 0;
+  int cmp = 0;   // 2 (index + 1) of the highest limb that differs from z, + 1 if it is above
+  for (int base = 0; base < n; base += 64 * kLinRounds * nw) {
+    const int rounds = min(kLinRounds, (n - base + 64 * nw - 1) / (64 * nw));
+    const int j0 = base + 64 * rounds * wv;
+    uint32_t r[kLinRounds], s[kLinRounds], zs[kLinRounds];
+#pragma unroll
+    for (int i = 0; i < kLinRounds; ++i)
+      if (i < rounds) {
+        const int j = j0 + 64 * i;
+        const int k = j + xa;
+        const uint32_t v = X(max(k, 0));
+        r[i] = k < 0 ? 0u : v;
+        s[i] = Y(j + lane);
+        if (nz) zs[i] = Z(j + lane);
+      }
+    if (j0 == 0) s[0] += lane == 0 ? low : 0u;
+    // x -> the sum without carries, s -> whether it overflowed
+    uint32_t cin = carry;
+    if (nw > 1) {
+      uint32_t c0 = 0u, c1 = 1u;   // carries out of this wave's limbs for both carries in
+#pragma unroll
+      for (int i = 0; i < kLinRounds; ++i)
+        if (i < rounds) {
+          const uint32_t t = r[i] + (s[i] ^ flip);
+          const uint64_t g = __ballot(t < r[i]), p = __ballot(t == ~0u);
+          (void)carry_bits(g, p, c0);
+          (void)carry_bits(g, p, c1);
+        }
+      uint32_t* slot = sh->lin + 8 * side;
+      side ^= 1;   // (the other half: no wave can be two blocks behind)
+      if (lane == 0) slot[wv] = c0 | c1 << 1;
+      __syncthreads();
+      const uint32_t v = slot[lane & 7];
+      const uint64_t b0 = __ballot(v & 1u), b1 = __ballot(v & 2u);
+      for (int k = 0; k < nw; ++k) {
+        if (k == wv) cin = carry;
+        carry = (uint32_t)((carry ? b1 : b0) >> k) & 1u;
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < kLinRounds; ++i)
+      if (i < rounds) {
+        const int j = j0 + 64 * i;
+        uint32_t t = r[i] + (s[i] ^ flip);
+        const uint64_t g = __ballot(t < r[i]), p = __ballot(t == ~0u);
+        const uint64_t in = carry_bits(g, p, cin);
+        t += __builtin_amdgcn_inverse_ballot_w64(in) ? 1u : 0u;
+        D.put(j + lane, t);
+        const bool valid = j + lane < n;
+        const uint64_t m = __ballot(valid && t != 0u);
+        if (m) top = j + 64 - __clzll(m);
+        if (nz) {
+          const uint64_t d = __ballot(valid && t != zs[i]), gt = __ballot(t > zs[i]);
+          const int hi = 63 - __clzll(d);
+          if (d) cmp = 2 * (j + hi + 1) + (int)((gt >> hi) & 1ull);
+        }
+      }
+    if (nw == 1) carry = cin;
+  }
+  if (nw > 1) {
+    if (lane == 0) {
+      sh->lin_top[wv] = top;
+      sh->lin_cmp[wv] = cmp;
+    }
+    __syncthreads();
+    top = lane < nw ? sh->lin_top[lane & 7] : 0;
+    cmp = lane < nw ? sh->lin_cmp[lane & 7] : 0;
+#pragma unroll
+    for (int d = 1; d < 8; d *= 2) {
+      top = max(top, __shfl_xor(top, d));
+      cmp = max(cmp, __shfl_xor(cmp, d));
+    }
+    top = __builtin_amdgcn_readfirstlane(top);
+    cmp = __builtin_amdgcn_readfirstlane(cmp);
+  } else {
+    __syncthreads();
+  }
+  return {top, cmp == 0 ? 0 : (cmp & 1 ? 1 : -1)};
 }
 
 constexpr int kSmallMul = 64;  // operands up to this many limbs: column-sum product
@@ -712,7 +828,7 @@ __device__ inline int fixup(const uint32_t* v, int k1, int c, Bufs& bf, int lw, 
       neg = false;
       auto X = [&](int) -> uint32_t { return 0u; };
       auto Y = [&](int j) -> uint32_t { return bf.T[j]; };
-      div_addsub<true>(bf.E, le, X, Y, sh);
+      wg_addsub<16, true>(bf.E, le, X, Y, 0u, sh->scan);
       have_e = true;
     }
   }
@@ -725,7 +841,7 @@ __device__ inline int fixup(const uint32_t* v, int k1, int c, Bufs& bf, int lw, 
       neg = false;
       auto X = [&](int) -> uint32_t { return 0u; };
       auto Y = [&](int j) -> uint32_t { return j < lp ? bf.T[j] : 0u; };
-      div_addsub<true>(bf.T, min(c, lp), X, Y, sh);  // in place
+      wg_addsub<16, true>(bf.T, min(c, lp), X, Y, 0u, sh->scan);  // in place
       // limbs [min(c,lp), c) of 0 - P are all ones only if P == 0, which w >= 1 rules out
       wg_shr_copy(bf.E, le, bf.T, min(c, lp), 0);
       if (c > lp) {
@@ -854,9 +970,7 @@ __device__ inline int shifted_inverse(const uint32_t* v, int k1, int h, Bufs& bf
         __syncthreads();
         break;
       }
-      auto X = [&](int) -> uint32_t { return 0u; };
-      auto Y = [&](int j) -> uint32_t { return bf.E[j]; };
-      div_addsub<true>(bf.E, le, X, Y, sh);   // e = 0 - (V w mod B^le), in place
+      wg_lin(bf.E, le, {nullptr, 0}, 0, {bf.E, le}, 1, 0u, 0u, nullptr, 0, sh);   // e = 0 - (V w mod B^le), in place
     }
     if (adjust) {
       adjust[0] += 1;
@@ -884,21 +998,14 @@ __device__ inline int shifted_inverse(const uint32_t* v, int k1, int h, Bufs& bf
         cin = 1u;
       }
     }
-    const int lnew = lw + m + 1;
-    auto X = [&](int j) -> uint32_t { return (j >= m && j - m < lw) ? bf.W[j - m] : 0u; };
-    auto Y = [&](int j) -> uint32_t { return j + sy < ly ? bf.T[j + sy] : 0u; };
-    // (the reset happens before every thread's atomicMax: the addition's
-    // carry scan synchronises the work-group first)
-    if (threadIdx.x == 0) sh->red[3] = 0;
-    if (neg) div_addsub<true>(bf.U2, lnew, X, Y, sh, &sh->red[3], cin);
-    else div_addsub<false>(bf.U2, lnew, X, Y, sh, &sh->red[3]);
+    const LinResult sum = wg_lin(bf.U2, lw + m + 1, {bf.W, lw}, m, {bf.T + sy, max(0, ly - sy)}, neg, cin, 0u,
+                                 nullptr, 0, sh);
     {  // the new w is in U2: swap the two buffers instead of copying
       uint32_t* tmp = bf.W;
       bf.W = bf.U2;
       bf.U2 = tmp;
     }
-    lw = max((int)sh->red[3], 1);   // w's length, from the addition itself
-    __syncthreads();
+    lw = max(sum.top, 1);   // w's length, from the addition itself
     cur += m;
   }
   return lw;
@@ -997,23 +1104,18 @@ __device__ inline int wg_divmod(uint32_t* q, int nq, uint32_t* r, int nr, const 
     uint32_t* rem = nx + (piece > 0 ? s : 0);
     if (piece > 0)
       for (int i = threadIdx.x; i < s; i += blockDim.x) nx[i] = u[lo - s + i];
-    wg_arith<true>(rem, lr, x, hd, bf.E, min(lr, lq + k1), sh);
+    LinResult res = wg_lin(rem, lr, {x, hd}, 0, {bf.E, min(lr, lq + k1)}, 1, 0u, 0u, v, k1, sh);
     // corrections: while r~ < 0, r~ += v (q~ - 1); while r~ >= v, r~ -= v (q~ + 1)
     // (each loop is bounded; leaving one at its bound marks the division failed,
     // which the error analysis rules out: at most 4 corrections are possible)
     int dq = 0;
-    bool done_neg = false, done_pos = false;
-    for (int rounds = 0; rounds < 8; ++rounds) {
-      const uint32_t top = __builtin_amdgcn_readfirstlane(rem[lr - 1]);
-      if (top == 0u) { done_neg = true; break; }
-      wg_arith<false>(rem, lr, rem, lr, v, k1, sh);
-      --dq;
+    for (int rounds = 0; rounds < 16; ++rounds) {
+      const int sub = res.top < lr;   // (a nonzero top limb: r~ < 0)
+      if (sub && res.cmp < 0) break;
+      res = wg_lin(rem, lr, {rem, lr}, 0, {v, k1}, sub, 0u, 0u, v, k1, sh);
+      dq += sub ? 1 : -1;
     }
-    for (int rounds = 0; rounds < 8 && done_neg; ++rounds) {
-      if (wg_cmp(rem, lr, v, k1, lr, sh) < 0) { done_pos = true; break; }
-      wg_arith<true>(rem, lr, rem, lr, v, k1, sh);
-      ++dq;
-    }
+    const bool done_pos = res.top < lr && res.cmp < 0;
     if (!done_pos && threadIdx.x == 0) sh->failed = 1u;
     cor += dq < 0 ? -dq : dq;
     // the piece of q = q~ + dq; with the last one r = r~ over nr limbs (the
@@ -1021,8 +1123,8 @@ __device__ inline int wg_divmod(uint32_t* q, int nq, uint32_t* r, int nr, const 
     if (piece == 0)
       for (int i = threadIdx.x; i < nr; i += blockDim.x) r[i] = i < k1 ? rem[i] : 0u;
     const int nqp = max(0, piece == pieces - 1 ? nq - lo : min(s, nq - lo));
-    if (dq >= 0) wg_arith1<false>(q + lo, nqp, qt, lq, (uint32_t)dq, sh);
-    else wg_arith1<true>(q + lo, nqp, qt, lq, (uint32_t)(-dq), sh);
+    if (nqp > 0)
+      wg_lin(q + lo, nqp, {qt, lq}, 0, {nullptr, 0}, dq < 0, 0u, (uint32_t)(dq < 0 ? -dq : dq), nullptr, 0, sh);
     __syncthreads();
     x = nx;
     hd = k1 + s;

@@ -703,21 +703,6 @@ __host__ __device__ __forceinline__ uint32_t crt_limb(uint32_t r0, int32_t r1, i
 // ---- the whole product on one work-group -------------------------------------------
 #if defined(__HIP_DEVICE_COMPILE__) || defined(__HIPCC__)
 
-// n limbs behind a buffer descriptor: reads past the end give 0 and writes
-// there are dropped, with no compare or mask
-struct Limbs {
-  __amdgpu_buffer_rsrc_t d;
-  int n;
-  __device__ __forceinline__ Limbs(const uint32_t* p, int n_)
-      : d(__builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(p), 0, 4 * n_, 0x00020000)), n(n_) {}
-  __device__ __forceinline__ uint32_t operator()(int i) const {
-    return __builtin_amdgcn_raw_buffer_load_b32(d, 4 * i, 0, 0);
-  }
-  __device__ __forceinline__ void put(int i, uint32_t v) const {
-    __builtin_amdgcn_raw_buffer_store_b32(v, d, 4 * i, 0, 0);
-  }
-};
-
 // The cyclic convolution of a and b modulo the prime of P on the T threads
 // t = 0 .. T - 1 (waves wv = 0 .. NW - 1 of a work-group whose other waves do
 // the same for other primes); the residues of the coefficients stay in lds,

@@ -389,3 +389,28 @@ def test_threads_by_batch(bi, nu, nv, batch):
     for i in range(0, batch, 100):
         a, b, _ = bi.divmod(u[i:i + 100].contiguous(), v[i:i + 100].contiguous())
         assert bool((a == q[i:i + 100]).all()) and bool((b == r[i:i + 100]).all()), i
+
+
+@pytest.mark.parametrize("nu,nv,batch", [(130, 65, 9000), (1023, 512, 5000), (2400, 1200, 4200), (2400, 1200, 2100),
+                                         (2400, 1200, 30), (16384, 8200, 3), (12000, 9, 3)])
+def test_carry_chains(bi, orc, nu, nv, batch):
+    """Operands of long runs of ones and zeros, whose sums carry and borrow
+    through whole waves, blocks and work-groups of every size."""
+    import torch
+    g = np.random.default_rng(nu + batch)
+    rows = min(batch, 12)
+    u, v = np.zeros((rows, nu), np.uint32), np.zeros((rows, nv), np.uint32)
+    for x, n in ((u, nu), (v, nv)):
+        for i in range(rows):
+            a, b = sorted(g.integers(0, n, 2))
+            x[i, a:b + 1] = 0xFFFFFFFF
+            x[i, g.integers(0, n)] = g.integers(1, 1 << 32)
+            x[i, n - 1] |= 1 << int(g.integers(0, 32))
+    V = _to_int(v[0])
+    u[0] = np.frombuffer((V * ((1 << (32 * (nu - nv))) - 1) - 1).to_bytes(4 * nu, "little"), np.uint32)
+    reps = -(-batch // rows)
+    q, r, st = bi.divmod(dev(np.tile(u, (reps, 1))[:batch].copy()), dev(np.tile(v, (reps, 1))[:batch].copy()))
+    assert int(st.abs().sum()) == 0
+    for i in range(rows):
+        wq, wr, _ = orc.divmod1(u[i], v[i])
+        assert bool((q[i::rows] == dev(wq)).all()) and bool((r[i::rows] == dev(wr)).all()), i
