@@ -219,6 +219,16 @@ int bigint_divmod(uint32_t* q, uint32_t* r, int32_t* status, const uint32_t* u,
                   int64_t nu, const uint32_t* v, int64_t nv, int64_t batch,
                   void* stream);
 
+/* bigint_divmod_ws: bigint_divmod with a workspace the caller provides and no
+ * allocation.  bigint_divmod_workspace_size reports the bytes the batch asks
+ * for (a multiple of one division's share); with fewer the call runs as
+ * bigint_divmod.  ws: device memory, 16-byte aligned, not overlapping the
+ * operands or the results, free again once the stream has passed the call. */
+int bigint_divmod_workspace_size(int64_t nu, int64_t nv, int64_t batch, size_t* bytes);
+int bigint_divmod_ws(uint32_t* q, uint32_t* r, int32_t* status, const uint32_t* u,
+                     int64_t nu, const uint32_t* v, int64_t nv, int64_t batch,
+                     void* ws, size_t ws_bytes, void* stream);
+
 /* bigint_divmod_noalloc: bigint_divmod (same arguments, same results, same
  * size limits) for callers that cannot allocate device memory: code under
  * HIP graph capture, tight serving loops, harnesses that forbid allocation.

@@ -77,6 +77,8 @@ def lib() -> ctypes.CDLL:
             "bigint_mul_workspace_size": ([_i64, _i64, _i64, ctypes.POINTER(ctypes.c_size_t)], _int),
             "bigint_mullo_ws": ([_vp, _vp, _vp, _i64, _i64, _vp, ctypes.c_size_t, _vp], _int),
             "bigint_divmod": ([_vp, _vp, _vp, _vp, _i64, _vp, _i64, _i64, _vp], _int),
+            "bigint_divmod_ws": ([_vp, _vp, _vp, _vp, _i64, _vp, _i64, _i64, _vp, ctypes.c_size_t, _vp], _int),
+            "bigint_divmod_workspace_size": ([_i64, _i64, _i64, ctypes.POINTER(ctypes.c_size_t)], _int),
             "bigint_divmod_noalloc": ([_vp, _vp, _vp, _vp, _i64, _vp, _i64, _i64, _vp], _int),
             "bigint_plan_create": ([ctypes.POINTER(_vp), _int, _vp, _vp, _i64, _int], _int),
             "bigint_plan_workspace_size": ([_vp, ctypes.POINTER(ctypes.c_size_t)], _int),
@@ -118,39 +120,57 @@ def _check(code: int, what: str):
         raise BigIntError(code, what)
 
 
+_torch_mod = None
+
+
 def _torch():
-    import torch
-    return torch
+    global _torch_mod
+    if _torch_mod is None:
+        import torch
+        _torch_mod = torch
+    return _torch_mod
 
 
 def _stream():
-    torch = _torch()
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    """The current torch stream's handle.  (torch's own accessor builds a
+    Stream object, 3.0 us of a small call's 11.5; the raw handle takes 0.2.)"""
+    c = _torch()._C
+    raw = getattr(c, "_cuda_getCurrentRawStream", None)
+    if raw is None:
+        return _torch().cuda.current_stream().cuda_stream
+    return raw(c._cuda_getDevice())
+
+
+_WIDE = None   # limb dtypes -> whether they are 64-bit
+
+
+def _limb_types():
+    global _WIDE
+    if _WIDE is None:
+        torch = _torch()
+        _WIDE = {getattr(torch, t): w for t, w in (("int32", False), ("uint32", False), ("int64", True),
+                                                   ("uint64", True)) if hasattr(torch, t)}
+    return _WIDE
 
 
 def _limbs(t, name):
     """The tensor as u32 limbs.  64-bit limb tensors (int64/uint64) are viewed
     as twice as many u32 limbs: on little-endian hosts and gfx950 the bytes of
     n u64 digits are those of 2n u32 limbs."""
-    torch = _torch()
-    if not isinstance(t, torch.Tensor) or not t.is_cuda:
+    if not isinstance(t, _torch().Tensor) or not t.is_cuda:
         raise TypeError(f"{name} must be a CUDA tensor")
-    wide = (torch.int64, getattr(torch, "uint64", torch.int64))
-    narrow = (torch.int32, getattr(torch, "uint32", torch.int32))
-    if t.dtype not in wide + narrow:
+    wide = _limb_types().get(t.dtype)
+    if wide is None:
         raise TypeError(f"{name} must hold 32- or 64-bit limbs, got {t.dtype}")
     if not t.is_contiguous():
         t = t.contiguous()
-    if t.dtype in wide:
-        t = t.view(torch.int32)
-    return t
+    return t.view(_torch().int32) if wide else t
 
 
 def _wide(t):
     """The dtype to hand results back in: 64-bit limb inputs get 64-bit limb
     outputs (a view of the same bytes), 32-bit inputs 32-bit outputs."""
-    torch = _torch()
-    return t.dtype if t.dtype in (torch.int64, getattr(torch, "uint64", torch.int64)) else None
+    return t.dtype if _limb_types().get(t.dtype) else None
 
 
 def _back(t, dtype):
@@ -162,7 +182,7 @@ def _rows(t):
 
 
 def _p(t):
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def add(a, b, out=None):
@@ -188,14 +208,12 @@ def _addsub(fn, a, b, out, what):
     return _back(out, wd), carry
 
 
-def _mul_ws(na, nb, batch, device):
-    """A workspace from torch's allocator for products that take one (ordered
-    on the current stream like every tensor), else None, and its size.  With
-    no memory left for it the product runs without."""
-    if na + nb <= 8192:
-        return None, 0
+def _workspace(query, what, device, *sizes):
+    """The workspace that C function `query` asks for, from torch's allocator
+    (ordered on the current stream like every tensor), else None, and its
+    size.  With no memory left for it the call runs without."""
     n = ctypes.c_size_t()
-    _check(lib().bigint_mul_workspace_size(na, nb, batch, ctypes.byref(n)), "bigint_mul_workspace_size")
+    _check(query(*sizes, ctypes.byref(n)), what)
     if n.value == 0:
         return None, 0
     torch = _torch()
@@ -203,6 +221,13 @@ def _mul_ws(na, nb, batch, device):
         return torch.empty(n.value, dtype=torch.uint8, device=device), n.value
     except torch.cuda.OutOfMemoryError:
         return None, 0
+
+
+def _mul_ws(na, nb, batch, device):
+    """The workspace of products that take one (none do up to 8192 limbs)."""
+    if na + nb <= 8192:
+        return None, 0
+    return _workspace(lib().bigint_mul_workspace_size, "bigint_mul_workspace_size", device, na, nb, batch)
 
 
 def mul(a, b, algo: int = MUL_AUTO):
@@ -235,8 +260,14 @@ def divmod(u, v):
     q = torch.empty((bu, nu), dtype=u.dtype, device=u.device)
     r = torch.empty((bu, nv), dtype=u.dtype, device=u.device)
     st = torch.empty(bu, dtype=torch.int32, device=u.device)
-    _check(lib().bigint_divmod(_p(q), _p(r), _p(st), _p(u), nu, _p(v), nv, bu, _stream()),
-           "bigint_divmod")
+    ws, size = None, 0
+    if 0 < nu <= DIV_MAX_LIMBS and 0 < nv <= DIV_MAX_LIMBS and bu > 0:
+        ws, size = _workspace(lib().bigint_divmod_workspace_size, "bigint_divmod", u.device, nu, nv, bu)
+    if ws is not None:
+        _check(lib().bigint_divmod_ws(_p(q), _p(r), _p(st), _p(u), nu, _p(v), nv, bu, _p(ws), size, _stream()),
+               "bigint_divmod")
+    else:
+        _check(lib().bigint_divmod(_p(q), _p(r), _p(st), _p(u), nu, _p(v), nv, bu, _stream()), "bigint_divmod")
     return _back(q, wd), _back(r, wd), st
 
 

@@ -1048,13 +1048,16 @@ int bigint_mul_ragged(uint32_t* out, const int64_t* out_off, const uint32_t* a,
 
 static int divmod_launch_alloc(uint32_t* q, uint32_t* r, int32_t* status, const uint32_t* u,
                                int64_t nu, const uint32_t* v, int64_t nv, int64_t batch, int h_inv,
-                               hipStream_t s) {
+                               hipStream_t s, void* given = nullptr, size_t given_bytes = 0) {
   const int cap_u = h_inv >= 0 ? h_inv + 2 : (int)nu;
   const int cap_v = (int)nv;
   // (the inverse's fix-up takes a product of v and all of w)
   const DivCfg cfg = div_cfg(cap_u, cap_v, h_inv >= 0 ? h_inv + 24 : div_product_limbs(nu, nv), batch);
   const int grid = div_chunk(cfg, batch);
   const size_t bytes = div_ws_bytes(cap_u, cap_v, grid);
+  if (given_bytes >= bytes)
+    return launch_divmod(q, nullptr, r, nullptr, status, u, nullptr, (int)nu, v, nullptr, (int)nv, nullptr, batch,
+                         given, cfg, grid, h_inv, nullptr, s);
   void* ws = nullptr;
   hipError_t e = hipMallocAsync(&ws, bytes, s);
   if (e != hipSuccess) { set_hip_error(e); return BIGINT_ENOMEM; }
@@ -1066,8 +1069,9 @@ static int divmod_launch_alloc(uint32_t* q, uint32_t* r, int32_t* status, const 
   return BIGINT_OK;
 }
 
-int bigint_divmod(uint32_t* q, uint32_t* r, int32_t* status, const uint32_t* u, int64_t nu,
-                  const uint32_t* v, int64_t nv, int64_t batch, void* stream) {
+// the argument checks of the uniform divisions
+static int divmod_check(uint32_t* q, uint32_t* r, int32_t* status, const uint32_t* u, int64_t nu, const uint32_t* v,
+                        int64_t nv, int64_t batch) {
   if (!q || !r || !u || !v || nu <= 0 || nv <= 0 || batch < 0) return BIGINT_EINVAL;
   if (nu > BIGINT_DIV_MAX_LIMBS || nv > BIGINT_DIV_MAX_LIMBS || batch > 0x7fffffff)
     return BIGINT_EUNSUPPORTED;
@@ -1079,27 +1083,46 @@ int bigint_divmod(uint32_t* q, uint32_t* r, int32_t* status, const uint32_t* u, 
   if (status && (overlap(status, sb, q, qb) || overlap(status, sb, r, rb) ||
                  overlap(status, sb, u, ub) || overlap(status, sb, v, vb)))
     return BIGINT_EINVAL;
-  if (batch == 0) return BIGINT_OK;
+  return BIGINT_OK;
+}
+
+int bigint_divmod(uint32_t* q, uint32_t* r, int32_t* status, const uint32_t* u, int64_t nu,
+                  const uint32_t* v, int64_t nv, int64_t batch, void* stream) {
+  const int rc = divmod_check(q, r, status, u, nu, v, nv, batch);
+  if (rc != BIGINT_OK || batch == 0) return rc;
   return divmod_launch_alloc(q, r, status, u, nu, v, nv, batch, -1, (hipStream_t)stream);
+}
+
+int bigint_divmod_workspace_size(int64_t nu, int64_t nv, int64_t batch, size_t* bytes) {
+  if (nu <= 0 || nv <= 0 || batch < 0 || !bytes) return BIGINT_EINVAL;
+  *bytes = 0;
+  if (nu > BIGINT_DIV_MAX_LIMBS || nv > BIGINT_DIV_MAX_LIMBS || batch > 0x7fffffff) return BIGINT_EUNSUPPORTED;
+  if (batch > 0)
+    *bytes = div_ws_bytes((int)nu, (int)nv,
+                          div_chunk(div_cfg((int)nu, (int)nv, div_product_limbs(nu, nv), batch), batch));
+  return BIGINT_OK;
+}
+
+int bigint_divmod_ws(uint32_t* q, uint32_t* r, int32_t* status, const uint32_t* u, int64_t nu, const uint32_t* v,
+                     int64_t nv, int64_t batch, void* ws, size_t ws_bytes, void* stream) {
+  const int rc = divmod_check(q, r, status, u, nu, v, nv, batch);
+  if (rc != BIGINT_OK) return rc;
+  if ((!ws && ws_bytes) || ((uintptr_t)ws & 15)) return BIGINT_EINVAL;
+  const size_t ub = (size_t)nu * batch * 4, vb = (size_t)nv * batch * 4;
+  if (overlap(ws, ws_bytes, q, ub) || overlap(ws, ws_bytes, r, vb) || overlap(ws, ws_bytes, u, ub) ||
+      overlap(ws, ws_bytes, v, vb) || (status && overlap(ws, ws_bytes, status, (size_t)batch * 4)))
+    return BIGINT_EINVAL;
+  if (batch == 0) return BIGINT_OK;
+  return divmod_launch_alloc(q, r, status, u, nu, v, nv, batch, -1, (hipStream_t)stream, ws, ws_bytes);
 }
 
 int bigint_divmod_noalloc(uint32_t* q, uint32_t* r, int32_t* status, const uint32_t* u, int64_t nu,
                           const uint32_t* v, int64_t nv, int64_t batch, void* stream) {
-  if (!q || !r || !u || !v || nu <= 0 || nv <= 0 || batch < 0) return BIGINT_EINVAL;
-  if (nu > BIGINT_DIV_MAX_LIMBS || nv > BIGINT_DIV_MAX_LIMBS || batch > 0x7fffffff)
-    return BIGINT_EUNSUPPORTED;
-  const size_t qb = (size_t)nu * batch * 4, rb = (size_t)nv * batch * 4;
-  const size_t ub = (size_t)nu * batch * 4, vb = (size_t)nv * batch * 4, sb = (size_t)batch * 4;
-  if (overlap(q, qb, u, ub) || overlap(q, qb, v, vb) || overlap(r, rb, u, ub) ||
-      overlap(r, rb, v, vb) || overlap(q, qb, r, rb))
-    return BIGINT_EINVAL;
-  if (status && (overlap(status, sb, q, qb) || overlap(status, sb, r, rb) ||
-                 overlap(status, sb, u, ub) || overlap(status, sb, v, vb)))
-    return BIGINT_EINVAL;
-  if (batch == 0) return BIGINT_OK;
+  int rc = divmod_check(q, r, status, u, nu, v, nv, batch);
+  if (rc != BIGINT_OK || batch == 0) return rc;
   void* ws = nullptr;
   size_t cap = 0;
-  const int rc = div_scratch(&ws, &cap);
+  rc = div_scratch(&ws, &cap);
   if (rc != BIGINT_OK) return rc;
   // work-groups per launch: as bigint_divmod, but no more workspace slots
   // than the scratch array holds (the launches run one after another)

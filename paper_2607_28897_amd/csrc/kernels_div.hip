@@ -97,8 +97,12 @@ DivCfg div_cfg(int cap_u, int cap_v, int64_t prod, int64_t batch) {
   return best;
 }
 
+// divisions per launch, a workspace slot each: 8 rounds of those resident, or
+// what 640 MiB hold, but at least two rounds
 int div_chunk(const DivCfg& c, int64_t batch) {
-  return (int)std::max<int64_t>(1, std::min<int64_t>(batch, (int64_t)8 * num_cus() * c.per_cu));
+  const int64_t resident = (int64_t)num_cus() * c.per_cu;
+  const int64_t fit = ((int64_t)640 << 20) / (int64_t)div_ws_bytes(c.cap_u, c.cap_v, 1);
+  return (int)std::max<int64_t>(1, std::min(batch, std::min(8 * resident, std::max(2 * resident, fit))));
 }
 
 // ---- workspace of the allocation-free division (bigint_divmod_noalloc) ----------

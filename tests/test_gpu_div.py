@@ -414,3 +414,41 @@ def test_carry_chains(bi, orc, nu, nv, batch):
     for i in range(rows):
         wq, wr, _ = orc.divmod1(u[i], v[i])
         assert bool((q[i::rows] == dev(wq)).all()) and bool((r[i::rows] == dev(wr)).all()), i
+
+
+def test_workspace_of_the_caller(bi):
+    """bigint_divmod_ws: the size asked for, a smaller one (the call allocates
+    as bigint_divmod does) and overlapping or misaligned ones (refused); and
+    the binding's workspace under graph capture, replayed on new inputs."""
+    import ctypes
+    import torch
+    L = bi.lib()
+    g = np.random.default_rng(4)
+    u, v = dev(rand_limbs(g, 40, 700)), dev(rand_limbs(g, 40, 350))
+    want = bi.divmod(u, v)
+    size = ctypes.c_size_t()
+    assert L.bigint_divmod_workspace_size(700, 350, 40, ctypes.byref(size)) == bi.OK and size.value > 0
+    assert L.bigint_divmod_workspace_size(16385, 350, 40, ctypes.byref(size)) == bi.EUNSUPPORTED
+    assert L.bigint_divmod_workspace_size(700, 350, 40, ctypes.byref(size)) == bi.OK
+    ws = torch.empty(size.value + 16, dtype=torch.uint8, device="cuda")
+    s = torch.cuda.current_stream().cuda_stream
+    for n in (size.value, size.value // 2, 0):
+        q, r = torch.empty_like(u), torch.empty_like(v)
+        st = torch.empty(40, dtype=torch.int32, device="cuda")
+        args = (q.data_ptr(), r.data_ptr(), st.data_ptr(), u.data_ptr(), 700, v.data_ptr(), 350, 40)
+        assert L.bigint_divmod_ws(*args, ws.data_ptr(), n, s) == bi.OK
+        assert all(bool((x == y).all()) for x, y in zip((q, r, st), want)), n
+    assert L.bigint_divmod_ws(*args, ws.data_ptr() + 4, size.value, s) == bi.EINVAL
+    assert L.bigint_divmod_ws(*args, q.data_ptr(), 4096, s) == bi.EINVAL
+    assert L.bigint_divmod_ws(*args, None, 4096, s) == bi.EINVAL
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        got = bi.divmod(u, v)
+    for seed in (5, 6, 7):
+        g = np.random.default_rng(seed)
+        u.copy_(dev(rand_limbs(g, 40, 700)))
+        v.copy_(dev(rand_limbs(g, 40, 350)))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(bool((x == y).all()) for x, y in zip(got, bi.divmod(u, v))), seed
