@@ -524,13 +524,15 @@ __device__ __noinline__ bool wg_mul(uint32_t* dst, const uint32_t* a, int na, co
 // no work-group barrier and no global round trip, while the other waves
 // wait at one barrier.  (On the whole work-group each such step took
 // 10-12 us, nearly all of it the fixed latency of a dozen passes and
-// barriers.  Four limbs per lane, which takes one more step onto the wave,
-// measured 1% slower: one wave's serial column sums then cost as much as
-// the work-group's step.)
+// barriers.  The column sums wait on the LDS: with bounds per column and one
+// read after another one division of 512 by 256 limbs took 90 us, with a
+// padded factor and four steps in flight 80; 16384 of them 658 and 596.  Four
+// limbs per lane, one more step on the wave: the same from 512 limbs on, and
+// 64 by 32 limbs 31 us against 25.)
 constexpr int kWaveGroups = 2;                             // limbs per lane
 constexpr int kWaveLimbs = 64 * kWaveGroups;
 constexpr int kEarlyArr = kWaveLimbs + 8;                  // limbs per LDS array
-constexpr size_t kEarlyLds = (size_t)5 * kEarlyArr * 4;   // w, new w, e, w e, V
+constexpr size_t kEarlyLds = (size_t)(5 * kEarlyArr + 2 * kWaveLimbs + 4) * 4;   // w, new w, e, w e, V, a padded factor
 
 __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -538,28 +540,62 @@ __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// dst[0 .. n) = a * b mod B^n for n <= kWaveLimbs, operands and result in
-// LDS (dst must not overlap them); lane l forms columns l + 64 g
-__device__ inline void wave_mul_lds(uint32_t* dst, const uint32_t* sa, int na, const uint32_t* sb,
-                                    int nb, int n) {
-  const int l = lane_id();
-  uint64_t s[kWaveGroups];
-  uint32_t c[kWaveGroups];
+// dst[0 .. n) = a * b mod B^n for n <= 64 H, operands and result in LDS (dst
+// must not overlap them); lane l forms columns l + 64 g.  sp: b's limbs with
+// zeros on both sides, so that column k meets a_i at sp[k - i] with no bounds
+// to look at, and four steps' reads are in flight together.
+template <int H>
+__device__ __forceinline__ void wave_cols(uint32_t* dst, const uint32_t* sa, int na, const uint32_t* sp, int n) {
+  const uint32_t* col = sp + lane_id();
+  uint64_t s[H] = {};
+  uint32_t c[H] = {};
+#pragma unroll 1
+  for (int i = 0; i < na; i += 4) {
+    uint32_t x[4], y[4][H];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      x[u] = sa[i + u];
+#pragma unroll
+      for (int g = 0; g < H; ++g) y[u][g] = col[64 * g - i - u];
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      x[u] = i + u < na ? x[u] : 0u;
+#pragma unroll
+      for (int g = 0; g < H; ++g) {
+        const uint64_t t = (uint64_t)x[u] * y[u][g] + s[g];
+        c[g] += t < s[g];
+        s[g] = t;
+      }
+    }
+  }
+  wave_cols_to_limbs<H>(s, c, dst, n);
+}
+
+// dst[0 .. n) = a * b mod B^n on one wave, n <= kWaveLimbs, na and nb below
+// it; spad: 2 kWaveLimbs + 4 limbs whose first half and 4 limbs are zero
+__device__ inline void wave_mul_lds(uint32_t* dst, const uint32_t* sa, int na, const uint32_t* sb, int nb, int n,
+                                    uint32_t* spad) {
+  if (na > nb) {
+    const uint32_t* t = sa;
+    sa = sb;
+    sb = t;
+    const int k = na;
+    na = nb;
+    nb = k;
+  }
+  uint32_t* sp = spad + kWaveLimbs + 4;
 #pragma unroll
   for (int g = 0; g < kWaveGroups; ++g) {
-    const int k = l + 64 * g;
-    uint64_t sum = 0;
-    uint32_t cnt = 0;
-    const int lo = max(0, k - nb + 1), hi = min(min(k, na - 1), k < n ? k : -1);
-    for (int i = lo; i <= hi; ++i) {
-      const uint64_t t = (uint64_t)sa[i] * sb[k - i] + sum;
-      cnt += t < sum;
-      sum = t;
-    }
-    s[g] = sum;
-    c[g] = cnt;
+    const int j = lane_id() + 64 * g;
+    sp[j] = j < nb ? sb[j] : 0u;
   }
-  wave_cols_to_limbs<kWaveGroups>(s, c, dst, n);
+  wave_lds_sync();
+  na = min(na, n);
+  if (n <= 64) wave_cols<1>(dst, sa, na, sp, n);
+  else if (n <= 128 || kWaveGroups <= 2) wave_cols<2>(dst, sa, na, sp, n);
+  else if (n <= 192) wave_cols<3>(dst, sa, na, sp, n);
+  else wave_cols<kWaveGroups>(dst, sa, na, sp, n);
   wave_lds_sync();
 }
 
@@ -609,8 +645,17 @@ __device__ inline void wave_newton_early(const uint32_t* v, int k1, int h, uint3
   uint32_t* sU = sW + kEarlyArr;
   uint32_t* sE = sU + kEarlyArr;
   uint32_t* sT = sE + kEarlyArr;
-  uint32_t* sV = sT + kEarlyArr;
+  uint32_t* sV = sT + kEarlyArr;   // the divisor's top limbs
+  uint32_t* spad = sV + kEarlyArr;
   const int l = lane_id();
+  const int nv = min(k1, kWaveLimbs);
+#pragma unroll
+  for (int g = 0; g < kWaveGroups; ++g) {
+    const int j = l + 64 * g;
+    if (j < nv) sV[j] = v[k1 - nv + j];
+    spad[j] = 0u;
+  }
+  if (l < 4) spad[kWaveLimbs + l] = 0u;
 #pragma unroll
   for (int g = 0; g < kWaveGroups; ++g) {
     const int j = l + 64 * g;
@@ -627,14 +672,8 @@ __device__ inline void wave_newton_early(const uint32_t* v, int k1, int h, uint3
     const int ly = lw + le - sd;
     const int lnew = lw + m + 1;
     if (le > kWaveLimbs || ly > kWaveLimbs || lnew > kWaveLimbs) break;
-#pragma unroll
-    for (int g = 0; g < kWaveGroups; ++g) {
-      const int j = l + 64 * g;
-      if (j < t) sV[j] = v[sdrop + j];
-    }
-    wave_lds_sync();
     // powDiff from the low product, as on the work-group
-    wave_mul_lds(sE, sV, t, sW, lw, le);
+    wave_mul_lds(sE, sV + (nv - t), t, sW, lw, le, spad);
     const uint32_t top = __builtin_amdgcn_readfirstlane(sE[le - 1]);
     const bool neg = top == 0u;
     if (!neg) {
@@ -647,7 +686,7 @@ __device__ inline void wave_newton_early(const uint32_t* v, int k1, int h, uint3
       adjust[1] += neg ? 1 : 0;
     }
     // step (the whole product w |e|: the ceiling's dropped-limb test is exact)
-    wave_mul_lds(sT, sW, lw, sE + sd, le - sd, ly);
+    wave_mul_lds(sT, sW, lw, sE + sd, le - sd, ly, spad);
     const int sy = c - m - sd;
     uint32_t cin = 0u;
     if (neg) {
