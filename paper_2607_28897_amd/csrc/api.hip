@@ -274,8 +274,10 @@ static bool split_forced() { return t_cfg_P || t_cfg_waves || t_cfg_dw || t_cfg_
 // for those sizes; the transform 12, 12, 15, 25, 60 and 108, with its
 // quarters apart 18 and 24 for the last two).  The estimates are good to some
 // 10 %, so the transform is taken where it is ahead by more than that.
+// Products mod B^n take half the first and 1.5e-3 of the second term (1024
+// limbs 4.2, 1536 7.7).
 static double mfma_load(int64_t na, int64_t nb, bool low) {
-  return 2.4e-6 * (low ? 0.5 : 1.0) * (double)na * (double)nb + 2.7e-3 * (double)(na + nb);
+  return (low ? 1.2e-6 : 2.4e-6) * (double)na * (double)nb + (low ? 1.5e-3 : 2.7e-3) * (double)(na + nb);
 }
 
 constexpr int kNttQuarters = 1000;   // ntt_choice: the quarters apart
