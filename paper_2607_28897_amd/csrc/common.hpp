@@ -100,6 +100,14 @@ __device__ __forceinline__ uint32_t wave_carry_out(const WaveCarry& w, uint32_t 
   return o1 | o2;
 }
 
+// the carry out of bit 63 and the carries into every bit of g + p bits with
+// carry c into bit 0 (p: propagate, g: generate, disjoint)
+__device__ __forceinline__ uint64_t carry_bits(uint64_t g, uint64_t p, uint32_t& c) {
+  const uint64_t a = g | p, s = a + g + c;
+  c = (uint32_t)(g >> 32 | (a >> 32 & ~(s >> 32))) >> 31;
+  return s ^ a ^ g;
+}
+
 // Work-group wide exclusive carry scan.  Every thread passes the (g, p)
 // summary of its own limb run; returns the carry entering that run.  cin is
 // the carry entering the whole work-group range.  `scratch` is >= 16 u32 of

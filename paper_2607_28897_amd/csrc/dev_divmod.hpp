@@ -274,14 +274,6 @@ struct LinResult {
 };
 constexpr int kLinRounds = 16;
 
-// the carry out of bit 63 and the carries into every bit of g + p bits with
-// carry c into bit 0 (p: propagate, g: generate, disjoint)
-__device__ __forceinline__ uint64_t carry_bits(uint64_t g, uint64_t p, uint32_t& c) {
-  const uint64_t a = g | p, s = a + g + c;
-  c = (uint32_t)(g >> 32 | (a >> 32 & ~(s >> 32))) >> 31;
-  return s ^ a ^ g;
-}
-
 // dst[0 .. n) = x B^at + y + c, or x B^at - y - c with sub, modulo B^n (n >= 1;
 // dst may be x's or y's storage, the former with at = 0); with y = {nullptr, 0}
 // its limb 0 is low.

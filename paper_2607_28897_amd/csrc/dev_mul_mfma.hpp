@@ -784,7 +784,119 @@ __device__ __forceinline__ void run_band32(int band, const Lds& s, const Geo& g,
   }
 }
 
-template <int DW, int P>
+// ---- signed digits (one wave per product) ------------------------------------------
+// The offset digits above need, for every coefficient, the digit sums that the
+// offset of 128 brings in.  Recoding the operand instead takes that term
+// away: with C = sum_i 128 256^i, the bytes of a + C less 128 each are signed
+// digits whose sum is a itself (the carry out of the top limb is one more
+// digit, 0 or 1).  The addition's carries are ballots of the wave that stages
+// the operand.  The coefficients are then signed, and so are the carries
+// between limbs and strips; a bias keeps the strips' carry words positive.
+
+constexpr int kStripBias = 1 << 24;   // above any strip's carry (2^20 at 2048 limbs)
+
+// limb l of a + C less C digit by digit, for l = 64 r + lane (l >= n: the
+// last carry at l = n, then 0); c: the carry into the round, updated
+__device__ __forceinline__ uint32_t signed_digits(uint32_t x, uint32_t& c) {
+  const uint32_t t = x + 0x80808080u;
+  const uint64_t g = __ballot(t < x), p = __ballot(t == ~0u);
+  const uint64_t in = carry_bits(g, p, c);
+  return (t + (__builtin_amdgcn_inverse_ballot_w64(in) ? 1u : 0u)) ^ 0x80808080u;
+}
+
+// Stage the signed digits of both operands (one wave; layout as stage<8>).
+// Adds each operand's last carry to its digit count.
+__device__ __forceinline__ void stage_signed(const Lds& s, Geo& g, const uint32_t* a, const uint32_t* b) {
+  constexpr int U = 4;
+  const int lane = lane_id();
+  uint32_t* A32 = reinterpret_cast<uint32_t*>(s.A);
+  uint32_t* B32 = reinterpret_cast<uint32_t*>(s.B);
+  const Limbs a_(a, g.na), b_(b, g.nb);
+  {
+    // dword QA/4 - 1 - l holds digits 4 l + 4 .. 4 l + 1; limb l - 1 is written
+    // with limb l at hand, so limb 0's low digit goes with "limb -1"
+    const int top = g.QA / 4, rounds = g.na / 64 + 1;   // (the round of limb na included)
+    for (int d = lane; d < top - 1 - g.na; d += 64) A32[d] = 0u;
+    for (int d = top + 1 + lane; d < g.SA / 4; d += 64) A32[d] = 0u;
+    uint32_t c = 0u, below = 0u;   // below: limb 64 r - 1
+    for (int r0 = 0; r0 < rounds; r0 += U) {
+      uint32_t x[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) x[u] = a_(64 * (r0 + u) + lane);
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (r0 + u < rounds) {
+          const int l = 64 * (r0 + u) + lane;
+          const uint32_t v = signed_digits(x[u], c);
+          // limb l - 1: the lane below (DPP wave_shr:1), below into lane 0
+          const uint32_t w = (uint32_t)__builtin_amdgcn_update_dpp((int)below, (int)v, 0x138, 0xf, 0xf, false);
+          below = (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+          if (l <= g.na) A32[top - l] = __builtin_bswap32(__builtin_amdgcn_alignbyte(v, w, 1));
+          if (r0 + u == rounds - 1) g.Na += __builtin_amdgcn_readlane((int)v, g.na & 63);
+        }
+    }
+    // digits 4 na + 1 .. 4 na + 3 and those above are zero
+    if (lane == 0) A32[top - 1 - g.na] = 0u;
+  }
+  {
+    const int base = kPadB / 4, end = g.SB / 4 - base, rounds = (end + 63) / 64;
+    if (lane < base) B32[lane] = 0u;
+    uint32_t c = 0u;
+    for (int r0 = 0; r0 < rounds; r0 += U) {
+      uint32_t x[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) x[u] = b_(64 * (r0 + u) + lane);
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (r0 + u < rounds) {
+          const int l = 64 * (r0 + u) + lane;
+          const uint32_t v = signed_digits(x[u], c);
+          if (l < end) B32[base + l] = v;
+          if (r0 + u == g.nb / 64) g.Nb += __builtin_amdgcn_readlane((int)v, g.nb & 63);
+        }
+    }
+  }
+}
+
+// Strip w from signed digits: its 64 limbs and carry word (+ kStripBias, which
+// strip w + 1 takes off its lowest limb).  With X_j the sum of limb j's four
+// coefficients (|X_j| < 2^52), limb j takes L_j + H_(j-1) - 1 + B, whose carry
+// is 0, 1 or 2; after that carry has moved up, what is left is a sum of
+// 32-bit words with carries 0 or 1, as with the offset digits.
+__device__ __forceinline__ void strip_out_signed(v4i acc, int w, const Lds& s, const Geo& g, uint32_t* out) {
+  const int lane = lane_id();
+  int32_t* sc = s.wscr;
+#pragma unroll
+  for (int v = 0; v < 4; ++v) sc[16 * (4 * (lane >> 4) + v) + (lane & 15)] = acc[v];
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+  const v4i cp = *reinterpret_cast<const v4i*>(sc + 4 * lane);
+  __builtin_amdgcn_wave_barrier();
+  int64_t X = cp[0];
+  X += (int64_t)cp[1] * 256;
+  X += (int64_t)cp[2] * 65536;
+  X += (int64_t)cp[3] * 16777216;
+  const uint32_t L = (uint32_t)X;
+  const int H = (int)(X >> 32);
+  const int h = __builtin_amdgcn_update_dpp(w > 0 ? 1 - kStripBias : 1, H, 0x138, 0xf, 0xf, false) - 1;
+  const uint32_t t = L + (uint32_t)h;
+  const int up = (t < L ? 1 : 0) + (h >> 31) + 1;
+  const uint32_t from = (uint32_t)__builtin_amdgcn_update_dpp(0, up, 0x138, 0xf, 0xf, false);
+  const uint32_t y = t + from;
+  const uint64_t gm = __ballot(y < t), pm = __ballot(y == ~0u);
+  uint32_t cout = 0u;
+  const uint64_t in = carry_bits(gm, pm, cout);
+  const uint32_t limb = y + (__builtin_amdgcn_inverse_ballot_w64(in) ? 1u : 0u);
+  const int jg = 64 * w + lane;
+  const uint64_t tail = ~3ull;   // limbs 2..63
+  const uint64_t ones = __ballot(jg >= g.nout || limb == 0xffffffffu);
+  if (jg < g.nout) out[jg] = limb;
+  if (lane == 63)
+    s.carry[w] = (uint64_t)(uint32_t)(H - 1 + up + (int)cout + kStripBias) |
+                 ((uint64_t)((ones & tail) == tail) << 63);
+}
+
+template <int DW, int P, bool SIGNED = false>
 __device__ __forceinline__ void run_band(int band, const Lds& s, const Geo& g, uint32_t* out, int32_t* coef) {
   const int w0 = band * P;
   v4i acc[P];
@@ -796,7 +908,9 @@ __device__ __forceinline__ void run_band(int band, const Lds& s, const Geo& g, u
 #pragma unroll
   for (int i = 0; i < P; ++i)
     if (w0 + i < g.W) {
-      if constexpr (DW == 8) {
+      if constexpr (SIGNED) {
+        strip_out_signed(acc[i], w0 + i, s, g, out);
+      } else if constexpr (DW == 8) {
         if (i == 0) S = strip_start_sum(s, g, w0);
         S = strip_out8(acc[i], w0 + i, s, g, out, S);
       } else {
@@ -969,14 +1083,19 @@ __device__ __forceinline__ void wg_mul_mfma(uint32_t* out, int32_t* coef, const 
 // sums, band scheduling, the strip carry scan) and their barriers cost more
 // than the MFMA work, so several instances share a work-group, one wave each
 // (the paper's ipb instances per block), and every phase runs inside the
-// wave: the same staging, block sums and bands, and the strip carry scan on
-// one lane per strip.  Needs W <= 64 strips (na + nb <= 4096 limbs).
+// wave: the staging with its recoding to signed digits, the bands, and the
+// strip carry scan on one lane per strip.  Needs W <= 64 strips (na + nb <=
+// 4096 limbs).  The vector ALU bounds it (256 limbs: 74 % busy, the matrix
+// cores 16 %): with offset digits and their sums 2457 vector instructions a
+// product, half of them for the strips' output, and 85.7 us for 16384
+// products; with signed digits 64.9 us.  (128 limbs: 43.4 and 32.7 us; 512
+// limbs: 172 and 143.)
 
 // LDS bytes of one wave's instance (8-bit digits): operands, the wave's
 // scratch, strip carries, misc, block prefix sums
 __host__ __device__ inline size_t wave_lds_bytes(int na, int nb) {
   const Geo g = make_geo<8>(na, nb);
-  return (((size_t)g.SA + g.SB + 1024 + (size_t)8 * g.W + 128 + bs_bytes(g)) + 15) & ~(size_t)15;
+  return (((size_t)g.SA + g.SB + 1024 + (size_t)8 * g.W) + 15) & ~(size_t)15;
 }
 
 __device__ __forceinline__ Lds carve_wave(char* smem, const Geo& g) {
@@ -985,11 +1104,10 @@ __device__ __forceinline__ Lds carve_wave(char* smem, const Geo& g) {
   s.A = reinterpret_cast<uint8_t*>(p); p += g.SA;
   s.B = reinterpret_cast<uint8_t*>(p); p += g.SB;
   s.scr = s.wscr = reinterpret_cast<int32_t*>(p); p += 1024;
-  s.carry = reinterpret_cast<uint64_t*>(p); p += 8 * g.W;
+  s.carry = reinterpret_cast<uint64_t*>(p);
   s.order = nullptr;
-  s.misc = reinterpret_cast<uint32_t*>(p); p += 128;
-  s.bsa = reinterpret_cast<int32_t*>(p);
-  s.bsb = s.bsa + g.NBa + 1;
+  s.misc = nullptr;
+  s.bsa = s.bsb = nullptr;
   return s;
 }
 
@@ -1000,25 +1118,21 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// out[0 .. nout) = a * b mod B^nout on the calling wave alone (offset 8-bit
+// out[0 .. nout) = a * b mod B^nout on the calling wave alone (signed 8-bit
 // digits; nout < 0: the whole na+nb limbs); smem: wave_lds_bytes(na, nb)
 // bytes of this wave's own LDS.
 template <int P>
 __device__ __forceinline__ void wave_mul_mfma(uint32_t* out, const uint32_t* __restrict__ a, int na,
                                               const uint32_t* __restrict__ b, int nb, char* smem,
                                               int nout = -1) {
-  const Geo g = make_geo<8>(na, nb, nout);
+  Geo g = make_geo<8>(na, nb, nout);
   const Lds s = carve_wave(smem, g);
   const int lane = lane_id();
-  stage<8>(s, g, a, b, lane, 64);
-  wave_sync();
-  block_sums(s, g, 0, 1);
-  wave_sync();
-  block_prefix(s, g, 0, 1);
+  stage_signed(s, g, a, b);
   wave_sync();
   const int NB = (g.W + P - 1) / P;
 #pragma unroll 1
-  for (int band = 0; band < NB; ++band) run_band<8, P>(band, s, g, out, nullptr);
+  for (int band = 0; band < NB; ++band) run_band<8, P, true>(band, s, g, out, nullptr);
   wave_sync();
   // strip carries (one lane per strip), as in wg_mul_mfma's closing scan
   constexpr int kStripLimbs = strip_limbs<8>();

@@ -521,3 +521,23 @@ def test_tile_query_and_errors(bi):
         bi.set_mfma_config(0, 0, 0)
         bi.set_mfma_tile(0)
 
+
+
+@pytest.mark.parametrize("na,nb", [(1, 1), (2, 63), (63, 64), (64, 64), (65, 127), (128, 128), (191, 64), (256, 256),
+                                   (257, 255), (511, 512), (512, 64), (600, 1)])
+def test_signed_digit_recoding(bi, orc, na, nb):
+    """One wave per product: operands whose bytes sit where the recoding to
+    signed digits carries (0x7f, 0x80, 0xff runs, the carry out of the top
+    limb), full products and products mod B^n."""
+    g = np.random.default_rng(na * 1000 + nb)
+    pool = np.array([0x7F7F7F7F, 0x7F7F7F80, 0x80808080, 0x80000000, 0x7FFFFFFF, 0xFFFFFFFF, 0, 1, 0x80, 0x8080],
+                    np.uint64).astype(np.uint32)
+    a, b = pool[g.integers(0, 10, (70, na))], pool[g.integers(0, 10, (70, nb))]
+    for i, (x, y) in enumerate([(7, 7), (0, 0), (2, 2), (5, 5), (0, 5), (2, 0), (5, 2), (3, 3)]):
+        a[i], b[i] = pool[x], pool[y]
+    got = host(bi.mul(dev(a), dev(b), bi.MUL_MFMA))
+    exp = [orc.mul1(a[i], b[i]) for i in range(70)]
+    assert [i for i in range(70) if not np.array_equal(got[i], exp[i])] == []
+    if na == nb:
+        low = host(bi.mullo(dev(a), dev(b)))
+        assert [i for i in range(70) if not np.array_equal(low[i], exp[i][:na])] == []
