@@ -496,7 +496,7 @@ __host__ __device__ inline int64_t mfma_pairs(int na, int nb, int nout, int nlo)
 // overlap a, b): small operands by column sums, the rest on the MFMA-split
 // multiply.  nlo > 0: only the limbs from nlo up are needed, and the MFMA
 // multiply may skip the strips below (dst[nlo ..) is then floor(a b / B^nlo)
-// or one less).  Returns true when every limb of dst is exact.  One
+// or one more).  Returns true when every limb of dst is exact.  One
 // out-of-line copy serves every call site of the division, so the kernel's
 // code stays small enough for the instruction cache.
 __device__ __noinline__ bool wg_mul(uint32_t* dst, const uint32_t* a, int na, const uint32_t* b,
@@ -506,7 +506,7 @@ __device__ __noinline__ bool wg_mul(uint32_t* dst, const uint32_t* a, int na, co
     return true;
   }
   if (adjust) adjust[3] += mfma_pairs(na, nb, nout, nlo);
-  mfma::wg_mul_mfma<kDW, kP>(dst, nullptr, a, na, b, nb, smem, nout, nlo);
+  mfma::wg_mul_mfma<kDW, kP, 16, true>(dst, nullptr, a, na, b, nb, smem, nout, nlo);
   return mfma::high_band<kDW>(nlo, kP) == 0;
 }
 
@@ -1013,21 +1013,17 @@ __device__ inline int shifted_inverse(const uint32_t* v, int k1, int h, Bufs& bf
     const int sd = max(0, min(le - 1, c - m - 1 - lw));
     const int sy = c - m - sd;           // Y / B^sy
     // only the limbs from sy up are needed: a high product, which may come
-    // out one unit low (inside the error bound as well)
+    // out one unit high (inside the error bound as well)
     const bool exact = wg_mul(bf.T, bf.W, lw, bf.E + sd, le - sd, smem, -1, adjust, sy);
     const int ly = lw + le - sd;
     // negative branch: the ceiling takes one more unit unless the dropped
-    // limbs Y[0 .. sy) are all zero (nullUpToInd); when the high product left
-    // them out it always takes it (one unit more at most)
+    // limbs Y[0 .. sy) are all zero (nullUpToInd); a high product that left
+    // them out is floor or floor + 1 already
     uint32_t cin = 0u;
-    if (neg) {
-      if (exact) {
-        int nz = 0;
-        for (int j = threadIdx.x; j < min(sy, ly); j += blockDim.x) nz |= bf.T[j] != 0u;
-        cin = __syncthreads_or(nz) ? 1u : 0u;
-      } else {
-        cin = 1u;
-      }
+    if (neg && exact) {
+      int nz = 0;
+      for (int j = threadIdx.x; j < min(sy, ly); j += blockDim.x) nz |= bf.T[j] != 0u;
+      cin = __syncthreads_or(nz) ? 1u : 0u;
     }
     const LinResult sum = wg_lin(bf.U2, lw + m + 1, {bf.W, lw}, m, {bf.T + sy, max(0, ly - sy)}, neg, cin, 0u,
                                  nullptr, 0, sh);
@@ -1120,7 +1116,7 @@ __device__ inline int wg_divmod(uint32_t* q, int nq, uint32_t* r, int nr, const 
     const int lo = piece * s;             // the piece's lowest limb of q
     // q~ = floor(x w / B^h2), from the top limbs of x only: the low su limbs
     // add less than B^(su+lw) <= B^(h2-1) to x w, so they move q~ by at most
-    // one unit; a high product (limbs from h2 - su up) takes at most one more
+    // one unit; a high product (limbs from h2 - su up) adds at most one
     const int su = max(0, h2 - 1 - lw);
     const int nd = hd - su;
     wg_mul(bf.T, x + su, nd, bf.W, lw, smem, -1, adjust, h2 - su);

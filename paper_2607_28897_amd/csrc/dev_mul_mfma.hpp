@@ -123,11 +123,11 @@ __host__ __device__ inline size_t lds_bytes(int na, int nb, int nwaves, int P, b
          (size_t)((2 * NB + 15) & ~15) + 128 + (DW == 8 ? bs_bytes(g) : 0);
 }
 
-// enough for any product of operands of na + nb = n limbs in all (8-bit digits)
+// enough for any product of operands of na + nb = n limbs in all (signed digits)
 __host__ __device__ inline size_t lds_bytes_sum(int n, int nwaves, int P) {
   const int W = n / strip_limbs<8>() + 1, NB = (W + P - 1) / P;
   return (size_t)4 * n + 2 * kPadA + kPadB + kPadBt + 64 + (size_t)nwaves * 1024 + (size_t)8 * W +
-         (size_t)((2 * NB + 15) & ~15) + 128 + (size_t)(4 * (n / 64 + 4) + 16);
+         (size_t)((2 * NB + 15) & ~15) + 128;
 }
 
 struct Lds {
@@ -784,16 +784,18 @@ __device__ __forceinline__ void run_band32(int band, const Lds& s, const Geo& g,
   }
 }
 
-// ---- signed digits (one wave per product) ------------------------------------------
+// ---- signed digits ----------------------------------------------------------------
 // The offset digits above need, for every coefficient, the digit sums that the
 // offset of 128 brings in.  Recoding the operand instead takes that term
 // away: with C = sum_i 128 256^i, the bytes of a + C less 128 each are signed
 // digits whose sum is a itself (the carry out of the top limb is one more
-// digit, 0 or 1).  The addition's carries are ballots of the wave that stages
-// the operand.  The coefficients are then signed, and so are the carries
-// between limbs and strips; a bias keeps the strips' carry words positive.
+// digit, 0 or 1).  The addition's carries are ballots of the waves that stage
+// the operand; a wave finds the carry into its part by looking at the limbs
+// below, of which nearly always the first decides.  The coefficients are then
+// signed, and so are the carries between limbs and strips; a bias keeps the
+// strips' carry words positive.
 
-constexpr int kStripBias = 1 << 24;   // above any strip's carry (2^20 at 2048 limbs)
+constexpr int kStripBias = 1 << 24;   // above any strip's carry (2^22 at 18432 limbs)
 
 // limb l of a + C less C digit by digit, for l = 64 r + lane (l >= n: the
 // last carry at l = n, then 0); c: the carry into the round, updated
@@ -804,11 +806,24 @@ __device__ __forceinline__ uint32_t signed_digits(uint32_t x, uint32_t& c) {
   return (t + (__builtin_amdgcn_inverse_ballot_w64(in) ? 1u : 0u)) ^ 0x80808080u;
 }
 
-// Stage the signed digits of both operands (one wave; layout as stage<8>).
-// Adds each operand's last carry to its digit count.
-__device__ __forceinline__ void stage_signed(const Lds& s, Geo& g, const uint32_t* a, const uint32_t* b) {
+// the carry into limb 64 r of a + C
+__device__ __forceinline__ uint32_t signed_carry_into(const Limbs& a, int r) {
+  while (r > 0) {
+    const uint32_t x = a(64 * --r + lane_id()), t = x + 0x80808080u;
+    const uint64_t g = __ballot(t < x), p = __ballot(t == ~0u);
+    if (p != ~0ull) return (uint32_t)(g >> (63 - __clzll(~p))) & 1u;
+  }
+  return 0u;
+}
+
+// Stage the signed digits of both operands (layout as stage<8>) on waves
+// wv = 0 .. nw - 1; with one wave the operands' last carries are returned.
+struct LastDigits { int a, b; };
+__device__ __forceinline__ LastDigits stage_signed(const Lds& s, const Geo& g, const uint32_t* a, const uint32_t* b,
+                                                   int wv, int nw) {
   constexpr int U = 4;
   const int lane = lane_id();
+  LastDigits last{0, 0};
   uint32_t* A32 = reinterpret_cast<uint32_t*>(s.A);
   uint32_t* B32 = reinterpret_cast<uint32_t*>(s.B);
   const Limbs a_(a, g.na), b_(b, g.nb);
@@ -816,54 +831,62 @@ __device__ __forceinline__ void stage_signed(const Lds& s, Geo& g, const uint32_
     // dword QA/4 - 1 - l holds digits 4 l + 4 .. 4 l + 1; limb l - 1 is written
     // with limb l at hand, so limb 0's low digit goes with "limb -1"
     const int top = g.QA / 4, rounds = g.na / 64 + 1;   // (the round of limb na included)
-    for (int d = lane; d < top - 1 - g.na; d += 64) A32[d] = 0u;
-    for (int d = top + 1 + lane; d < g.SA / 4; d += 64) A32[d] = 0u;
+    const int tid = 64 * wv + lane, T = 64 * nw;
+    for (int d = tid; d < top - g.na; d += T) A32[d] = 0u;   // (digits 4 na + 1 and up)
+    for (int d = top + 1 + tid; d < g.SA / 4; d += T) A32[d] = 0u;
+    const int per = (rounds + nw - 1) / nw, first = per * wv, end = min(rounds, first + per);
     uint32_t c = 0u, below = 0u;   // below: limb 64 r - 1
-    for (int r0 = 0; r0 < rounds; r0 += U) {
+    if (first > 0 && first < end) {
+      c = signed_carry_into(a_, first - 1);
+      below = (uint32_t)__builtin_amdgcn_readlane((int)signed_digits(a_(64 * (first - 1) + lane), c), 63);
+    }
+    for (int r0 = first; r0 < end; r0 += U) {
       uint32_t x[U];
 #pragma unroll
       for (int u = 0; u < U; ++u) x[u] = a_(64 * (r0 + u) + lane);
 #pragma unroll
       for (int u = 0; u < U; ++u)
-        if (r0 + u < rounds) {
+        if (r0 + u < end) {
           const int l = 64 * (r0 + u) + lane;
           const uint32_t v = signed_digits(x[u], c);
           // limb l - 1: the lane below (DPP wave_shr:1), below into lane 0
           const uint32_t w = (uint32_t)__builtin_amdgcn_update_dpp((int)below, (int)v, 0x138, 0xf, 0xf, false);
           below = (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
           if (l <= g.na) A32[top - l] = __builtin_bswap32(__builtin_amdgcn_alignbyte(v, w, 1));
-          if (r0 + u == rounds - 1) g.Na += __builtin_amdgcn_readlane((int)v, g.na & 63);
+          if (nw == 1 && r0 + u == rounds - 1) last.a = __builtin_amdgcn_readlane((int)v, g.na & 63);
         }
     }
-    // digits 4 na + 1 .. 4 na + 3 and those above are zero
-    if (lane == 0) A32[top - 1 - g.na] = 0u;
   }
   {
-    const int base = kPadB / 4, end = g.SB / 4 - base, rounds = (end + 63) / 64;
-    if (lane < base) B32[lane] = 0u;
-    uint32_t c = 0u;
-    for (int r0 = 0; r0 < rounds; r0 += U) {
+    const int base = kPadB / 4, n = g.SB / 4 - base, rounds = (n + 63) / 64;
+    if (wv == 0 && lane < base) B32[lane] = 0u;
+    const int per = (rounds + nw - 1) / nw, first = per * wv, end = min(rounds, first + per);
+    uint32_t c = first < end ? signed_carry_into(b_, first) : 0u;
+    for (int r0 = first; r0 < end; r0 += U) {
       uint32_t x[U];
 #pragma unroll
       for (int u = 0; u < U; ++u) x[u] = b_(64 * (r0 + u) + lane);
 #pragma unroll
       for (int u = 0; u < U; ++u)
-        if (r0 + u < rounds) {
+        if (r0 + u < end) {
           const int l = 64 * (r0 + u) + lane;
           const uint32_t v = signed_digits(x[u], c);
-          if (l < end) B32[base + l] = v;
-          if (r0 + u == g.nb / 64) g.Nb += __builtin_amdgcn_readlane((int)v, g.nb & 63);
+          if (l < n) B32[base + l] = v;
+          if (nw == 1 && r0 + u == g.nb / 64) last.b = __builtin_amdgcn_readlane((int)v, g.nb & 63);
         }
     }
   }
+  return last;
 }
 
 // Strip w from signed digits: its 64 limbs and carry word (+ kStripBias, which
 // strip w + 1 takes off its lowest limb).  With X_j the sum of limb j's four
 // coefficients (|X_j| < 2^52), limb j takes L_j + H_(j-1) - 1 + B, whose carry
 // is 0, 1 or 2; after that carry has moved up, what is left is a sum of
-// 32-bit words with carries 0 or 1, as with the offset digits.
-__device__ __forceinline__ void strip_out_signed(v4i acc, int w, const Lds& s, const Geo& g, uint32_t* out) {
+// 32-bit words with carries 0 or 1, as with the offset digits.  w_first: the
+// product's first strip; one unit is added at limb bump.
+__device__ __forceinline__ void strip_out_signed(v4i acc, int w, const Lds& s, const Geo& g, uint32_t* out,
+                                                 int w_first, int bump) {
   const int lane = lane_id();
   int32_t* sc = s.wscr;
 #pragma unroll
@@ -876,9 +899,10 @@ __device__ __forceinline__ void strip_out_signed(v4i acc, int w, const Lds& s, c
   X += (int64_t)cp[1] * 256;
   X += (int64_t)cp[2] * 65536;
   X += (int64_t)cp[3] * 16777216;
+  if (64 * w + lane == bump) X += 1;
   const uint32_t L = (uint32_t)X;
   const int H = (int)(X >> 32);
-  const int h = __builtin_amdgcn_update_dpp(w > 0 ? 1 - kStripBias : 1, H, 0x138, 0xf, 0xf, false) - 1;
+  const int h = __builtin_amdgcn_update_dpp(w > w_first ? 1 - kStripBias : 1, H, 0x138, 0xf, 0xf, false) - 1;
   const uint32_t t = L + (uint32_t)h;
   const int up = (t < L ? 1 : 0) + (h >> 31) + 1;
   const uint32_t from = (uint32_t)__builtin_amdgcn_update_dpp(0, up, 0x138, 0xf, 0xf, false);
@@ -897,7 +921,8 @@ __device__ __forceinline__ void strip_out_signed(v4i acc, int w, const Lds& s, c
 }
 
 template <int DW, int P, bool SIGNED = false>
-__device__ __forceinline__ void run_band(int band, const Lds& s, const Geo& g, uint32_t* out, int32_t* coef) {
+__device__ __forceinline__ void run_band(int band, const Lds& s, const Geo& g, uint32_t* out, int32_t* coef,
+                                         int w_first = 0, int bump = -1) {
   const int w0 = band * P;
   v4i acc[P];
 #pragma unroll
@@ -909,7 +934,7 @@ __device__ __forceinline__ void run_band(int band, const Lds& s, const Geo& g, u
   for (int i = 0; i < P; ++i)
     if (w0 + i < g.W) {
       if constexpr (SIGNED) {
-        strip_out_signed(acc[i], w0 + i, s, g, out);
+        strip_out_signed(acc[i], w0 + i, s, g, out, w_first, bump);
       } else if constexpr (DW == 8) {
         if (i == 0) S = strip_start_sum(s, g, w0);
         S = strip_out8(acc[i], w0 + i, s, g, out, S);
@@ -1001,14 +1026,18 @@ __host__ __device__ inline int high_band(int nlo, int P) {
 // lead (8-bit digits, whole instance; smem sized by lds_bytes with lead):
 // every strip's limbs 0-1 are also kept in LDS, where the closing scan reads
 // them instead of reading them back from out.
-template <int DW, int P, int TS = 16>
+// SIGNED (8-bit digits, 16x16 tiles, whole instances, no raw coefficients):
+// signed digits; with nlo the limbs from nlo up then hold floor(a b / B^nlo)
+// or one more (the part left out can have either sign and is below B^(nlo-1);
+// that much is added).
+template <int DW, int P, int TS = 16, bool SIGNED = false>
 __device__ __forceinline__ void wg_mul_mfma(uint32_t* out, int32_t* coef, const uint32_t* __restrict__ a, int na,
                             const uint32_t* __restrict__ b, int nb, char* smem, int nout = -1,
                             int nlo = 0, int part = 0, int nparts = 1, uint64_t* carry_ext = nullptr,
                             bool lead = false) {
   static_assert(DW == 7 || DW == 8, "digit width");
   static_assert(TS == 16 || (TS == 32 && DW == 8 && P % 4 == 0), "32x32 tiles: 8-bit digits, whole tiles per band");
-  const Geo g = make_geo<DW, TS>(na, nb, coef ? -1 : nout);
+  Geo g = make_geo<DW, TS>(na, nb, coef ? -1 : nout);
   Lds s = carve<DW>(smem, g, P, lead && coef == nullptr && nparts == 1);
   if (nparts > 1) s.carry = carry_ext;
   const int NBall = (g.W + P - 1) / P;
@@ -1017,8 +1046,16 @@ __device__ __forceinline__ void wg_mul_mfma(uint32_t* out, int32_t* coef, const 
   const int w_first = band_lo * P;
   const int NB = NBall - band_lo;
 
-  stage<DW>(s, g, a, b);
-  if constexpr (DW == 8) {
+  if constexpr (SIGNED) {
+    static_assert(DW == 8 && TS == 16, "signed digits");
+    (void)stage_signed(s, g, a, b, __builtin_amdgcn_readfirstlane(wave_id()),
+                       __builtin_amdgcn_readfirstlane(num_waves()));
+    g.Na += 1;   // (the operands' last carries)
+    g.Nb += 1;
+  } else {
+    stage<DW>(s, g, a, b);
+  }
+  if constexpr (DW == 8 && !SIGNED) {
     __syncthreads();
     block_sums(s, g);
     __syncthreads();
@@ -1071,7 +1108,7 @@ __device__ __forceinline__ void wg_mul_mfma(uint32_t* out, int32_t* coef, const 
     if ((int)t >= PN) break;
     const int band = band_lo + __builtin_amdgcn_readfirstlane((int)s.order[t]);
     if constexpr (TS == 32) run_band32<P>(band, s, g, out);
-    else run_band<DW, P>(band, s, g, out, coef);
+    else run_band<DW, P, SIGNED>(band, s, g, out, coef, w_first, band_lo > 0 ? nlo - 1 : -1);
   }
   __syncthreads();
   if (coef == nullptr && nparts == 1) close_strips<DW>(out, g, s.carry, w_first, s.misc + 1, s.lead);
@@ -1128,7 +1165,9 @@ __device__ __forceinline__ void wave_mul_mfma(uint32_t* out, const uint32_t* __r
   Geo g = make_geo<8>(na, nb, nout);
   const Lds s = carve_wave(smem, g);
   const int lane = lane_id();
-  stage_signed(s, g, a, b);
+  const LastDigits last = stage_signed(s, g, a, b, 0, 1);
+  g.Na += last.a;
+  g.Nb += last.b;
   wave_sync();
   const int NB = (g.W + P - 1) / P;
 #pragma unroll 1

@@ -452,3 +452,26 @@ def test_workspace_of_the_caller(bi):
         graph.replay()
         torch.cuda.synchronize()
         assert all(bool((x == y).all()) for x, y in zip(got, bi.divmod(u, v))), seed
+
+
+@pytest.mark.parametrize("nu,nv,batch", [(260, 130, 3), (700, 350, 5000), (2400, 1200, 4200), (2400, 1200, 2100),
+                                         (2400, 1200, 7), (8200, 4100, 3), (16384, 8192, 3)])
+def test_digit_carry_runs(bi, orc, nu, nv, batch):
+    """Operands of 0x7f7f7f7f limbs, over which the recoding to signed digits
+    carries from limb to limb and from one wave's part to the next, with the
+    limb that starts the carry at varying places."""
+    g = np.random.default_rng(nu * 3 + batch)
+    rows = min(batch, 8)
+    u, v = np.full((rows, nu), 0x7F7F7F7F, np.uint32), np.full((rows, nv), 0x7F7F7F7F, np.uint32)
+    for x, n in ((u, nu), (v, nv)):
+        for i in range(1, rows):
+            x[i, g.integers(0, n)] = 0x80 if i % 2 else 0x7F7F7F80
+            x[i, 0] = (0x7F7F7F80, 0x7F7F7F7E, 0xFFFFFFFF)[i % 3]
+            if i % 4 == 3:
+                x[i, n // 2:n // 2 + 70] = 0xFFFFFFFF
+    reps = -(-batch // rows)
+    q, r, st = bi.divmod(dev(np.tile(u, (reps, 1))[:batch].copy()), dev(np.tile(v, (reps, 1))[:batch].copy()))
+    assert int(st.abs().sum()) == 0
+    for i in range(rows):
+        wq, wr, _ = orc.divmod1(u[i], v[i])
+        assert bool((q[i::rows] == dev(wq)).all()) and bool((r[i::rows] == dev(wr)).all()), i
