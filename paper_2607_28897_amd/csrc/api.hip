@@ -1,5 +1,6 @@
 // api.hip -- the C-ABI entry points: argument checks, dispatch, plans.
 #include <algorithm>
+#include <cmath>
 #include <climits>
 #include <cstdio>
 #include <cstdlib>
@@ -266,18 +267,20 @@ static bool split_forced() { return t_cfg_P || t_cfg_waves || t_cfg_dw || t_cfg_
 
 // The transform kernel for a uniform batch of na x nb products (mod B^n with
 // low), or -1 where the MFMA multiply is faster.  The MFMA multiply takes
-// about 2.4e-6 na nb + 2.7e-3 (na + nb) us of a CU per product in a large
-// batch (640 limbs 5.2, 1024 7.2, 2048 17, 4096 56, 8192 190, 16384 640; the
+// about 2.2e-6 na nb + 1.4e-3 (na + nb) us of a CU per product in a large
+// batch (640 limbs 3.5, 1024 5.2, 2048 14, 4096 48, 8192 175, 16384 635; the
 // transform takes 3.9, 5.8, 10, 26, 53 and 122 there), and one product alone
 // 9 us plus 0.7 of that up to 50 us, where its bands start to be split over
-// the CUs, and a sixth of the rest (measured 12, 14, 24, 41, 69 and 127 us
-// for those sizes; the transform 12, 12, 15, 25, 60 and 108, with its
-// quarters apart 18 and 24 for the last two).  The estimates are good to some
+// the CUs, and a sixth of the rest (measured 11, 11, 22, 39, 66 and 120 us
+// for those sizes; the transform 11, 11, 15, 24, 60 and 108, with its
+// quarters apart 16 and 22 for the last two).  A last round of products that
+// leaves CUs idle counts half (4096 limbs: batch 256 60 us, 300 85, 512 106).
+// The estimates are good to some
 // 10 %, so the transform is taken where it is ahead by more than that.
-// Products mod B^n take half the first and 1.5e-3 of the second term (1024
-// limbs 4.2, 1536 7.7).
+// Products mod B^n take half the first and 1.2e-3 of the second term (1024
+// limbs 3.7, 1536 6.2).
 static double mfma_load(int64_t na, int64_t nb, bool low) {
-  return (low ? 1.2e-6 : 2.4e-6) * (double)na * (double)nb + (low ? 1.5e-3 : 2.7e-3) * (double)(na + nb);
+  return (low ? 1.1e-6 : 2.2e-6) * (double)na * (double)nb + (low ? 1.2e-3 : 1.4e-3) * (double)(na + nb);
 }
 
 constexpr int kNttQuarters = 1000;   // ntt_choice: the quarters apart
@@ -295,7 +298,8 @@ static int ntt_choice(int64_t na, int64_t nb, int64_t batch, bool low, size_t ws
   }
   const double load = mfma_load(na, nb, low);
   const double lat = 9.0 + 0.7 * std::min(load, 50.0) + std::max(load - 50.0, 0.0) / 6.0;
-  return us <= 0.92 * std::max(lat, load * (double)batch / num_cus()) ? pick : -1;
+  const double x = (double)batch / num_cus();
+  return us <= 0.92 * std::max(lat, 10.0 + load * (x + std::ceil(x)) / 2) ? pick : -1;
 }
 
 static int mul_ntt(uint32_t* out, const uint32_t* a, int64_t na, const uint32_t* b, int64_t nb, int nout,

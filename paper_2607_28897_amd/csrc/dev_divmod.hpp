@@ -506,7 +506,7 @@ __device__ __noinline__ bool wg_mul(uint32_t* dst, const uint32_t* a, int na, co
     return true;
   }
   if (adjust) adjust[3] += mfma_pairs(na, nb, nout, nlo);
-  mfma::wg_mul_mfma<kDW, kP, 16, true>(dst, nullptr, a, na, b, nb, smem, nout, nlo);
+  mfma::wg_mul_mfma<kDW, kP>(dst, nullptr, a, na, b, nb, smem, nout, nlo);
   return mfma::high_band<kDW>(nlo, kP) == 0;
 }
 

@@ -1,4 +1,4 @@
-// dev_mul_mfma.hpp -- the MFMA-split multiply: 7-bit (or offset 8-bit)
+// dev_mul_mfma.hpp -- the MFMA-split multiply: 7-bit (or signed 8-bit)
 // digits, int8 MFMA Toeplitz tiles, int32 accumulation, 64-bit recombination
 // and a carry scan.
 //
@@ -40,20 +40,12 @@
 // 57th column (with its carry) as the strip's carry word C_w.  A final
 // work-group carry scan adds every C_w at limb 56(w+1).
 //
-// Offset 8-bit digits (DW = 8).  The digits are the bytes of the limbs
-// (Na = 4 na), fed to the MFMA as alpha'_i = alpha_i - 128 in [-128, 127]
-// (the byte with its top bit flipped, read as signed), zero outside [0, Na).
-// Then c_k = c'_k + 128 S_k + 2^14 cnt_k with c'_k = sum alpha'_i beta'_j
-// from the MFMA (|alpha' beta'| <= 2^14, so int32 is exact up to 131,071
-// digits), cnt_k = the number of pairs (i, k - i) inside both operands and
-// S_k = sum over those pairs of alpha'_i + beta'_{k-i}.  With PA / PB the
-// prefix sums of alpha' / beta', S_k = PA(k+1) - PA(k+1-Nb) + PB(k+1) -
-// PB(k+1-Na); from one k to the next it changes by alpha'_k - alpha'_{k-Nb}
-// + beta'_k - beta'_{k-Na}, four digits of 4-digit groups that are limbs.
-// A strip (256 coefficients = 64 limbs) takes S at its start from per-block
-// (256 digit) prefix sums plus a partial block, and the rest by a wave scan
-// of those differences.  The strip's limb j then takes X_j = sum_t c_{4j+t}
-// 2^(8t) < 2^58, and the spill of limb 63 is the strip's carry word.
+// Signed 8-bit digits (DW = 8).  The digits are the bytes of a + C less 128
+// each, C = sum_i 128 256^i, in [-128, 127], and the carry out of that sum
+// as one more digit: their sum is a (|alpha beta| <= 2^14, so int32 is exact
+// up to 131,071 digits).  A strip's 256 coefficients are 64 limbs; limb j
+// takes X_j = sum_t c_{4j+t} 2^(8t), |X_j| < 2^56, and the spill of limb 63
+// is the strip's carry word.
 #pragma once
 
 #include "common.hpp"
@@ -85,7 +77,6 @@ struct Geo {
   int SB;   // bytes of Bbuf; Bbuf[kPadB + j] = beta[j]
   int W;    // strips
   int nout; // na + nb
-  int NBa, NBb;  // 8-bit digits: 256-digit blocks of each operand
 };
 
 // nout < na + nb asks for the product mod B^nout only: the strips past limb
@@ -97,8 +88,6 @@ __host__ __device__ inline Geo make_geo(int na, int nb, int nout = -1) {
   Geo g;
   g.na = na; g.nb = nb;
   g.Na = ndigits_w<DW>(na); g.Nb = ndigits_w<DW>(nb);
-  g.NBa = (g.Na + kStrip - 1) / kStrip;
-  g.NBb = (g.Nb + kStrip - 1) / kStrip;
   g.QA = ((g.Na - 1 + kPA) + 15) & ~15;
   g.SA = ((g.QA + kPA + 1) + 15) & ~15;
   g.SB = ((kPadB + g.Nb + kPadBt) + 15) & ~15;
@@ -109,18 +98,15 @@ __host__ __device__ inline Geo make_geo(int na, int nb, int nout = -1) {
   return g;
 }
 
-// block prefix sums (8-bit digits): NBa + 1 and NBb + 1 ints
-__host__ __device__ inline int bs_bytes(const Geo& g) { return (4 * (g.NBa + g.NBb + 2) + 15) & ~15; }
-
 // LDS layout: [Abuf SA][Bbuf SB][per-wave scratch 1 KiB each][strip carries
 // 8W][with lead (8-bit digits): every strip's limbs 0-1, 8W][band order
-// 2*NB][misc 128][block prefix sums (8-bit digits)]
+// 2*NB][misc 128]
 template <int DW, int TS = 16>
 __host__ __device__ inline size_t lds_bytes(int na, int nb, int nwaves, int P, bool lead = false) {
   const Geo g = make_geo<DW, TS>(na, nb);
   const int NB = (g.W + P - 1) / P;
   return (size_t)g.SA + g.SB + (size_t)nwaves * 1024 + (size_t)((DW == 8 && lead) ? 16 : 8) * g.W +
-         (size_t)((2 * NB + 15) & ~15) + 128 + (DW == 8 ? bs_bytes(g) : 0);
+         (size_t)((2 * NB + 15) & ~15) + 128;
 }
 
 // enough for any product of operands of na + nb = n limbs in all (signed digits)
@@ -140,8 +126,6 @@ struct Lds {
                              // them, so the closing scan need not read them back from out
   uint16_t* order;   // NB entries
   uint32_t* misc;    // [0] band counter, [1..16] scan scratch (32 words)
-  int32_t* bsa;      // 8-bit digits: bsa[b] = sum of alpha'_i, i < 256 b (b <= NBa)
-  int32_t* bsb;      // the same for beta' (b <= NBb)
 };
 
 // lead: carve the strips' limbs 0-1 area (8-bit digits; the LDS must have
@@ -161,9 +145,7 @@ __device__ __forceinline__ Lds carve(char* smem, const Geo& g, int P, bool lead)
     p += 8 * g.W;
   }
   s.order = reinterpret_cast<uint16_t*>(p); p += (2 * NB + 15) & ~15;
-  s.misc = reinterpret_cast<uint32_t*>(p); p += 128;
-  s.bsa = reinterpret_cast<int32_t*>(p);
-  s.bsb = s.bsa + g.NBa + 1;
+  s.misc = reinterpret_cast<uint32_t*>(p);
   return s;
 }
 
@@ -185,152 +167,22 @@ __device__ __forceinline__ uint32_t digits4(const uint32_t* __restrict__ a, int 
   return k0 >= 0 ? w : (k0 <= -4 ? 0u : w << (8 * -k0));
 }
 
-// Limb m of an n-limb operand as four offset 8-bit digits (bytes with the
-// top bit flipped: alpha' = alpha - 128 read as signed); 0 outside [0, n).
-__device__ __forceinline__ uint32_t limb8(const uint32_t* __restrict__ a, int n, int m) {
-  // a mask rather than a select, so that the load stays unconditional and
-  // the loads of an unrolled loop issue together
-  const uint32_t mask = (m >= 0 && m < n) ? 0xffffffffu : 0u;
-  return (a[min(max(m, 0), n - 1)] ^ 0x80808080u) & mask;
-}
-
-// Stage the reversed digits of a and the digits of b into LDS (zero padded).
-// Abuf[q] = alpha[QA - q]: dword d holds digits QA-4d-3 .. QA-4d, byte-reversed.
-// (tid, T): this thread's index and the number of threads taking part
-// (the whole work-group by default, one wave for the wave-level multiply)
-template <int DW>
-__device__ __forceinline__ void stage(const Lds& s, const Geo& g, const uint32_t* __restrict__ a,
-                                      const uint32_t* __restrict__ b, int tid = -1, int T = 0) {
-  if (T == 0) { tid = threadIdx.x; T = blockDim.x; }
+// Stage the reversed 7-bit digits of a and the digits of b into LDS (zero
+// padded).  Abuf[q] = alpha[QA - q]: dword d holds digits QA-4d-3 .. QA-4d,
+// byte-reversed.
+__device__ __forceinline__ void stage7(const Lds& s, const Geo& g, const uint32_t* __restrict__ a,
+                                       const uint32_t* __restrict__ b) {
   uint32_t* A32 = reinterpret_cast<uint32_t*>(s.A);
   uint32_t* B32 = reinterpret_cast<uint32_t*>(s.B);
   const int nA = g.SA / 4, nB = g.SB / 4;
-  if constexpr (DW == 8) {
-    // digits QA-4d-3 .. QA-4d: bytes 1..3 of limb l and byte 0 of limb l+1
-    // (QA = 0 mod 16, so QA-4d-4 = 4l)
 #pragma unroll 8
-    for (int d = tid; d < nA; d += T) {
-      const int l = (g.QA - 4 * d - 4) >> 2;
-      const uint32_t v = __builtin_amdgcn_alignbyte(limb8(a, g.na, l + 1), limb8(a, g.na, l), 1);
-      A32[d] = __builtin_bswap32(v);
-    }
-#pragma unroll 8
-    for (int d = tid; d < nB; d += T) B32[d] = limb8(b, g.nb, d - kPadB / 4);
-  } else {
-#pragma unroll 8
-    for (int d = tid; d < nA; d += T) {
-      const int k0 = g.QA - 4 * d - 3;
-      // digits at index >= Na come out 0 because the bits past the top limb are 0
-      A32[d] = __builtin_bswap32(digits4(a, g.na, k0));
-    }
-#pragma unroll 8
-    for (int d = tid; d < nB; d += T) B32[d] = digits4(b, g.nb, 4 * d - kPadB);
+  for (int d = threadIdx.x; d < nA; d += blockDim.x) {
+    const int k0 = g.QA - 4 * d - 3;
+    // digits at index >= Na come out 0 because the bits past the top limb are 0
+    A32[d] = __builtin_bswap32(digits4(a, g.na, k0));
   }
-}
-
-// ---- 8-bit digits: sums of alpha' and beta' ---------------------------------------
-
-// sum of the four signed digits of an offset group (0 for a zero group)
-__device__ __forceinline__ int group_sum(uint32_t x) {
-  return (int)__builtin_amdgcn_sad_u8(x ^ 0x80808080u, 0u, 0u) - 512;
-}
-
-// digits 4m .. 4m+3 of alpha' from the reversed buffer (byte t = digit
-// 4m+3-t); 0 outside [0, na)
-__device__ __forceinline__ uint32_t groupA(const uint8_t* Abuf, const Geo& g, int m) {
-  const int mc = min(max(m, 0), g.na - 1);
-  const uint32_t* p = reinterpret_cast<const uint32_t*>(Abuf + (g.QA - 4 * mc - 4));
-  const uint32_t v = __builtin_amdgcn_alignbyte(p[1], p[0], 1);
-  return v & ((m >= 0 && m < g.na) ? 0xffffffffu : 0u);
-}
-
-// digits 4m .. 4m+3 of beta' (byte t = digit 4m+t); 0 outside [0, nb)
-__device__ __forceinline__ uint32_t groupB(const uint8_t* Bbuf, const Geo& g, int m) {
-  const int mc = min(max(m, 0), g.nb - 1);
-  const uint32_t v = reinterpret_cast<const uint32_t*>(Bbuf + kPadB)[mc];
-  return v & ((m >= 0 && m < g.nb) ? 0xffffffffu : 0u);
-}
-
-// inclusive prefix sum over the 64 lanes with DPP: shifts of 1, 2, 4, 8
-// inside each row of 16 lanes, then the row totals broadcast to the rows
-// above (row_bcast:15 into rows 1 and 3, row_bcast:31 into rows 2 and 3)
-template <int CTRL, int ROWS>
-__device__ __forceinline__ int dpp_add(int x) {
-  return x + __builtin_amdgcn_update_dpp(0, x, CTRL, ROWS, 0xf, false);
-}
-
-__device__ __forceinline__ int wave_incl_scan(int x) {
-  x = dpp_add<0x111, 0xf>(x);  // row_shr:1
-  x = dpp_add<0x112, 0xf>(x);  // row_shr:2
-  x = dpp_add<0x114, 0xf>(x);  // row_shr:4
-  x = dpp_add<0x118, 0xf>(x);  // row_shr:8
-  x = dpp_add<0x142, 0xa>(x);  // row_bcast:15
-  x = dpp_add<0x143, 0xc>(x);  // row_bcast:31
-  return x;
-}
-
-__device__ __forceinline__ int wave_sum(int x) {
-  return __builtin_amdgcn_readlane(wave_incl_scan(x), 63);
-}
-
-// bsa[b] = sum of alpha'_i over i < 256 b for b = 0..NBa (bsa[NBa] is the
-// whole sum); likewise bsb.  Reads the staged buffers; the caller
-// synchronises before and after.
-__device__ __forceinline__ void block_sums(const Lds& s, const Geo& g, int wid = -1, int nw = 0) {
-  if (nw == 0) { wid = wave_id(); nw = num_waves(); }
-  // a row of 16 lanes per block, four consecutive groups per lane (no LDS
-  // bank conflicts); the row total by DPP shifts inside the row
-  const int nblk = g.NBa + g.NBb;
-  const int lane = lane_id(), row = lane >> 4, col = lane & 15;
-  for (int t0 = 4 * wid; t0 < nblk; t0 += 4 * nw) {
-    const int t = t0 + row;
-    const bool isA = t < g.NBa;
-    const int blk = isA ? t : t - g.NBa;
-    const int m = 64 * blk + 4 * col;
-    int v = 0;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) v += group_sum(isA ? groupA(s.A, g, m + e) : groupB(s.B, g, m + e));
-    v = dpp_add<0x111, 0xf>(v);  // row_shr:1
-    v = dpp_add<0x112, 0xf>(v);  // row_shr:2
-    v = dpp_add<0x114, 0xf>(v);  // row_shr:4
-    v = dpp_add<0x118, 0xf>(v);  // row_shr:8
-    if (col == 15 && t < nblk) (isA ? s.bsa : s.bsb)[blk + 1] = v;
-  }
-}
-
-// exclusive prefix over the block totals (wave 0: alpha', wave 1 or 0: beta')
-__device__ __forceinline__ void block_prefix(const Lds& s, const Geo& g, int wid = -1, int nw = 0) {
-  if (nw == 0) { wid = wave_id(); nw = num_waves(); }
-  for (int op = 0; op < 2; ++op) {
-    if (wid != (nw > 1 ? op : 0)) continue;
-    int32_t* bs = op == 0 ? s.bsa : s.bsb;
-    const int nb = op == 0 ? g.NBa : g.NBb;
-    int carry = 0;
-    for (int base = 0; base < nb; base += 64) {
-      const int b = base + lane_id();
-      const int v = b < nb ? bs[b + 1] : 0;
-      const int inc = wave_incl_scan(v) + carry;
-      if (b < nb) bs[b + 1] = inc;
-      carry = __builtin_amdgcn_readlane(inc, 63);
-    }
-    if (lane_id() == 0) bs[0] = 0;
-  }
-}
-
-// prefix sum of alpha' (or beta') over digits [0, 4 gx) = a block prefix
-// (the whole blocks below gx, returned in .base, the same in every lane)
-// plus this lane's group of the partial block when it lies below gx (.part;
-// the wave-wide sum of .part completes it).
-struct Prefix { int base, part; };
-
-__device__ __forceinline__ Prefix prefix_groups(const Lds& s, const Geo& g, bool isA, int gx) {
-  const int n = isA ? g.na : g.nb;
-  const int32_t* bs = isA ? s.bsa : s.bsb;
-  const int gc = min(max(gx, 0), n);
-  const int blk = gc >> 6;
-  const int m = 64 * blk + lane_id();
-  const uint32_t x = m < gc ? (isA ? groupA(s.A, g, m) : groupB(s.B, g, m)) : 0u;
-  return Prefix{bs[blk], group_sum(x)};
+#pragma unroll 8
+  for (int d = threadIdx.x; d < nB; d += blockDim.x) B32[d] = digits4(b, g.nb, 4 * d - kPadB);
 }
 
 // y range of phase rho for the band starting at strip w0 (P strips).
@@ -541,43 +393,112 @@ __device__ __forceinline__ void strip_out7(v4i acc, int w, const Lds& s, const G
   }
 }
 
-// The same for offset 8-bit digits: the strip's 64 limbs and its carry word.
-// S_{256w-1} = PA(256w) - PA(256w-Nb) + PB(256w) - PB(256w-Na), the digit-sum
-// term at the start of strip w: block prefixes, plus a partial block where a
-// boundary is not block-aligned (the tests are wave-uniform).  Later strips of
-// a band carry it forward instead (strip_out8 returns the next one).
-__device__ __forceinline__ int strip_start_sum(const Lds& s, const Geo& g, int w) {
-  const int lane = lane_id();
-  const int g0 = 64 * w;
-  int S0 = 0, part = 0;
-  bool partial = false;
-  auto pre = [&](bool isA, int gx, int sign) __attribute__((always_inline)) {
-    const int n = isA ? g.na : g.nb;
-    const int gc = min(max(gx, 0), n);
-    const int blk = gc >> 6;
-    S0 += sign * (isA ? s.bsa : s.bsb)[blk];
-    if (gc & 63) {
-      partial = true;
-      const int m = 64 * blk + lane;
-      const uint32_t x = m < gc ? (isA ? groupA(s.A, g, m) : groupB(s.B, g, m)) : 0u;
-      part += sign * group_sum(x);
-    }
-  };
-  pre(true, g0, 1);
-  pre(true, g0 - g.nb, -1);
-  pre(false, g0, 1);
-  pre(false, g0 - g.na, -1);
-  if (partial) S0 += wave_sum(part);
-  return S0;
+// ---- signed digits ----------------------------------------------------------------
+// The matrix instructions take signed bytes.  Bytes less 128 would do, but bring
+// a sum of digits into every coefficient, half of the vector instructions of
+// a short product.  Recoding the operand instead brings none: with C = sum_i 128 256^i, the bytes of a + C less 128 each are signed
+// digits whose sum is a itself (the carry out of the top limb is one more
+// digit, 0 or 1).  The addition's carries are ballots of the waves that stage
+// the operand; a wave finds the carry into its part by looking at the limbs
+// below, of which nearly always the first decides.  The coefficients are then
+// signed, and so are the carries between limbs and strips; a bias keeps the
+// strips' carry words positive.
+
+constexpr int kStripBias = 1 << 24;   // above any strip's carry (2^22 at 18432 limbs)
+
+// limb l of a + C less C digit by digit, for l = 64 r + lane (l >= n: the
+// last carry at l = n, then 0); c: the carry into the round, updated
+__device__ __forceinline__ uint32_t signed_digits(uint32_t x, uint32_t& c) {
+  const uint32_t t = x + 0x80808080u;
+  const uint64_t g = __ballot(t < x), p = __ballot(t == ~0u);
+  const uint64_t in = carry_bits(g, p, c);
+  return (t + (__builtin_amdgcn_inverse_ballot_w64(in) ? 1u : 0u)) ^ 0x80808080u;
 }
 
-// Strip w with offset 8-bit digits: its 64 limbs and carry word.  S0 is the
-// digit-sum term at the strip start; returns the one of strip w + 1.
+// the carry into limb 64 r of a + C
+__device__ __forceinline__ uint32_t signed_carry_into(const Limbs& a, int r) {
+  while (r > 0) {
+    const uint32_t x = a(64 * --r + lane_id()), t = x + 0x80808080u;
+    const uint64_t g = __ballot(t < x), p = __ballot(t == ~0u);
+    if (p != ~0ull) return (uint32_t)(g >> (63 - __clzll(~p))) & 1u;
+  }
+  return 0u;
+}
+
+// Stage the signed digits of both operands (layout as stage7) on waves
+// wv = 0 .. nw - 1; with one wave the operands' last carries are returned.
+struct LastDigits { int a, b; };
+__device__ __forceinline__ LastDigits stage_signed(const Lds& s, const Geo& g, const uint32_t* a, const uint32_t* b,
+                                                   int wv, int nw) {
+  constexpr int U = 4;
+  const int lane = lane_id();
+  LastDigits last{0, 0};
+  uint32_t* A32 = reinterpret_cast<uint32_t*>(s.A);
+  uint32_t* B32 = reinterpret_cast<uint32_t*>(s.B);
+  const Limbs a_(a, g.na), b_(b, g.nb);
+  {
+    // dword QA/4 - 1 - l holds digits 4 l + 4 .. 4 l + 1; limb l - 1 is written
+    // with limb l at hand, so limb 0's low digit goes with "limb -1"
+    const int top = g.QA / 4, rounds = g.na / 64 + 1;   // (the round of limb na included)
+    const int tid = 64 * wv + lane, T = 64 * nw;
+    for (int d = tid; d < top - g.na; d += T) A32[d] = 0u;   // (digits 4 na + 1 and up)
+    for (int d = top + 1 + tid; d < g.SA / 4; d += T) A32[d] = 0u;
+    const int per = (rounds + nw - 1) / nw, first = per * wv, end = min(rounds, first + per);
+    uint32_t c = 0u, below = 0u;   // below: limb 64 r - 1
+    if (first > 0 && first < end) {
+      c = signed_carry_into(a_, first - 1);
+      below = (uint32_t)__builtin_amdgcn_readlane((int)signed_digits(a_(64 * (first - 1) + lane), c), 63);
+    }
+    for (int r0 = first; r0 < end; r0 += U) {
+      uint32_t x[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) x[u] = a_(64 * (r0 + u) + lane);
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (r0 + u < end) {
+          const int l = 64 * (r0 + u) + lane;
+          const uint32_t v = signed_digits(x[u], c);
+          // limb l - 1: the lane below (DPP wave_shr:1), below into lane 0
+          const uint32_t w = (uint32_t)__builtin_amdgcn_update_dpp((int)below, (int)v, 0x138, 0xf, 0xf, false);
+          below = (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+          if (l <= g.na) A32[top - l] = __builtin_bswap32(__builtin_amdgcn_alignbyte(v, w, 1));
+          if (nw == 1 && r0 + u == rounds - 1) last.a = __builtin_amdgcn_readlane((int)v, g.na & 63);
+        }
+    }
+  }
+  {
+    const int base = kPadB / 4, n = g.SB / 4 - base, rounds = (n + 63) / 64;
+    if (wv == 0 && lane < base) B32[lane] = 0u;
+    const int per = (rounds + nw - 1) / nw, first = per * wv, end = min(rounds, first + per);
+    uint32_t c = first < end ? signed_carry_into(b_, first) : 0u;
+    for (int r0 = first; r0 < end; r0 += U) {
+      uint32_t x[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) x[u] = b_(64 * (r0 + u) + lane);
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (r0 + u < end) {
+          const int l = 64 * (r0 + u) + lane;
+          const uint32_t v = signed_digits(x[u], c);
+          if (l < n) B32[base + l] = v;
+          if (nw == 1 && r0 + u == g.nb / 64) last.b = __builtin_amdgcn_readlane((int)v, g.nb & 63);
+        }
+    }
+  }
+  return last;
+}
+
+// Strip w from signed digits: its 64 limbs and carry word (+ kStripBias, which
+// strip w + 1 takes off its lowest limb).  With X_j the sum of limb j's four
+// coefficients (|X_j| < 2^52), limb j takes L_j + H_(j-1) - 1 + B, whose carry
+// is 0, 1 or 2; after that carry has moved up, what is left is a sum of
+// 32-bit words with carries 0 or 1.  w_first: the
+// product's first strip; one unit is added at limb bump.
 // TS = 32: acc is a quarter of a 32x32 result tile (registers 4q..4q+3:
 // column lane & 31, rows 4 (lane >> 5) + v of the quarter's eight).
 template <int TS = 16>
-__device__ __forceinline__ int strip_out8(v4i acc, int w, const Lds& s, const Geo& g,
-                                          uint32_t* out, int S0) {
+__device__ __forceinline__ void strip_out_signed(v4i acc, int w, const Lds& s, const Geo& g, uint32_t* out,
+                                                 int w_first, int bump) {
   const int lane = lane_id();
   int32_t* sc = s.wscr;
 #pragma unroll
@@ -585,65 +506,34 @@ __device__ __forceinline__ int strip_out8(v4i acc, int w, const Lds& s, const Ge
     if constexpr (TS == 32) sc[32 * (4 * (lane >> 5) + v) + (lane & 31)] = acc[v];
     else sc[16 * (4 * (lane >> 4) + v) + (lane & 15)] = acc[v];
   }
-  const int g0 = 64 * w;         // the strip's first limb (4-digit group)
-  const int m1 = g0 + lane;      // this lane's limb; its digits k = 4 m1 + t
-  // per-digit changes of S: alpha'_k - alpha'_{k-Nb} + beta'_k - beta'_{k-Na};
-  // a group range entirely outside its operand is skipped (wave-uniform)
-  int d[4] = {0, 0, 0, 0};
-  int sigma = 0;
-  auto add_group = [&](uint32_t x, int sign, bool rev) __attribute__((always_inline)) {
-    sigma += sign * group_sum(x);
-#pragma unroll
-    for (int t = 0; t < 4; ++t) d[t] += sign * __builtin_amdgcn_sbfe((int)x, 8 * (rev ? 3 - t : t), 8);
-  };
-  auto live = [&](int lo, int n) { return lo + 63 >= 0 && lo < n; };  // [lo, lo+64) meets [0, n)
-  if (live(g0, g.na)) add_group(groupA(s.A, g, m1), 1, true);
-  if (live(g0 - g.nb, g.na)) add_group(groupA(s.A, g, m1 - g.nb), -1, true);
-  if (live(g0, g.nb)) add_group(groupB(s.B, g, m1), 1, false);
-  if (live(g0 - g.na, g.nb)) add_group(groupB(s.B, g, m1 - g.na), -1, false);
-  const int incl = wave_incl_scan(sigma);
-  const int excl = incl - sigma;
-  const int S_next = S0 + __builtin_amdgcn_readlane(incl, 63);
-  // pair counts cnt_k = min(k+1, Na) - max(0, k+1-Nb) (clamped at 0) change by
-  // the same step for the four digits of a limb: both bounds are multiples of 4
-  const int k0 = 4 * m1;
-  const int cnt0 = min(k0 + 1, g.Na) - max(0, k0 + 1 - g.Nb);
-  const int step = (k0 + 4 <= g.Na ? 1 : 0) - (m1 >= g.nb ? 1 : 0);
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
   const v4i cp = *reinterpret_cast<const v4i*>(sc + 4 * lane);
-  int S = S0 + excl;
-  uint64_t X = 0;
-#pragma unroll
-  for (int t = 0; t < 4; ++t) {
-    S += d[t];
-    const int cnt = max(0, cnt0 + t * step);
-    // c_k = c'_k + 128 (S_k + 128 cnt_k), at most 2^33
-    const int64_t c = (int64_t)cp[t] + ((int64_t)(S + 128 * cnt) << 7);
-    X += (uint64_t)c << (8 * t);
-  }
   __builtin_amdgcn_wave_barrier();
+  int64_t X = cp[0];
+  X += (int64_t)cp[1] * 256;
+  X += (int64_t)cp[2] * 65536;
+  X += (int64_t)cp[3] * 16777216;
+  if (64 * w + lane == bump) X += 1;
   const uint32_t L = (uint32_t)X;
-  const uint32_t H = (uint32_t)(X >> 32);
-  // H of the lane below, 0 into lane 0 (DPP wave_shr:1)
-  const uint32_t Hprev = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)H, 0x138, 0xf, 0xf, false);
-  const uint64_t sum = (uint64_t)L + Hprev;
-  const uint32_t res = (uint32_t)sum;
-  const bool gb = (sum >> 32) != 0;
-  const bool pb = res == 0xffffffffu;
-  const WaveCarry wc = wave_carry_masks(gb, pb);
-  const uint32_t cin = wave_carry_in(wc, 0);
-  const uint32_t limb = res + cin;
-  const int jg = g0 + lane;
+  const int H = (int)(X >> 32);
+  const int h = __builtin_amdgcn_update_dpp(w > w_first ? 1 - kStripBias : 1, H, 0x138, 0xf, 0xf, false) - 1;
+  const uint32_t t = L + (uint32_t)h;
+  const int up = (t < L ? 1 : 0) + (h >> 31) + 1;
+  const uint32_t from = (uint32_t)__builtin_amdgcn_update_dpp(0, up, 0x138, 0xf, 0xf, false);
+  const uint32_t y = t + from;
+  const uint64_t gm = __ballot(y < t), pm = __ballot(y == ~0u);
+  uint32_t cout = 0u;
+  const uint64_t in = carry_bits(gm, pm, cout);
+  const uint32_t limb = y + (__builtin_amdgcn_inverse_ballot_w64(in) ? 1u : 0u);
+  const int jg = 64 * w + lane;
   const uint64_t tail = ~3ull;   // limbs 2..63
   const uint64_t ones = __ballot(jg >= g.nout || limb == 0xffffffffu);
   if (jg < g.nout) out[jg] = limb;
   if (s.lead && lane < 2) reinterpret_cast<uint32_t*>(s.lead)[2 * w + lane] = jg < g.nout ? limb : 0u;
-  if (lane == 63) {
-    const uint32_t cout = (uint32_t)gb | ((uint32_t)pb & cin);
-    s.carry[w] = (uint64_t)(H + cout) | ((uint64_t)((ones & tail) == tail) << 63);
-  }
-  return S_next;
+  if (lane == 63)
+    s.carry[w] = (uint64_t)(uint32_t)(H - 1 + up + (int)cout + kStripBias) |
+                 ((uint64_t)((ones & tail) == tail) << 63);
 }
 
 // ---- 32x32x32 tiles (v_mfma_i32_32x32x32_i8) ----------------------------------------
@@ -756,7 +646,7 @@ __device__ __forceinline__ void band_phase32(v16i (&acc)[P32], const Lds& s, con
   }
 }
 
-// A band of P strips (P / 4 tiles of 32x32) with offset 8-bit digits.
+// A band of P strips (P / 4 tiles of 32x32) with signed 8-bit digits.
 template <int P>
 __device__ __forceinline__ void run_band32(int band, const Lds& s, const Geo& g, uint32_t* out) {
   constexpr int P32 = P / 4;
@@ -769,158 +659,20 @@ __device__ __forceinline__ void run_band32(int band, const Lds& s, const Geo& g,
   }
 #pragma unroll 1
   for (int rho = 0; rho < 32; ++rho) band_phase32<P32>(acc, s, g, T0, rho);
-  int S = 0;
 #pragma unroll
   for (int i = 0; i < P32; ++i) {
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const int w = 4 * (T0 + i) + q;
       if (w < g.W) {
-        if (i == 0 && q == 0) S = strip_start_sum(s, g, w);
         const v4i part = {acc[i][4 * q], acc[i][4 * q + 1], acc[i][4 * q + 2], acc[i][4 * q + 3]};
-        S = strip_out8<32>(part, w, s, g, out, S);
+        strip_out_signed<32>(part, w, s, g, out, 0, -1);
       }
     }
   }
 }
 
-// ---- signed digits ----------------------------------------------------------------
-// The offset digits above need, for every coefficient, the digit sums that the
-// offset of 128 brings in.  Recoding the operand instead takes that term
-// away: with C = sum_i 128 256^i, the bytes of a + C less 128 each are signed
-// digits whose sum is a itself (the carry out of the top limb is one more
-// digit, 0 or 1).  The addition's carries are ballots of the waves that stage
-// the operand; a wave finds the carry into its part by looking at the limbs
-// below, of which nearly always the first decides.  The coefficients are then
-// signed, and so are the carries between limbs and strips; a bias keeps the
-// strips' carry words positive.
-
-constexpr int kStripBias = 1 << 24;   // above any strip's carry (2^22 at 18432 limbs)
-
-// limb l of a + C less C digit by digit, for l = 64 r + lane (l >= n: the
-// last carry at l = n, then 0); c: the carry into the round, updated
-__device__ __forceinline__ uint32_t signed_digits(uint32_t x, uint32_t& c) {
-  const uint32_t t = x + 0x80808080u;
-  const uint64_t g = __ballot(t < x), p = __ballot(t == ~0u);
-  const uint64_t in = carry_bits(g, p, c);
-  return (t + (__builtin_amdgcn_inverse_ballot_w64(in) ? 1u : 0u)) ^ 0x80808080u;
-}
-
-// the carry into limb 64 r of a + C
-__device__ __forceinline__ uint32_t signed_carry_into(const Limbs& a, int r) {
-  while (r > 0) {
-    const uint32_t x = a(64 * --r + lane_id()), t = x + 0x80808080u;
-    const uint64_t g = __ballot(t < x), p = __ballot(t == ~0u);
-    if (p != ~0ull) return (uint32_t)(g >> (63 - __clzll(~p))) & 1u;
-  }
-  return 0u;
-}
-
-// Stage the signed digits of both operands (layout as stage<8>) on waves
-// wv = 0 .. nw - 1; with one wave the operands' last carries are returned.
-struct LastDigits { int a, b; };
-__device__ __forceinline__ LastDigits stage_signed(const Lds& s, const Geo& g, const uint32_t* a, const uint32_t* b,
-                                                   int wv, int nw) {
-  constexpr int U = 4;
-  const int lane = lane_id();
-  LastDigits last{0, 0};
-  uint32_t* A32 = reinterpret_cast<uint32_t*>(s.A);
-  uint32_t* B32 = reinterpret_cast<uint32_t*>(s.B);
-  const Limbs a_(a, g.na), b_(b, g.nb);
-  {
-    // dword QA/4 - 1 - l holds digits 4 l + 4 .. 4 l + 1; limb l - 1 is written
-    // with limb l at hand, so limb 0's low digit goes with "limb -1"
-    const int top = g.QA / 4, rounds = g.na / 64 + 1;   // (the round of limb na included)
-    const int tid = 64 * wv + lane, T = 64 * nw;
-    for (int d = tid; d < top - g.na; d += T) A32[d] = 0u;   // (digits 4 na + 1 and up)
-    for (int d = top + 1 + tid; d < g.SA / 4; d += T) A32[d] = 0u;
-    const int per = (rounds + nw - 1) / nw, first = per * wv, end = min(rounds, first + per);
-    uint32_t c = 0u, below = 0u;   // below: limb 64 r - 1
-    if (first > 0 && first < end) {
-      c = signed_carry_into(a_, first - 1);
-      below = (uint32_t)__builtin_amdgcn_readlane((int)signed_digits(a_(64 * (first - 1) + lane), c), 63);
-    }
-    for (int r0 = first; r0 < end; r0 += U) {
-      uint32_t x[U];
-#pragma unroll
-      for (int u = 0; u < U; ++u) x[u] = a_(64 * (r0 + u) + lane);
-#pragma unroll
-      for (int u = 0; u < U; ++u)
-        if (r0 + u < end) {
-          const int l = 64 * (r0 + u) + lane;
-          const uint32_t v = signed_digits(x[u], c);
-          // limb l - 1: the lane below (DPP wave_shr:1), below into lane 0
-          const uint32_t w = (uint32_t)__builtin_amdgcn_update_dpp((int)below, (int)v, 0x138, 0xf, 0xf, false);
-          below = (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
-          if (l <= g.na) A32[top - l] = __builtin_bswap32(__builtin_amdgcn_alignbyte(v, w, 1));
-          if (nw == 1 && r0 + u == rounds - 1) last.a = __builtin_amdgcn_readlane((int)v, g.na & 63);
-        }
-    }
-  }
-  {
-    const int base = kPadB / 4, n = g.SB / 4 - base, rounds = (n + 63) / 64;
-    if (wv == 0 && lane < base) B32[lane] = 0u;
-    const int per = (rounds + nw - 1) / nw, first = per * wv, end = min(rounds, first + per);
-    uint32_t c = first < end ? signed_carry_into(b_, first) : 0u;
-    for (int r0 = first; r0 < end; r0 += U) {
-      uint32_t x[U];
-#pragma unroll
-      for (int u = 0; u < U; ++u) x[u] = b_(64 * (r0 + u) + lane);
-#pragma unroll
-      for (int u = 0; u < U; ++u)
-        if (r0 + u < end) {
-          const int l = 64 * (r0 + u) + lane;
-          const uint32_t v = signed_digits(x[u], c);
-          if (l < n) B32[base + l] = v;
-          if (nw == 1 && r0 + u == g.nb / 64) last.b = __builtin_amdgcn_readlane((int)v, g.nb & 63);
-        }
-    }
-  }
-  return last;
-}
-
-// Strip w from signed digits: its 64 limbs and carry word (+ kStripBias, which
-// strip w + 1 takes off its lowest limb).  With X_j the sum of limb j's four
-// coefficients (|X_j| < 2^52), limb j takes L_j + H_(j-1) - 1 + B, whose carry
-// is 0, 1 or 2; after that carry has moved up, what is left is a sum of
-// 32-bit words with carries 0 or 1, as with the offset digits.  w_first: the
-// product's first strip; one unit is added at limb bump.
-__device__ __forceinline__ void strip_out_signed(v4i acc, int w, const Lds& s, const Geo& g, uint32_t* out,
-                                                 int w_first, int bump) {
-  const int lane = lane_id();
-  int32_t* sc = s.wscr;
-#pragma unroll
-  for (int v = 0; v < 4; ++v) sc[16 * (4 * (lane >> 4) + v) + (lane & 15)] = acc[v];
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-  const v4i cp = *reinterpret_cast<const v4i*>(sc + 4 * lane);
-  __builtin_amdgcn_wave_barrier();
-  int64_t X = cp[0];
-  X += (int64_t)cp[1] * 256;
-  X += (int64_t)cp[2] * 65536;
-  X += (int64_t)cp[3] * 16777216;
-  if (64 * w + lane == bump) X += 1;
-  const uint32_t L = (uint32_t)X;
-  const int H = (int)(X >> 32);
-  const int h = __builtin_amdgcn_update_dpp(w > w_first ? 1 - kStripBias : 1, H, 0x138, 0xf, 0xf, false) - 1;
-  const uint32_t t = L + (uint32_t)h;
-  const int up = (t < L ? 1 : 0) + (h >> 31) + 1;
-  const uint32_t from = (uint32_t)__builtin_amdgcn_update_dpp(0, up, 0x138, 0xf, 0xf, false);
-  const uint32_t y = t + from;
-  const uint64_t gm = __ballot(y < t), pm = __ballot(y == ~0u);
-  uint32_t cout = 0u;
-  const uint64_t in = carry_bits(gm, pm, cout);
-  const uint32_t limb = y + (__builtin_amdgcn_inverse_ballot_w64(in) ? 1u : 0u);
-  const int jg = 64 * w + lane;
-  const uint64_t tail = ~3ull;   // limbs 2..63
-  const uint64_t ones = __ballot(jg >= g.nout || limb == 0xffffffffu);
-  if (jg < g.nout) out[jg] = limb;
-  if (lane == 63)
-    s.carry[w] = (uint64_t)(uint32_t)(H - 1 + up + (int)cout + kStripBias) |
-                 ((uint64_t)((ones & tail) == tail) << 63);
-}
-
-template <int DW, int P, bool SIGNED = false>
+template <int DW, int P>
 __device__ __forceinline__ void run_band(int band, const Lds& s, const Geo& g, uint32_t* out, int32_t* coef,
                                          int w_first = 0, int bump = -1) {
   const int w0 = band * P;
@@ -929,15 +681,11 @@ __device__ __forceinline__ void run_band(int band, const Lds& s, const Geo& g, u
   for (int i = 0; i < P; ++i) acc[i] = v4i{0, 0, 0, 0};
 #pragma unroll 1
   for (int rho = 0; rho < 4; ++rho) band_phase<P>(acc, s, g, w0, rho);
-  int S = 0;
 #pragma unroll
   for (int i = 0; i < P; ++i)
     if (w0 + i < g.W) {
-      if constexpr (SIGNED) {
+      if constexpr (DW == 8) {
         strip_out_signed(acc[i], w0 + i, s, g, out, w_first, bump);
-      } else if constexpr (DW == 8) {
-        if (i == 0) S = strip_start_sum(s, g, w0);
-        S = strip_out8(acc[i], w0 + i, s, g, out, S);
       } else {
         strip_out7(acc[i], w0 + i, s, g, out, coef);
       }
@@ -1001,9 +749,8 @@ __device__ __forceinline__ void close_strips(uint32_t* out, const Geo& g, const 
 }
 
 // First band of a product whose limbs below nlo are not needed: the strips
-// of the bands before it lie entirely below limb nlo - 2.  (The part of the
-// product they hold is below 2^34 B^(first strip's limb) <= B^nlo, so leaving
-// it out lowers floor(a b / B^nlo) by at most one.)
+// of the bands before it lie entirely below limb nlo - 2, and the part of the
+// product that they hold is below 2^31 B^(the first strip's limb) < B^(nlo-1).
 template <int DW>
 __host__ __device__ inline int high_band(int nlo, int P) {
   return nlo > 2 ? ((nlo - 2) / strip_limbs<DW>()) / P : 0;
@@ -1013,7 +760,8 @@ __host__ __device__ inline int high_band(int nlo, int P) {
 // digits of DW bits; nout < 0 means the whole na+nb limbs.  nlo > 0 asks
 // only for the limbs from nlo up: the bands below high_band(nlo) are not
 // computed, out[nlo ..) then holds floor(a b / B^nlo) mod B^(nout-nlo) or
-// one less, and the limbs below nlo are left as they were or wrong.  With
+// one more (the part left out can have either sign and is below B^(nlo-1),
+// which is added), and the limbs below nlo are left as they were or wrong.  With
 // coef != nullptr (7-bit digits only, whole product) the raw coefficients
 // c_k (k < Na+Nb-1) are written instead.
 // nparts > 1 (full products, coef == nullptr, nlo == 0): this work-group is
@@ -1026,11 +774,7 @@ __host__ __device__ inline int high_band(int nlo, int P) {
 // lead (8-bit digits, whole instance; smem sized by lds_bytes with lead):
 // every strip's limbs 0-1 are also kept in LDS, where the closing scan reads
 // them instead of reading them back from out.
-// SIGNED (8-bit digits, 16x16 tiles, whole instances, no raw coefficients):
-// signed digits; with nlo the limbs from nlo up then hold floor(a b / B^nlo)
-// or one more (the part left out can have either sign and is below B^(nlo-1);
-// that much is added).
-template <int DW, int P, int TS = 16, bool SIGNED = false>
+template <int DW, int P, int TS = 16>
 __device__ __forceinline__ void wg_mul_mfma(uint32_t* out, int32_t* coef, const uint32_t* __restrict__ a, int na,
                             const uint32_t* __restrict__ b, int nb, char* smem, int nout = -1,
                             int nlo = 0, int part = 0, int nparts = 1, uint64_t* carry_ext = nullptr,
@@ -1046,20 +790,13 @@ __device__ __forceinline__ void wg_mul_mfma(uint32_t* out, int32_t* coef, const 
   const int w_first = band_lo * P;
   const int NB = NBall - band_lo;
 
-  if constexpr (SIGNED) {
-    static_assert(DW == 8 && TS == 16, "signed digits");
+  if constexpr (DW == 8) {
     (void)stage_signed(s, g, a, b, __builtin_amdgcn_readfirstlane(wave_id()),
                        __builtin_amdgcn_readfirstlane(num_waves()));
     g.Na += 1;   // (the operands' last carries)
     g.Nb += 1;
   } else {
-    stage<DW>(s, g, a, b);
-  }
-  if constexpr (DW == 8 && !SIGNED) {
-    __syncthreads();
-    block_sums(s, g);
-    __syncthreads();
-    block_prefix(s, g);
+    stage7(s, g, a, b);
   }
   // band order: most expensive first (rank sort by cost; the costs sit in
   // the wave scratch area, which holds 256 ints per wave >= NB)
@@ -1108,7 +845,7 @@ __device__ __forceinline__ void wg_mul_mfma(uint32_t* out, int32_t* coef, const 
     if ((int)t >= PN) break;
     const int band = band_lo + __builtin_amdgcn_readfirstlane((int)s.order[t]);
     if constexpr (TS == 32) run_band32<P>(band, s, g, out);
-    else run_band<DW, P, SIGNED>(band, s, g, out, coef, w_first, band_lo > 0 ? nlo - 1 : -1);
+    else run_band<DW, P>(band, s, g, out, coef, w_first, band_lo > 0 ? nlo - 1 : -1);
   }
   __syncthreads();
   if (coef == nullptr && nparts == 1) close_strips<DW>(out, g, s.carry, w_first, s.misc + 1, s.lead);
@@ -1123,13 +860,13 @@ __device__ __forceinline__ void wg_mul_mfma(uint32_t* out, int32_t* coef, const 
 // wave: the staging with its recoding to signed digits, the bands, and the
 // strip carry scan on one lane per strip.  Needs W <= 64 strips (na + nb <=
 // 4096 limbs).  The vector ALU bounds it (256 limbs: 74 % busy, the matrix
-// cores 16 %): with offset digits and their sums 2457 vector instructions a
+// cores 16 %): with digits offset by 128 and their sums 2457 vector instructions a
 // product, half of them for the strips' output, and 85.7 us for 16384
 // products; with signed digits 64.9 us.  (128 limbs: 43.4 and 32.7 us; 512
 // limbs: 172 and 143.)
 
 // LDS bytes of one wave's instance (8-bit digits): operands, the wave's
-// scratch, strip carries, misc, block prefix sums
+// scratch, strip carries
 __host__ __device__ inline size_t wave_lds_bytes(int na, int nb) {
   const Geo g = make_geo<8>(na, nb);
   return (((size_t)g.SA + g.SB + 1024 + (size_t)8 * g.W) + 15) & ~(size_t)15;
@@ -1144,7 +881,6 @@ __device__ __forceinline__ Lds carve_wave(char* smem, const Geo& g) {
   s.carry = reinterpret_cast<uint64_t*>(p);
   s.order = nullptr;
   s.misc = nullptr;
-  s.bsa = s.bsb = nullptr;
   return s;
 }
 
@@ -1171,7 +907,7 @@ __device__ __forceinline__ void wave_mul_mfma(uint32_t* out, const uint32_t* __r
   wave_sync();
   const int NB = (g.W + P - 1) / P;
 #pragma unroll 1
-  for (int band = 0; band < NB; ++band) run_band<8, P, true>(band, s, g, out, nullptr);
+  for (int band = 0; band < NB; ++band) run_band<8, P>(band, s, g, out, nullptr);
   wave_sync();
   // strip carries (one lane per strip), as in wg_mul_mfma's closing scan
   constexpr int kStripLimbs = strip_limbs<8>();

@@ -541,3 +541,25 @@ def test_signed_digit_recoding(bi, orc, na, nb):
     if na == nb:
         low = host(bi.mullo(dev(a), dev(b)))
         assert [i for i in range(70) if not np.array_equal(low[i], exp[i][:na])] == []
+
+
+@pytest.mark.parametrize("na,nb,batch,tile", [(1300, 1300, 2, 0), (1300, 900, 300, 0), (5000, 5000, 2, 0), (5000, 4100, 260, 0),
+                                              (16384, 16384, 260, 32), (9000, 300, 2, 0)])
+def test_digit_carry_runs_across_waves(bi, orc, na, nb, batch, tile):
+    """Work-groups of several waves, whole and split products and both tiles:
+    runs of 0x7f7f7f7f limbs, over which the recoding to signed digits carries
+    from one wave's part of the operand into the next."""
+    g = np.random.default_rng(na + nb + batch)
+    a, b = np.full((4, na), 0x7F7F7F7F, np.uint32), np.full((4, nb), 0x7F7F7F7F, np.uint32)
+    for x, n in ((a, na), (b, nb)):
+        x[1, 0] = 0x7F7F7F80
+        x[2, [0, n // 3, n // 2]] = 0x80, 0xFFFFFFFF, 0
+        x[3, g.integers(0, n, 3)] = 0x7F7F7F80
+    reps = -(-batch // 4)
+    bi.set_mfma_tile(tile)
+    try:
+        got = bi.mul(dev(np.tile(a, (reps, 1))[:batch].copy()), dev(np.tile(b, (reps, 1))[:batch].copy()), bi.MUL_MFMA)
+    finally:
+        bi.set_mfma_tile(0)
+    for i in range(min(4, batch)):
+        assert bool((got[i::4] == dev(orc.mul1(a[i], b[i]))).all()), i
