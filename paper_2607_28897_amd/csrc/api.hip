@@ -268,10 +268,10 @@ static bool split_forced() { return t_cfg_P || t_cfg_waves || t_cfg_dw || t_cfg_
 // The transform kernel for a uniform batch of na x nb products (mod B^n with
 // low), or -1 where the MFMA multiply is faster.  The MFMA multiply takes
 // about 2.2e-6 na nb + 1.4e-3 (na + nb) us of a CU per product in a large
-// batch (640 limbs 3.5, 1024 5.2, 2048 14, 4096 48, 8192 175, 16384 635; the
+// batch (640 limbs 3.1, 1024 4.7, 2048 14, 4096 48, 8192 175, 16384 635; the
 // transform takes 3.9, 5.8, 10, 26, 53 and 122 there), and one product alone
-// 9 us plus 0.7 of that up to 50 us, where its bands start to be split over
-// the CUs, and a sixth of the rest (measured 11, 11, 22, 39, 66 and 120 us
+// 8 us plus 0.7 of that up to 50 us, where its bands start to be split over
+// the CUs, and a sixth of the rest (measured 9, 11, 20, 36, 63 and 115 us
 // for those sizes; the transform 11, 11, 15, 24, 60 and 108, with its
 // quarters apart 16 and 22 for the last two).  A last round of products that
 // leaves CUs idle counts half (4096 limbs: batch 256 60 us, 300 85, 512 106).
@@ -297,9 +297,9 @@ static int ntt_choice(int64_t na, int64_t nb, int64_t batch, bool low, size_t ws
     us = quarters;
   }
   const double load = mfma_load(na, nb, low);
-  const double lat = 9.0 + 0.7 * std::min(load, 50.0) + std::max(load - 50.0, 0.0) / 6.0;
+  const double lat = 8.0 + 0.7 * std::min(load, 50.0) + std::max(load - 50.0, 0.0) / 6.0;
   const double x = (double)batch / num_cus();
-  return us <= 0.92 * std::max(lat, 10.0 + load * (x + std::ceil(x)) / 2) ? pick : -1;
+  return us <= 0.92 * std::max(lat, 9.0 + load * (x + std::ceil(x)) / 2) ? pick : -1;
 }
 
 static int mul_ntt(uint32_t* out, const uint32_t* a, int64_t na, const uint32_t* b, int64_t nb, int nout,

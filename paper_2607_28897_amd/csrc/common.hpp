@@ -54,13 +54,6 @@ __device__ __forceinline__ void store4(uint32_t* p, uint32_t x, uint32_t y, uint
   *reinterpret_cast<Limb4*>(p) = Limb4{x, y, z, w};
 }
 
-// Floor / ceiling division of a (possibly negative) int by a positive int.
-__device__ __forceinline__ int floor_div(int a, int b) {
-  int q = a / b;
-  return (a % b != 0 && a < 0) ? q - 1 : q;
-}
-__device__ __forceinline__ int ceil_div(int a, int b) { return -floor_div(-a, b); }
-
 // Carry (or borrow) resolution over the 64 lanes of a wave.
 //
 // Each lane summarises a contiguous run of limbs by (g, p): g = the run emits
@@ -151,6 +144,14 @@ __device__ __forceinline__ uint32_t digit7(const uint32_t* __restrict__ a, int n
   uint32_t v = a[l] >> s;
   if (s > 25 && l + 1 < n) v |= a[l + 1] << (32 - s);
   return v & 127u;
+}
+
+// a pointer that is the same in every lane, in scalar registers
+template <class T>
+__device__ __forceinline__ T* uniform_ptr(T* p) {
+  const uint64_t v = (uint64_t)p;
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+  return (T*)(((uint64_t)hi << 32) | lo);
 }
 
 // n limbs behind a buffer descriptor: reads past the end give 0 and writes

@@ -5,8 +5,9 @@
 // q~ = floor(u w / B^h) is within a few units of floor(u / v), and the signed
 // remainder u - q~ v, reduced into [0, v) by adding or subtracting v, fixes
 // it.  Long quotients are taken so in pieces from the top, from an inverse of
-// one piece's precision (see kHalves).  w is grown by Newton steps in the integral domain, the paper's `step`
-// (Section 5.3, Fig. bdiv-F-code) with both of its branches: with
+// one piece's precision (see kHalves).  w is grown by Newton steps in the
+// integral domain, the paper's `step` (Section 5.3, Fig. bdiv-F-code) with
+// both of its branches: with
 // e = B^c - V w (the signed powDiff, V the divisor's top limbs),
 //     w' = w B^m + floor(w e / B^(c-m))      if e > 0
 //     w' = w B^m - ceil(w |e| / B^(c-m))     if e <= 0
@@ -254,14 +255,6 @@ __device__ __forceinline__ uint32_t wg_arith1(uint32_t* dst, int n, const uint32
   return wg_addsub<16, SUB>(dst, n, X, Y, 0u, sh->scan);
 }
 
-// a pointer that is the same in every lane, in scalar registers
-template <class T>
-__device__ __forceinline__ T* uniform_ptr(T* p) {
-  const uint64_t v = (uint64_t)p;
-  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
-  return (T*)(((uint64_t)hi << 32) | lo);
-}
-
 // ---- one pass of additions, with what the next step asks of its result --------------
 // n limbs, zero from there on
 struct Operand {
@@ -501,6 +494,14 @@ __host__ __device__ inline int64_t mfma_pairs(int na, int nb, int nout, int nlo)
 // code stays small enough for the instruction cache.
 __device__ __noinline__ bool wg_mul(uint32_t* dst, const uint32_t* a, int na, const uint32_t* b,
                                     int nb, char* smem, int nout, int64_t* adjust, int nlo = 0) {
+  // (arguments of an out-of-line function come in vector registers)
+  dst = uniform_ptr(dst);
+  a = uniform_ptr(a);
+  b = uniform_ptr(b);
+  na = __builtin_amdgcn_readfirstlane(na);
+  nb = __builtin_amdgcn_readfirstlane(nb);
+  nout = __builtin_amdgcn_readfirstlane(nout);
+  nlo = __builtin_amdgcn_readfirstlane(nlo);
   if (na <= kSmallMul && nb <= kSmallMul) {
     wg_mul_small(dst, a, na, b, nb, smem, nout);
     return true;
@@ -786,10 +787,11 @@ __device__ inline unsigned __int128 seed_inverse(const uint32_t* v, int k1) {
 // of half its precision (Karp and Markstein's last step): against the last
 // Newton step and one quotient of full length, two thirds of the digit
 // products, and no product longer than (nu + nv) / 2 limbs.  The LDS of a
-// division thus holds 0.4 of what a product of two dividends would take, and
+// division thus holds half of what a product of two quotients would take, and
 // the registers alone decide how many share a CU (4096 divisions of 2048 by
-// 1024 limbs: 7 per CU and 802 us in one piece, 16 per CU and 501 us in two;
-// 512 of 8192 by 4096: 536 and 490).  Shorter quotients gain nothing by it.
+// 1024 limbs: 553 us in one piece, 364 in two; 512 of 8192 by 4096: 449 and
+// 389; one: 293 and 263).  Shorter quotients gain nothing by it (512 by 256
+// limbs the same).
 constexpr int kHalves = 300;
 constexpr int kProdSlack = 8;   // limbs of a division's products beyond its pieces
 

@@ -191,11 +191,12 @@ struct Range { int lo, hi, xlo, xhi; };
 __device__ __forceinline__ Range band_range(const Geo& g, int w0, int P, int rho) {
   Range r;
   // B tile covers beta[Y .. Y+78]; it is nonzero iff that meets [0, Nb)
-  const int yb_lo = ceil_div(-78 - 64 * rho, 256);
-  const int yb_hi = floor_div(g.Nb - 1 - 64 * rho, 256);
+  // (arithmetic shifts: floors; x + 255 for the ceilings)
+  const int yb_lo = (177 - 64 * rho) >> 8;
+  const int yb_hi = (g.Nb - 1 - 64 * rho) >> 8;
   // A tile covers alpha[Z-63 .. Z+240]; nonzero iff that meets [0, Na)
-  r.xlo = ceil_div(64 * rho - 240, 256);
-  r.xhi = floor_div(g.Na + 62 + 64 * rho, 256);
+  r.xlo = (64 * rho + 15) >> 8;
+  r.xhi = (g.Na + 62 + 64 * rho) >> 8;
   r.lo = max(yb_lo, w0 - r.xhi);
   r.hi = min(yb_hi, w0 + P - 1 - r.xlo);
   return r;
@@ -211,13 +212,13 @@ __device__ __forceinline__ int band_cost(const Geo& g, int band, int P) {
 }
 
 // A tile x of phase rho.  Tiles entirely outside alpha read the zero padding
-// at the start of Abuf (every lane the same 16 bytes), so no branch is needed.
+// at the start of Abuf, so no branch is needed.
 __device__ __forceinline__ v4i load_A(const uint8_t* Abuf, const Geo& g, int x, int rho,
                                       const Range& r) {
   const int lane = lane_id();
-  const int Z = 256 * x - 64 * rho;
-  const bool ok = x >= r.xlo && x <= r.xhi;  // wave-uniform
-  const int addr = ok ? g.QA - Z - 16 * (lane & 15) + 16 * (lane >> 4) : 0;
+  // the scalar part of the address (240: every lane inside the low padding)
+  const int at = (unsigned)(x - r.xlo) <= (unsigned)(r.xhi - r.xlo) ? g.QA + 64 * rho - 256 * x : 240;
+  const int addr = at + 16 * ((lane >> 4) - (lane & 15));
   return *reinterpret_cast<const v4i*>(Abuf + addr);
 }
 
@@ -404,13 +405,14 @@ __device__ __forceinline__ void strip_out7(v4i acc, int w, const Lds& s, const G
 // signed, and so are the carries between limbs and strips; a bias keeps the
 // strips' carry words positive.
 
+constexpr int kEqual = 32, kGreater = 34, kLess = 36;   // predicates of the unsigned comparison builtin
 constexpr int kStripBias = 1 << 24;   // above any strip's carry (2^22 at 18432 limbs)
 
 // limb l of a + C less C digit by digit, for l = 64 r + lane (l >= n: the
 // last carry at l = n, then 0); c: the carry into the round, updated
 __device__ __forceinline__ uint32_t signed_digits(uint32_t x, uint32_t& c) {
   const uint32_t t = x + 0x80808080u;
-  const uint64_t g = __ballot(t < x), p = __ballot(t == ~0u);
+  const uint64_t g = __builtin_amdgcn_uicmp(x, 0x7f7f7f7fu, kGreater), p = __builtin_amdgcn_uicmp(x, 0x7f7f7f7fu, kEqual);
   const uint64_t in = carry_bits(g, p, c);
   return (t + (__builtin_amdgcn_inverse_ballot_w64(in) ? 1u : 0u)) ^ 0x80808080u;
 }
@@ -510,10 +512,12 @@ __device__ __forceinline__ void strip_out_signed(v4i acc, int w, const Lds& s, c
   __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
   const v4i cp = *reinterpret_cast<const v4i*>(sc + 4 * lane);
   __builtin_amdgcn_wave_barrier();
+  int k8 = 1 << 8, k16 = 1 << 16, k24 = 1 << 24;   // (opaque: multiply-adds, not 64-bit shifts)
+  asm("" : "+s"(k8), "+s"(k16), "+s"(k24));
   int64_t X = cp[0];
-  X += (int64_t)cp[1] * 256;
-  X += (int64_t)cp[2] * 65536;
-  X += (int64_t)cp[3] * 16777216;
+  X += (int64_t)cp[1] * k8;
+  X += (int64_t)cp[2] * k16;
+  X += (int64_t)cp[3] * k24;
   if (64 * w + lane == bump) X += 1;
   const uint32_t L = (uint32_t)X;
   const int H = (int)(X >> 32);
@@ -522,14 +526,15 @@ __device__ __forceinline__ void strip_out_signed(v4i acc, int w, const Lds& s, c
   const int up = (t < L ? 1 : 0) + (h >> 31) + 1;
   const uint32_t from = (uint32_t)__builtin_amdgcn_update_dpp(0, up, 0x138, 0xf, 0xf, false);
   const uint32_t y = t + from;
-  const uint64_t gm = __ballot(y < t), pm = __ballot(y == ~0u);
+  const uint64_t gm = __builtin_amdgcn_uicmp(y, t, kLess), pm = __builtin_amdgcn_uicmp(y, ~0u, kEqual);
   uint32_t cout = 0u;
   const uint64_t in = carry_bits(gm, pm, cout);
   const uint32_t limb = y + (__builtin_amdgcn_inverse_ballot_w64(in) ? 1u : 0u);
   const int jg = 64 * w + lane;
   const uint64_t tail = ~3ull;   // limbs 2..63
-  const uint64_t ones = __ballot(jg >= g.nout || limb == 0xffffffffu);
-  if (jg < g.nout) out[jg] = limb;
+  const uint64_t ones = __builtin_amdgcn_uicmp(limb, ~0u, kEqual) |
+                        ~__builtin_amdgcn_uicmp((uint32_t)jg, (uint32_t)g.nout, kLess);
+  Limbs(out, g.nout).put(jg, limb);
   if (s.lead && lane < 2) reinterpret_cast<uint32_t*>(s.lead)[2 * w + lane] = jg < g.nout ? limb : 0u;
   if (lane == 63)
     s.carry[w] = (uint64_t)(uint32_t)(H - 1 + up + (int)cout + kStripBias) |
@@ -554,10 +559,10 @@ typedef int v16i __attribute__((ext_vector_type(16)));
 __device__ __forceinline__ Range band_range32(const Geo& g, int T0, int P32, int rho) {
   Range r;
   // B tile covers beta[Y .. Y+62]; A tile covers alpha[Z-31 .. Z+992]
-  const int yb_lo = ceil_div(-62 - 32 * rho, 1024);
-  const int yb_hi = floor_div(g.Nb - 1 - 32 * rho, 1024);
-  r.xlo = ceil_div(32 * rho - 992, 1024);
-  r.xhi = floor_div(g.Na + 30 + 32 * rho, 1024);
+  const int yb_lo = (961 - 32 * rho) >> 10;
+  const int yb_hi = (g.Nb - 1 - 32 * rho) >> 10;
+  r.xlo = (32 * rho + 31) >> 10;
+  r.xhi = (g.Na + 30 + 32 * rho) >> 10;
   r.lo = max(yb_lo, T0 - r.xhi);
   r.hi = min(yb_hi, T0 + P32 - 1 - r.xlo);
   return r;
@@ -781,6 +786,9 @@ __device__ __forceinline__ void wg_mul_mfma(uint32_t* out, int32_t* coef, const 
                             bool lead = false) {
   static_assert(DW == 7 || DW == 8, "digit width");
   static_assert(TS == 16 || (TS == 32 && DW == 8 && P % 4 == 0), "32x32 tiles: 8-bit digits, whole tiles per band");
+  out = uniform_ptr(out);
+  a = uniform_ptr(a);
+  b = uniform_ptr(b);
   Geo g = make_geo<DW, TS>(na, nb, coef ? -1 : nout);
   Lds s = carve<DW>(smem, g, P, lead && coef == nullptr && nparts == 1);
   if (nparts > 1) s.carry = carry_ext;
@@ -859,11 +867,12 @@ __device__ __forceinline__ void wg_mul_mfma(uint32_t* out, int32_t* coef, const 
 // (the paper's ipb instances per block), and every phase runs inside the
 // wave: the staging with its recoding to signed digits, the bands, and the
 // strip carry scan on one lane per strip.  Needs W <= 64 strips (na + nb <=
-// 4096 limbs).  The vector ALU bounds it (256 limbs: 74 % busy, the matrix
-// cores 16 %): with digits offset by 128 and their sums 2457 vector instructions a
-// product, half of them for the strips' output, and 85.7 us for 16384
-// products; with signed digits 64.9 us.  (128 limbs: 43.4 and 32.7 us; 512
-// limbs: 172 and 143.)
+// 4096 limbs).  The vector and the scalar ALU bound it (256 limbs, 16384
+// products: with digits offset by 128 and their sums 2457 vector instructions
+// a product, 85.7 us; with signed digits 1638 and as many scalar ones, of
+// which a CU runs one a cycle, 64.9 us; with ranges by shifts, descriptors in
+// scalar registers and multiply-adds for the columns 53.7 us.  128 limbs 43.4,
+// 32.7 and 27.9 us; 512 limbs 172, 143 and 118.)
 
 // LDS bytes of one wave's instance (8-bit digits): operands, the wave's
 // scratch, strip carries
@@ -898,6 +907,10 @@ template <int P>
 __device__ __forceinline__ void wave_mul_mfma(uint32_t* out, const uint32_t* __restrict__ a, int na,
                                               const uint32_t* __restrict__ b, int nb, char* smem,
                                               int nout = -1) {
+  // (scalar registers: otherwise every access through a descriptor loops over its values)
+  out = uniform_ptr(out);
+  a = uniform_ptr(a);
+  b = uniform_ptr(b);
   Geo g = make_geo<8>(na, nb, nout);
   const Lds s = carve_wave(smem, g);
   const int lane = lane_id();

@@ -76,13 +76,13 @@ static size_t div_lds_bytes(const DivCfg& c) {
 
 // A division is mostly a chain of short passes that wait on memory and on one
 // another, and more of them on a CU hardly slow one another down (2048 / 1024
-// limbs, 64 threads: one 249 us, 16 per CU 501).  So the work-group is the
+// limbs, 64 threads: one 190 us, 16 per CU 374).  So the work-group is the
 // largest useful one that still lets the whole batch run at once, and where
 // none does, the one with the most divisions resident (2048 / 1024 limbs, us
-// with 64 / 128 / 256 / 512 threads: batch 1 249 / 190 / 168 / 171, 1024
-// 308 / 251 / 261 / 444, 2048 386 / 329 / 533 / 876, 4096 529 / 673 / 979 /
-// 1726; 16384 / 8192 limbs: one 2553 / 1416 / 836 / 623; 512 / 256 limbs: one
-// 113 / 100 / 103 / 110).
+// with 64 / 128 / 256 / 512 threads: batch 1 190 / 147 / 128 / 129, 1024
+// 229 / 189 / 192 / 330, 2048 264 / 252 / 373 / 644, 4096 374 / 483 / 721 /
+// 1257; 16384 / 8192 limbs: one 2281 / 1262 / 713 / 514; 512 / 256 limbs: one
+// 79 / 72 / 73 / 77).
 DivCfg div_cfg(int cap_u, int cap_v, int64_t prod, int64_t batch) {
   DivCfg best{cap_u, cap_v, (int)prod, 0, 0};
   for (int t = cap_u <= 724 ? 128 : (cap_u <= 2896 ? 256 : kDivThreads); t >= 64; t /= 2) {
