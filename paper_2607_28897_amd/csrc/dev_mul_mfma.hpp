@@ -402,11 +402,12 @@ __device__ __forceinline__ void strip_out7(v4i acc, int w, const Lds& s, const G
 // digit, 0 or 1).  The addition's carries are ballots of the waves that stage
 // the operand; a wave finds the carry into its part by looking at the limbs
 // below, of which nearly always the first decides.  The coefficients are then
-// signed, and so are the carries between limbs and strips; a bias keeps the
-// strips' carry words positive.
+// signed, and so are the carries between limbs and strips.  (Carry words kept
+// positive by a bias that the next strip takes off again made strips of zero
+// limbs borrow and carry through all their limbs: 43 divisions of all-ones
+// operands took 340 us, of random ones 222.)
 
 constexpr int kEqual = 32, kGreater = 34, kLess = 36;   // predicates of the unsigned comparison builtin
-constexpr int kStripBias = 1 << 24;   // above any strip's carry (2^22 at 18432 limbs)
 
 // limb l of a + C less C digit by digit, for l = 64 r + lane (l >= n: the
 // last carry at l = n, then 0); c: the carry into the round, updated
@@ -490,17 +491,17 @@ __device__ __forceinline__ LastDigits stage_signed(const Lds& s, const Geo& g, c
   return last;
 }
 
-// Strip w from signed digits: its 64 limbs and carry word (+ kStripBias, which
-// strip w + 1 takes off its lowest limb).  With X_j the sum of limb j's four
+// Strip w from signed digits: its 64 limbs and signed carry word (32 bits, and
+// the tail flag in bit 63).  With X_j the sum of limb j's four
 // coefficients (|X_j| < 2^52), limb j takes L_j + H_(j-1) - 1 + B, whose carry
 // is 0, 1 or 2; after that carry has moved up, what is left is a sum of
-// 32-bit words with carries 0 or 1.  w_first: the
-// product's first strip; one unit is added at limb bump.
+// 32-bit words with carries 0 or 1.  One unit is added
+// at limb bump.
 // TS = 32: acc is a quarter of a 32x32 result tile (registers 4q..4q+3:
 // column lane & 31, rows 4 (lane >> 5) + v of the quarter's eight).
 template <int TS = 16>
 __device__ __forceinline__ void strip_out_signed(v4i acc, int w, const Lds& s, const Geo& g, uint32_t* out,
-                                                 int w_first, int bump) {
+                                                 int bump) {
   const int lane = lane_id();
   int32_t* sc = s.wscr;
 #pragma unroll
@@ -521,7 +522,7 @@ __device__ __forceinline__ void strip_out_signed(v4i acc, int w, const Lds& s, c
   if (64 * w + lane == bump) X += 1;
   const uint32_t L = (uint32_t)X;
   const int H = (int)(X >> 32);
-  const int h = __builtin_amdgcn_update_dpp(w > w_first ? 1 - kStripBias : 1, H, 0x138, 0xf, 0xf, false) - 1;
+  const int h = __builtin_amdgcn_update_dpp(1, H, 0x138, 0xf, 0xf, false) - 1;
   const uint32_t t = L + (uint32_t)h;
   const int up = (t < L ? 1 : 0) + (h >> 31) + 1;
   const uint32_t from = (uint32_t)__builtin_amdgcn_update_dpp(0, up, 0x138, 0xf, 0xf, false);
@@ -537,7 +538,7 @@ __device__ __forceinline__ void strip_out_signed(v4i acc, int w, const Lds& s, c
   Limbs(out, g.nout).put(jg, limb);
   if (s.lead && lane < 2) reinterpret_cast<uint32_t*>(s.lead)[2 * w + lane] = jg < g.nout ? limb : 0u;
   if (lane == 63)
-    s.carry[w] = (uint64_t)(uint32_t)(H - 1 + up + (int)cout + kStripBias) |
+    s.carry[w] = (uint64_t)(uint32_t)(H - 1 + up + (int)cout) |
                  ((uint64_t)((ones & tail) == tail) << 63);
 }
 
@@ -671,7 +672,7 @@ __device__ __forceinline__ void run_band32(int band, const Lds& s, const Geo& g,
       const int w = 4 * (T0 + i) + q;
       if (w < g.W) {
         const v4i part = {acc[i][4 * q], acc[i][4 * q + 1], acc[i][4 * q + 2], acc[i][4 * q + 3]};
-        strip_out_signed<32>(part, w, s, g, out, 0, -1);
+        strip_out_signed<32>(part, w, s, g, out, -1);
       }
     }
   }
@@ -679,7 +680,7 @@ __device__ __forceinline__ void run_band32(int band, const Lds& s, const Geo& g,
 
 template <int DW, int P>
 __device__ __forceinline__ void run_band(int band, const Lds& s, const Geo& g, uint32_t* out, int32_t* coef,
-                                         int w_first = 0, int bump = -1) {
+                                         int bump = -1) {
   const int w0 = band * P;
   v4i acc[P];
 #pragma unroll
@@ -690,20 +691,43 @@ __device__ __forceinline__ void run_band(int band, const Lds& s, const Geo& g, u
   for (int i = 0; i < P; ++i)
     if (w0 + i < g.W) {
       if constexpr (DW == 8) {
-        strip_out_signed(acc[i], w0 + i, s, g, out, w_first, bump);
+        strip_out_signed(acc[i], w0 + i, s, g, out, bump);
       } else {
         strip_out7(acc[i], w0 + i, s, g, out, coef);
       }
     }
 }
 
+// One unit off out at limb j, by one wave (modulo B^nout): the borrow runs up
+// through zero limbs, 64 a step.
+__device__ __forceinline__ void wave_borrow(uint32_t* out, int j, int nout) {
+  for (; j < nout; j += 64) {
+    const int k = j + lane_id();
+    const uint32_t v = k < nout ? out[k] : 1u;
+    const uint64_t stop = __ballot(v != 0u);
+    const int last = stop ? __ffsll((long long)stop) - 1 : 63;
+    if (lane_id() <= last && k < nout) out[k] = v - 1u;
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
+    if (stop) break;
+  }
+}
+
+// The signed carry word of a strip (8-bit digits) onto limbs 0-1 of the next:
+// whether they overflow, or go below zero (x is then modulo 2^64, and the
+// borrow is taken from the limbs above once all strips are closed)
+struct StripSum { uint64_t x; bool over, under; };
+__device__ __forceinline__ StripSum strip_sum(uint64_t x0, int32_t d) {
+  const uint64_t x = x0 + (uint64_t)(int64_t)d;
+  return {x, d >= 0 && x < x0, d < 0 && x > x0};
+}
+
 // The closing strip carry scan of an instance (whole work-group): carry[w]
-// holds strip w's carry word (bits 0-62) and tail flag (bit 63), out its
-// limbs, strips from w_first up; scratch: >= 16 words of LDS.  lead
+// holds strip w's carry word (bits 0-62; with 8-bit digits signed, bits 0-31)
+// and tail flag (bit 63), out its limbs, strips from w_first up; scratch: >= 16 words of LDS.  lead
 // (nullable, LDS): lead[w] = strip w's limbs 0-1 as written to out, read
 // there instead of from out.
 template <int DW>
-__device__ __forceinline__ void close_strips(uint32_t* out, const Geo& g, const uint64_t* carry, int w_first,
+__device__ __forceinline__ void close_strips(uint32_t* out, const Geo& g, uint64_t* carry, int w_first,
                                              uint32_t* scratch, const uint64_t* lead = nullptr) {
   constexpr int kStripLimbs = strip_limbs<DW>();
   // out += sum_w C_w B^(L(w+1)), L limbs per strip.  Strip w' receives C_{w'-1} (< 2^35) on its
@@ -714,6 +738,7 @@ __device__ __forceinline__ void close_strips(uint32_t* out, const Geo& g, const 
   // 0..1 plus C_{w'-1} are all ones and so is its tail.
   const uint64_t kC = (1ull << 63) - 1;
   uint32_t cy = 0u;
+  int under = 0;
   for (int base = w_first; base < g.W; base += blockDim.x) {
     const int w = base + threadIdx.x;
     const bool valid = w < g.W;
@@ -728,8 +753,17 @@ __device__ __forceinline__ void close_strips(uint32_t* out, const Geo& g, const 
     }
     const uint64_t d = (valid && w > w_first) ? (carry[w - 1] & kC) : 0ull;
     const bool ones = valid && (carry[w] >> 63);
-    const uint64_t x = x0 + d;
-    const bool xh = x < x0;  // carry out of limb 1
+    uint64_t x = x0 + d;
+    bool xh = x < x0;  // carry out of limb 1
+    if constexpr (DW == 8) {
+      const StripSum sum = strip_sum(x0, (int32_t)(uint32_t)d);
+      x = sum.x;
+      xh = sum.over;
+      if (sum.under) {   // (the strip above reads only the low half of this word)
+        reinterpret_cast<uint32_t*>(carry + w)[1] |= 1u << 30;
+        under = 1;
+      }
+    }
     const bool gen = valid && xh && ones;
     const bool prop = valid && !xh && x == ~0ull && ones;
     uint32_t cout;
@@ -750,6 +784,15 @@ __device__ __forceinline__ void close_strips(uint32_t* out, const Geo& g, const 
         }
       }
     }
+  }
+  if constexpr (DW == 8) {
+    if (__syncthreads_or(under) && wave_id() == 0)
+      for (int base = w_first; base < g.W; base += 64) {
+        const int w = base + lane_id();
+        uint64_t mask = __ballot(w < g.W && ((carry[min(w, g.W - 1)] >> 62) & 1ull));
+        for (; mask; mask &= mask - 1ull)
+          wave_borrow(out, kStripLimbs * (base + __ffsll((long long)mask) - 1) + 2, g.nout);
+      }
   }
 }
 
@@ -853,7 +896,7 @@ __device__ __forceinline__ void wg_mul_mfma(uint32_t* out, int32_t* coef, const 
     if ((int)t >= PN) break;
     const int band = band_lo + __builtin_amdgcn_readfirstlane((int)s.order[t]);
     if constexpr (TS == 32) run_band32<P>(band, s, g, out);
-    else run_band<DW, P>(band, s, g, out, coef, w_first, band_lo > 0 ? nlo - 1 : -1);
+    else run_band<DW, P>(band, s, g, out, coef, band_lo > 0 ? nlo - 1 : -1);
   }
   __syncthreads();
   if (coef == nullptr && nparts == 1) close_strips<DW>(out, g, s.carry, w_first, s.misc + 1, s.lead);
@@ -924,17 +967,17 @@ __device__ __forceinline__ void wave_mul_mfma(uint32_t* out, const uint32_t* __r
   wave_sync();
   // strip carries (one lane per strip), as in wg_mul_mfma's closing scan
   constexpr int kStripLimbs = strip_limbs<8>();
-  const uint64_t kC = (1ull << 63) - 1;
   const int w = lane;
   const bool valid = w < g.W;
   const int j0 = kStripLimbs * (valid ? w : 0);
   const uint32_t l0 = (valid && j0 < g.nout) ? out[j0] : 0u;
   const uint32_t l1 = (valid && j0 + 1 < g.nout) ? out[j0 + 1] : 0u;
-  const uint64_t d = (valid && w > 0) ? (s.carry[w - 1] & kC) : 0ull;
+  const int32_t d = (valid && w > 0) ? (int32_t)(uint32_t)s.carry[w - 1] : 0;
   const bool ones = valid && (s.carry[w] >> 63);
   const uint64_t x0 = ((uint64_t)l1 << 32) | l0;
-  const uint64_t x = x0 + d;
-  const bool xh = x < x0;
+  const StripSum sum = strip_sum(x0, d);
+  const uint64_t x = sum.x;
+  const bool xh = sum.over;
   const bool gen = valid && xh && ones;
   const bool prop = valid && !xh && x == ~0ull && ones;
   const WaveCarry wc = wave_carry_masks(gen, prop);
@@ -954,6 +997,10 @@ __device__ __forceinline__ void wave_mul_mfma(uint32_t* out, const uint32_t* __r
       }
     }
   }
+  uint64_t mask = __ballot(valid && sum.under);
+  if (mask) __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
+  for (; mask; mask &= mask - 1ull)
+    wave_borrow(out, kStripLimbs * (__ffsll((long long)mask) - 1) + 2, g.nout);
 }
 
 }  // namespace mfma

@@ -391,7 +391,7 @@ __global__ __launch_bounds__(64 * kSplitWaves) void k_mul_mfma_part(uint32_t* ou
 
 template <int DW>
 __global__ __launch_bounds__(1024) void k_mul_mfma_close(uint32_t* out, int na, int nb, int nout,
-                                                         const uint64_t* ws, int wstride) {
+                                                         uint64_t* ws, int wstride) {
   __shared__ uint32_t scratch[32];
   const int64_t inst = blockIdx.x;
   const mfma::Geo g = mfma::make_geo<DW>(na, nb, nout);
@@ -847,7 +847,7 @@ __global__ __launch_bounds__(64 * kSplitWaves) void k_mul_mfma_part_ragged(
 template <int DW>
 __global__ __launch_bounds__(1024) void k_mul_mfma_close_ragged(uint32_t* out, const int64_t* out_off,
                                                                 const int64_t* a_off, const int64_t* b_off,
-                                                                const QueueItem* queue, const uint64_t* ws,
+                                                                const QueueItem* queue, uint64_t* ws,
                                                                 int wstride) {
   __shared__ uint32_t scratch[32];
   const int t = blockIdx.x;

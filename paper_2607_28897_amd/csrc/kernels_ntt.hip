@@ -154,7 +154,7 @@ struct NttKernel {
 constexpr NttKernel kNtt[] = {
     {1280, false, 25.f, 3.9f},    {1536, false, 28.f, 4.4f},   {1792, false, 34.f, 5.8f},
     {2048, false, 34.f, 5.8f},    {2048, true, 11.5f, 8.2f},    {2560, false, 27.f, 7.9f},
-    {3072, false, 28.f, 8.9f},    {3072, true, 14.f, 9.5f},    {4096, true, 15.f, 10.4f},
+    {3072, false, 28.f, 8.9f},    {3072, true, 13.f, 9.5f},    {4096, true, 15.f, 10.4f},
     {5120, false, 31.f, 18.f},    {5120, true, 22.f, 22.f},    {6144, false, 33.f, 20.f},
     {6144, true, 23.f, 23.f},     {7168, true, 26.f, 27.f},    {8192, true, 25.f, 26.f},
     {10240, false, 45.f, 36.f},   {12288, false, 48.f, 41.f},  {14336, false, 57.f, 53.f},

@@ -563,3 +563,31 @@ def test_digit_carry_runs_across_waves(bi, orc, na, nb, batch, tile):
         bi.set_mfma_tile(0)
     for i in range(min(4, batch)):
         assert bool((got[i::4] == dev(orc.mul1(a[i], b[i]))).all()), i
+
+
+@pytest.mark.parametrize("na,nb", [(60, 70), (256, 256), (500, 130), (1500, 1500), (3000, 700), (8192, 8192)])
+def test_borrows_through_zero_strips(bi, orc, na, nb):
+    """Products with long runs of zero and all-ones limbs (all-ones operands,
+    powers of the base less or plus a little, sparse operands): strips whose
+    carry word takes more than their lowest limbs hold, full and mod B^n."""
+    g = np.random.default_rng(na + 7 * nb)
+    a, b = np.zeros((9, na), np.uint32), np.zeros((9, nb), np.uint32)
+    for x, n in ((a, na), (b, nb)):
+        x[0] = 0xFFFFFFFF
+        x[1, n - 1] = 1
+        x[2, 0] = x[2, n - 1] = 1
+        x[3, n // 2:] = 0xFFFFFFFF
+        x[4, :n // 2] = 0xFFFFFFFF
+        for i in (5, 6, 7):
+            x[i, g.integers(0, n, 2)] = g.integers(0, 1 << 32, 2)
+        x[8] = 0xFFFFFFFF
+        x[8, g.integers(0, n)] = 0x7FFFFFFF
+    pa, pb = np.repeat(a, 9, 0), np.tile(b, (9, 1))
+    exp = oracle_map(lambda i: orc.mul1(pa[i], pb[i]), range(81))
+    got = host(bi.mul(dev(pa), dev(pb), bi.MUL_MFMA))
+    assert [i for i in range(81) if not np.array_equal(got[i], exp[i])] == []
+    got = host(bi.mul(dev(np.tile(pa, (30, 1))), dev(np.tile(pb, (30, 1))), bi.MUL_MFMA))
+    assert [i for i in range(81) if not (got[i::81] == exp[i]).all()] == []
+    if na == nb:
+        got = host(bi.mullo(dev(pa), dev(pb)))
+        assert [i for i in range(81) if not np.array_equal(got[i], exp[i][:na])] == []
