@@ -27,14 +27,22 @@ __global__ __launch_bounds__(3 * Z::T) void k_mul_ntt3(uint32_t* out, const uint
                       reinterpret_cast<int32_t*>(smem));
 }
 
+// The work-groups of one launch: HIP takes fewer than 2^32 work-items, which
+// 5.6 million products side by side (768 threads each) exceed; larger batches
+// go in several launches.
+static int64_t max_groups(int threads) { return 0xffffffffll / threads; }
+
 template <int T, int Q, int R1, int R2>
 static int launch_ntt3_size(uint32_t* out, const uint32_t* a, int64_t na, const uint32_t* b, int64_t nb,
                             int64_t batch, int nout, hipStream_t s) {
   typedef ntt::Size<T, Q, R1, R2> Z;
   constexpr size_t lds = ntt::ntt3_lds_bytes<Z>();
   BI_HIP(hipFuncSetAttribute((const void*)k_mul_ntt3<Z>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-  hipLaunchKernelGGL(k_mul_ntt3<Z>, dim3((unsigned)batch), dim3(3 * T), lds, s, out, a, (int)na, b, (int)nb, nout);
-  BI_LAUNCH_CHECK();
+  for (int64_t first = 0, step = max_groups(3 * T); first < batch; first += step) {
+    hipLaunchKernelGGL(k_mul_ntt3<Z>, dim3((unsigned)std::min(step, batch - first)), dim3(3 * T), lds, s,
+                       out + first * nout, a + first * na, (int)na, b + first * nb, (int)nb, nout);
+    BI_LAUNCH_CHECK();
+  }
   return BIGINT_OK;
 }
 
@@ -44,9 +52,11 @@ static int launch_ntt_size(uint32_t* out, const uint32_t* a, int64_t na, const u
   typedef ntt::Size<T, Q, R1, R2> Z;
   BI_HIP(hipFuncSetAttribute((const void*)k_mul_ntt<Z>, hipFuncAttributeMaxDynamicSharedMemorySize,
                              (int)Z::LDS_BYTES));
-  hipLaunchKernelGGL(k_mul_ntt<Z>, dim3((unsigned)batch), dim3(T), Z::LDS_BYTES, s, out, a, (int)na, b, (int)nb,
-                     nout);
-  BI_LAUNCH_CHECK();
+  for (int64_t first = 0, step = max_groups(T); first < batch; first += step) {
+    hipLaunchKernelGGL(k_mul_ntt<Z>, dim3((unsigned)std::min(step, batch - first)), dim3(T), Z::LDS_BYTES, s,
+                       out + first * nout, a + first * na, (int)na, b + first * nb, (int)nb, nout);
+    BI_LAUNCH_CHECK();
+  }
   return BIGINT_OK;
 }
 
@@ -341,24 +351,27 @@ int launch_mul_ntt_ragged(uint32_t* out, const int64_t* out_off, const uint32_t*
                           const uint32_t* b, const int64_t* b_off, const QueueItem* queue, const RaggedClass& c,
                           hipStream_t s) {
   if (c.count < 1) return BIGINT_OK;
-  const dim3 gd((unsigned)c.count), bd(ragged_threads(c.ntt));
+  const int threads = ragged_threads(c.ntt);
   BI_HIP(hipFuncSetAttribute(ragged_kernel_ntt(c.ntt), hipFuncAttributeMaxDynamicSharedMemorySize, (int)c.lds));
   queue += c.first;
-  switch (c.ntt) {
-    case kRagged1024:
-      hipLaunchKernelGGL(k_mul_ntt_ragged<kRagged1024>, gd, bd, c.lds, s, out, out_off, a, a_off, b, b_off, queue);
-      break;
-    case kRagged512:
-      hipLaunchKernelGGL(k_mul_ntt_ragged<kRagged512>, gd, bd, c.lds, s, out, out_off, a, a_off, b, b_off, queue);
-      break;
-    case kRaggedSide:
-      hipLaunchKernelGGL(k_mul_ntt_ragged<kRaggedSide>, gd, bd, c.lds, s, out, out_off, a, a_off, b, b_off, queue);
-      break;
-    default:
-      hipLaunchKernelGGL(k_mul_ntt_ragged<kRaggedSideSmall>, gd, bd, c.lds, s, out, out_off, a, a_off, b, b_off,
-                         queue);
+  for (int64_t first = 0, step = max_groups(threads); first < c.count; first += step, queue += step) {
+    const dim3 gd((unsigned)std::min<int64_t>(step, c.count - first)), bd(threads);
+    switch (c.ntt) {
+      case kRagged1024:
+        hipLaunchKernelGGL(k_mul_ntt_ragged<kRagged1024>, gd, bd, c.lds, s, out, out_off, a, a_off, b, b_off, queue);
+        break;
+      case kRagged512:
+        hipLaunchKernelGGL(k_mul_ntt_ragged<kRagged512>, gd, bd, c.lds, s, out, out_off, a, a_off, b, b_off, queue);
+        break;
+      case kRaggedSide:
+        hipLaunchKernelGGL(k_mul_ntt_ragged<kRaggedSide>, gd, bd, c.lds, s, out, out_off, a, a_off, b, b_off, queue);
+        break;
+      default:
+        hipLaunchKernelGGL(k_mul_ntt_ragged<kRaggedSideSmall>, gd, bd, c.lds, s, out, out_off, a, a_off, b, b_off,
+                           queue);
+    }
+    BI_LAUNCH_CHECK();
   }
-  BI_LAUNCH_CHECK();
   return BIGINT_OK;
 }
 
