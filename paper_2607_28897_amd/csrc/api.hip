@@ -869,13 +869,16 @@ static int plan_build_mul(bigint_plan_s* p) {
 static int plan_build_div(bigint_plan_s* p) {
   const int64_t B = p->batch;
   int64_t cu = 1, cv = 1, prod = div_product_limbs(1, 1);
+  double size = 0.0, count = 0.0;
   for (int64_t i = 0; i < B; ++i) {
     if (p->la[i] > BIGINT_DIV_MAX_LIMBS || p->lb[i] > BIGINT_DIV_MAX_LIMBS) return BIGINT_EUNSUPPORTED;
     cu = std::max(cu, p->la[i]);
     cv = std::max(cv, p->lb[i]);
     prod = std::max(prod, div_product_limbs(p->la[i], p->lb[i]));
+    size = std::max(size, div_size(p->la[i], p->lb[i]));
   }
-  p->div = div_cfg((int)cu, (int)cv, prod, B);
+  for (int64_t i = 0; i < B; ++i) count += std::min(1.0, 2.0 * std::sqrt(div_size(p->la[i], p->lb[i]) / size));
+  p->div = div_cfg((int)cu, (int)cv, prod, size, count);
   // largest first: the cost grows like (nu - nv) (nu + 4 nv) limb products
   std::vector<int64_t> idx(B);
   std::iota(idx.begin(), idx.end(), 0);
@@ -1052,13 +1055,19 @@ int bigint_mul_ragged(uint32_t* out, const int64_t* out_off, const uint32_t* a,
 
 // ---- division ------------------------------------------------------------------
 
+// how `count` divisions of one size, under way together, run
+static DivCfg uniform_div_cfg(int64_t nu, int64_t nv, int64_t count) {
+  return div_cfg((int)nu, (int)nv, div_product_limbs(nu, nv), div_size(nu, nv), (double)count);
+}
+
 static int divmod_launch_alloc(uint32_t* q, uint32_t* r, int32_t* status, const uint32_t* u,
                                int64_t nu, const uint32_t* v, int64_t nv, int64_t batch, int h_inv,
                                hipStream_t s, void* given = nullptr, size_t given_bytes = 0) {
   const int cap_u = h_inv >= 0 ? h_inv + 2 : (int)nu;
   const int cap_v = (int)nv;
   // (the inverse's fix-up takes a product of v and all of w)
-  const DivCfg cfg = div_cfg(cap_u, cap_v, h_inv >= 0 ? h_inv + 24 : div_product_limbs(nu, nv), batch);
+  const DivCfg cfg = h_inv >= 0 ? div_cfg(cap_u, cap_v, h_inv + 24, div_size(cap_u, nv), (double)batch)
+                                : uniform_div_cfg(nu, nv, batch);
   const int grid = div_chunk(cfg, batch);
   const size_t bytes = div_ws_bytes(cap_u, cap_v, grid);
   if (given_bytes >= bytes)
@@ -1104,8 +1113,7 @@ int bigint_divmod_workspace_size(int64_t nu, int64_t nv, int64_t batch, size_t* 
   *bytes = 0;
   if (nu > BIGINT_DIV_MAX_LIMBS || nv > BIGINT_DIV_MAX_LIMBS || batch > 0x7fffffff) return BIGINT_EUNSUPPORTED;
   if (batch > 0)
-    *bytes = div_ws_bytes((int)nu, (int)nv,
-                          div_chunk(div_cfg((int)nu, (int)nv, div_product_limbs(nu, nv), batch), batch));
+    *bytes = div_ws_bytes((int)nu, (int)nv, div_chunk(uniform_div_cfg(nu, nv, batch), batch));
   return BIGINT_OK;
 }
 
@@ -1132,9 +1140,9 @@ int bigint_divmod_noalloc(uint32_t* q, uint32_t* r, int32_t* status, const uint3
   if (rc != BIGINT_OK) return rc;
   // work-groups per launch: as bigint_divmod, but no more workspace slots
   // than the scratch array holds (the launches run one after another)
-  const size_t slot = div_ws_bytes((int)nu, (int)nv, 1);
-  const DivCfg cfg = div_cfg((int)nu, (int)nv, div_product_limbs(nu, nv), batch);
-  const int64_t grid = std::min<int64_t>(div_chunk(cfg, batch), (int64_t)(cap / slot));
+  const int64_t slots = (int64_t)(cap / div_ws_bytes((int)nu, (int)nv, 1));
+  const DivCfg cfg = uniform_div_cfg(nu, nv, std::min(batch, slots));
+  const int64_t grid = std::min<int64_t>(div_chunk(cfg, batch), slots);
   if (grid < 1) return BIGINT_EUNSUPPORTED;
   return launch_divmod(q, nullptr, r, nullptr, status, u, nullptr, (int)nu, v, nullptr, (int)nv,
                        nullptr, batch, ws, cfg, (int)grid, -1, nullptr,

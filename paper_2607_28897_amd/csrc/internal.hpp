@@ -138,7 +138,8 @@ size_t div_ws_bytes(int cap_u, int cap_v, int slots);
 // division, divisions resident per CU (0: they do not fit)
 struct DivCfg { int cap_u, cap_v, prod, threads, per_cu; };
 int64_t div_product_limbs(int64_t nu, int64_t nv);
-DivCfg div_cfg(int cap_u, int cap_v, int64_t prod, int64_t batch);
+double div_size(int64_t nu, int64_t nv);
+DivCfg div_cfg(int cap_u, int cap_v, int64_t prod, double size, double count);
 int div_chunk(const DivCfg& c, int64_t batch);
 // The allocation-free division's device workspace on the current device:
 // its address (from hipGetSymbolAddress, once per device) and size.

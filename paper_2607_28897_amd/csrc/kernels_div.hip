@@ -1,6 +1,7 @@
 // kernels_div.hip -- division kernels: one work-group per division, the
 // divisions taken in queue order (largest first).
 #include <algorithm>
+#include <cmath>
 #include <mutex>
 
 #include "internal.hpp"
@@ -74,25 +75,46 @@ static size_t div_lds_bytes(const DivCfg& c) {
                           std::max(div::kSmallMulLds, div::kEarlyLds));
 }
 
+// Dividend limbs of the division by half as many limbs that does as much work.
+double div_size(int64_t nu, int64_t nv) {
+  return std::sqrt((double)std::max<int64_t>(nu - nv + 1, 1) * (double)(nu + 4 * nv) / 1.5);
+}
+
 // A division is mostly a chain of short passes that wait on memory and on one
 // another, and more of them on a CU hardly slow one another down (2048 / 1024
-// limbs, 64 threads: one 190 us, 16 per CU 374).  So the work-group is the
-// largest useful one that still lets the whole batch run at once, and where
-// none does, the one with the most divisions resident (2048 / 1024 limbs, us
-// with 64 / 128 / 256 / 512 threads: batch 1 190 / 147 / 128 / 129, 1024
-// 229 / 189 / 192 / 330, 2048 264 / 252 / 373 / 644, 4096 374 / 483 / 721 /
-// 1257; 16384 / 8192 limbs: one 2281 / 1262 / 713 / 514; 512 / 256 limbs: one
-// 79 / 72 / 73 / 77).
-DivCfg div_cfg(int cap_u, int cap_v, int64_t prod, int64_t batch) {
+// limbs, 64 threads: one 182 us, 16 per CU 360).  So the work-group is the
+// largest useful one that still lets the whole batch run at once (2048 / 1024
+// limbs, us with 64 / 128 / 256 / 512 threads: batch 1 182 / 142 / 127 / 130,
+// 1024 217 / 185 / 195 / 334, 4096 360 / 470 / 708 / 1247), and where none
+// does, the one that finishes the most of them: half the threads take
+// 1 + 0.16 log2(size / 8 threads) of the time, and are worth it only if the
+// LDS lets that many more in (8192 / 4096 limbs, batch 2048: 4 per CU with 256
+// threads 1090 us, 6 with 128 1346; 8192 / 6144, batch 1500: 4 with 256 713, 5
+// with 64 1565; 16384 / 8192, batch 700: 2 with 512 1224, 3 with 128 2491).
+// Up to some 4096 limbs, where caches hold their data, running all at once is
+// worth it too (4096 / 2048, batch 2500: 8 with 128 627, 11 with 64 552).
+// size: the largest division's (div_size).  count: the divisions that can be
+// under way together, those of a ragged batch each by its time against the
+// largest's, near twice the root of their sizes' ratio up to one (two in a row
+// must fit beside the largest): what is done beside the largest needs no place
+// of its own (600 of 64..16384 limbs by half as many: 512 threads, 2 per CU,
+// 499 us; 128 threads, 3 per CU, 1094).
+DivCfg div_cfg(int cap_u, int cap_v, int64_t prod, double size, double count) {
   DivCfg best{cap_u, cap_v, (int)prod, 0, 0};
+  double slower = 1.0;   // than with best.threads
   for (int t = cap_u <= 724 ? 128 : (cap_u <= 2896 ? 256 : kDivThreads); t >= 64; t /= 2) {
     DivCfg c{cap_u, cap_v, (int)prod, t, 0};
     // work-groups that fit one CU: the kernel is built for 4 waves per SIMD (16
     // per CU), so that many waves (over the work-group's) and then the LDS decide
     const size_t per = div_lds_bytes(c) + sizeof(div::Shared) + 64;
     c.per_cu = std::min<int>(16 / (t / 64), (int)(163840 / per));
-    if (c.per_cu > best.per_cu) best = c;
-    if ((int64_t)num_cus() * best.per_cu >= batch) break;
+    if (best.per_cu > 0) slower *= 1.0 + 0.16 * std::max(0.0, std::log2(size / (8 * t)));
+    const bool all = size < 4500 && num_cus() * c.per_cu >= count;
+    if (c.per_cu > best.per_cu * (all ? 1.0 : slower)) {
+      best = c;
+      slower = 1.0;
+    }
+    if (num_cus() * best.per_cu >= count) break;
   }
   return best;
 }
