@@ -167,6 +167,19 @@ int bigint_mul_ws(uint32_t* out, const uint32_t* a, int64_t na, const uint32_t* 
                   int64_t nb, int64_t batch, int algo, void* ws, size_t ws_bytes,
                   void* stream);
 
+/* bigint_mul_transform: how AUTO runs `batch` products of na x nb limbs on this
+ * thread (low != 0: bigint_mullo's products mod B^na, na == nb) when given
+ * ws_bytes of workspace.  *points: the transforms' points, 0 for a product by
+ * another multiply.  *way: BIGINT_TRANSFORM_SERIAL (a work-group per product,
+ * one prime after another), _SIDE (the three primes side by side) or
+ * _QUARTERS (every prime and quarter of a transform a work-group of its own).
+ * BIGINT_EINVAL for null pointers, sizes or batch < 1, or low with na != nb. */
+#define BIGINT_TRANSFORM_SERIAL 0
+#define BIGINT_TRANSFORM_SIDE 1
+#define BIGINT_TRANSFORM_QUARTERS 2
+int bigint_mul_transform(int64_t na, int64_t nb, int64_t batch, int low, size_t ws_bytes,
+                         int* points, int* way);
+
 /* ---- fixed-precision product and the evaluation's fused workloads (Section 6) ---
  * bigint_mullo: out[i] = a[i] * b[i] mod B^n (B = 2^32), the paper's
  *   multiplication, whose quadratic formula keeps only digits k < n

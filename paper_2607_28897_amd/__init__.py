@@ -75,6 +75,7 @@ def lib() -> ctypes.CDLL:
             "bigint_mul": ([_vp, _vp, _i64, _vp, _i64, _i64, _int, _vp], _int),
             "bigint_mul_ws": ([_vp, _vp, _i64, _vp, _i64, _i64, _int, _vp, ctypes.c_size_t, _vp], _int),
             "bigint_mul_workspace_size": ([_i64, _i64, _i64, ctypes.POINTER(ctypes.c_size_t)], _int),
+            "bigint_mul_transform": ([_i64, _i64, _i64, _int, ctypes.c_size_t, _pint, _pint], _int),
             "bigint_mullo_ws": ([_vp, _vp, _vp, _i64, _i64, _vp, ctypes.c_size_t, _vp], _int),
             "bigint_divmod": ([_vp, _vp, _vp, _vp, _i64, _vp, _i64, _i64, _vp], _int),
             "bigint_divmod_ws": ([_vp, _vp, _vp, _vp, _i64, _vp, _i64, _i64, _vp, ctypes.c_size_t, _vp], _int),
@@ -375,6 +376,16 @@ def mfma_config(na: int, nb: int):
     _check(lib().bigint_mfma_config(na, nb, ctypes.byref(p), ctypes.byref(w), ctypes.byref(d)),
            "bigint_mfma_config")
     return p.value, w.value, d.value
+
+
+def mul_transform(na: int, nb: int, batch: int, low: bool = False, workspace: bool = True):
+    """(points, way) of the transform that mul (low: mullo) takes for this batch,
+    None if it takes another multiply.  way: "serial", "side" or "quarters";
+    workspace=False: what the C calls without a workspace take."""
+    m, w = ctypes.c_int(), ctypes.c_int()
+    _check(lib().bigint_mul_transform(na, nb, batch, low, ctypes.c_size_t(-1 if workspace else 0), ctypes.byref(m),
+                                      ctypes.byref(w)), "bigint_mul_transform")
+    return (m.value, ("serial", "side", "quarters")[w.value]) if m.value else None
 
 
 def mfma_split_parts(na: int, nb: int, batch: int) -> int:

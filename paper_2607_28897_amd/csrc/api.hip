@@ -411,6 +411,15 @@ int bigint_mul_workspace_size(int64_t na, int64_t nb, int64_t batch, size_t* byt
   return BIGINT_OK;
 }
 
+int bigint_mul_transform(int64_t na, int64_t nb, int64_t batch, int low, size_t ws_bytes, int* points, int* way) {
+  if (na <= 0 || nb <= 0 || batch < 1 || !points || !way || (low && na != nb)) return BIGINT_EINVAL;
+  const int pick = ntt_choice(na, nb, batch, low != 0, ws_bytes);
+  bool side = false;
+  *points = pick < 0 ? 0 : (pick == kNttQuarters ? ntt_quarters_points(na, nb) : ntt_points(pick, &side));
+  *way = pick == kNttQuarters ? BIGINT_TRANSFORM_QUARTERS : (side ? BIGINT_TRANSFORM_SIDE : BIGINT_TRANSFORM_SERIAL);
+  return BIGINT_OK;
+}
+
 int bigint_mfma_split_parts(int64_t na, int64_t nb, int64_t batch, int* parts) {
   if (na <= 0 || nb <= 0 || batch < 1 || !parts) return BIGINT_EINVAL;
   *parts = 1;

@@ -39,11 +39,13 @@ int launch_mul_mfma(uint32_t* out, int32_t* coef, const uint32_t* a, int64_t na,
 // transform multiply: out = a * b mod B^nout, nout <= na + nb.  ntt_pick: the
 // kernel for this batch and its estimated time, -1 if the operands are too large
 int ntt_pick(int64_t na, int64_t nb, int64_t batch, double* us);
+int ntt_points(int pick, bool* side);
 int launch_mul_ntt(uint32_t* out, const uint32_t* a, int64_t na, const uint32_t* b, int64_t nb, int64_t batch,
                    int nout, int pick, hipStream_t s);
 // few large products: every prime and quarter of a product its own work-group
 double ntt_quarters_us(int64_t na, int64_t nb, int64_t batch);   // estimated time
 size_t ntt_quarters_ws(int64_t na, int64_t nb, int64_t batch);
+int ntt_quarters_points(int64_t na, int64_t nb);
 int launch_mul_ntt_quarters(uint32_t* out, const uint32_t* a, int64_t na, const uint32_t* b, int64_t nb,
                             int64_t batch, int nout, void* ws, hipStream_t s);
 size_t kara_ws_bytes(int n, int64_t batch);

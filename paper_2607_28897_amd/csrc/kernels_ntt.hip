@@ -114,6 +114,8 @@ static int launch_ntt_quarters(uint32_t* out, const uint32_t* a, int64_t na, con
 
 static int quarter_q(int64_t need) { return (int)std::max<int64_t>(3, cdiv(need, 4096)); }
 
+int ntt_quarters_points(int64_t na, int64_t nb) { return 4096 * quarter_q(na + nb); }
+
 size_t ntt_quarters_ws(int64_t na, int64_t nb, int64_t batch) {
   return (size_t)std::min(batch, kQuarterChunk) * quarter_q(na + nb) * (12 * 1024 * 4 + 8 * 16);
 }
@@ -188,6 +190,11 @@ int ntt_pick(int64_t na, int64_t nb, int64_t batch, double* us) {
     }
   }
   return best;
+}
+
+int ntt_points(int pick, bool* side) {
+  *side = kNtt[pick].side;
+  return kNtt[pick].M;
 }
 
 int launch_mul_ntt(uint32_t* out, const uint32_t* a, int64_t na, const uint32_t* b, int64_t nb, int64_t batch,

@@ -1,0 +1,56 @@
+"""CPU-only: the query of the transform that AUTO takes (256 CUs are assumed where
+there is no GPU)."""
+import ctypes
+import os
+
+import pytest
+
+
+@pytest.fixture(scope="module")
+def bi():
+    import paper_2607_28897_amd as m
+    if not os.path.exists(m.LIB_PATH):
+        pytest.skip("library not built")
+    m.lib()
+    yield m
+    m.set_mfma_config(0, 0, 0)
+
+
+def test_arguments(bi):
+    L, m, w = bi.lib(), ctypes.c_int(), ctypes.c_int()
+    r = (ctypes.byref(m), ctypes.byref(w))
+    assert L.bigint_mul_transform(4096, 4096, 64, 1, 0, *r) == 0
+    assert L.bigint_mul_transform(4096, 4000, 64, 1, 0, *r) == bi.EINVAL   # mod B^n: one size
+    assert L.bigint_mul_transform(0, 4096, 64, 0, 0, *r) == bi.EINVAL
+    assert L.bigint_mul_transform(4096, 0, 64, 0, 0, *r) == bi.EINVAL
+    assert L.bigint_mul_transform(4096, 4096, 0, 0, 0, *r) == bi.EINVAL
+    assert L.bigint_mul_transform(4096, 4096, 64, 0, 0, None, r[1]) == bi.EINVAL
+    assert L.bigint_mul_transform(4096, 4096, 64, 0, 0, r[0], None) == bi.EINVAL
+
+
+def test_choice(bi):
+    # the calls of perf/cases.py
+    assert bi.mul_transform(1024, 1024, 64) is None
+    assert bi.mul_transform(256, 256, 16384) is None
+    assert bi.mul_transform(4096, 4096, 1024) == (8192, "side")
+    assert bi.mul_transform(16384, 16384, 256) == (32768, "serial")
+    assert bi.mul_transform(16384, 16384, 3) == (32768, "quarters")
+    assert bi.mul_transform(5003, 2777, 300) == (8192, "side")
+    assert bi.mul_transform(8192, 8192, 512, low=True) == (16384, "serial")
+    # operands it does not take: short ones, more points than it has
+    assert bi.mul_transform(16384, 63, 64) is None
+    assert bi.mul_transform(16385, 16384, 64) is None
+    # a forced configuration keeps the MFMA multiply
+    bi.set_mfma_config(0, 8, 0)
+    assert bi.mul_transform(16384, 16384, 256) is None
+    bi.set_mfma_config(0, 0, 0)
+
+
+@pytest.mark.parametrize("n", [4097, 6144, 8192, 10000, 16384])
+@pytest.mark.parametrize("batch", [1, 40, 300, 5000])
+def test_workspace_is_for_the_quarters(bi, n, batch):
+    size = ctypes.c_size_t()
+    assert bi.lib().bigint_mul_workspace_size(n, n, batch, ctypes.byref(size)) == 0
+    t = bi.mul_transform(n, n, batch)
+    assert (size.value > 0) == (t is not None and t[1] == "quarters")
+    assert (bi.mul_transform(n, n, batch, workspace=False) or (0, ""))[1] != "quarters"
