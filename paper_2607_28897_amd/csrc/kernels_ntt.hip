@@ -152,26 +152,27 @@ int launch_mul_ntt_quarters(uint32_t* out, const uint32_t* a, int64_t na, const 
 // by side, with what one product takes alone on an idle CU and what it takes
 // of a CU in a large batch (us, measured on batches of 1 to 8192).  In
 // between, work-groups that fill a CU by themselves go in whole rounds, and of
-// the small ones several overlap (1024 limbs: batch 2048 66 us, 4096 94, 8192
-// 181; 1536 limbs side by side: 256 14 us, 512 23, 1024 40).  Side by
-// side wins wherever waves are idle, and above 3072 points also in large
-// batches except at 5120 and 6144 points, whose serial kernels fit four
-// work-groups a CU against one (2560-limb products, batch 1024: 73 against
-// 88 us; batch 256: 35 against 25 us).
+// the small ones several overlap (1536 limbs side by side: 256 14 us, 512 23,
+// 1024 40).  Side by side wins wherever waves are idle, and above 3072 points
+// also in large batches except at 5120 and 6144 points, whose serial kernels
+// fit four work-groups a CU against one (2560-limb products, batch 1024: 73
+// against 88 us; batch 256: 35 against 25 us).  Serial kernels below 3072
+// points (2048: 5.8 us of a CU) are not built: where a batch would fill them,
+// the MFMA multiply is faster (1024 limbs 5.2).  7168 points side by side
+// take what 8192 do, and are built for ragged plans only.
 struct NttKernel {
   int M;
   bool side;     // three primes side by side
   float lat, load;
 };
 constexpr NttKernel kNtt[] = {
-    {1280, false, 25.f, 3.9f},    {1536, false, 28.f, 4.4f},   {1792, false, 34.f, 5.8f},
-    {2048, false, 34.f, 5.8f},    {2048, true, 11.5f, 8.2f},    {2560, false, 27.f, 7.9f},
-    {3072, false, 28.f, 8.9f},    {3072, true, 13.f, 9.5f},    {4096, true, 15.f, 10.4f},
-    {5120, false, 31.f, 18.f},    {5120, true, 22.f, 22.f},    {6144, false, 33.f, 20.f},
-    {6144, true, 23.f, 23.f},     {7168, true, 26.f, 27.f},    {8192, true, 25.f, 26.f},
-    {10240, false, 45.f, 36.f},   {12288, false, 48.f, 41.f},  {14336, false, 57.f, 53.f},
-    {16384, false, 60.f, 53.f},   {20480, false, 80.f, 79.f},  {24576, false, 84.f, 86.f},
+    {2048, true, 11.5f, 8.2f},   {3072, false, 28.f, 8.9f},   {3072, true, 13.f, 9.5f},
+    {4096, true, 15.f, 10.4f},   {5120, false, 31.f, 18.f},   {5120, true, 22.f, 22.f},
+    {6144, false, 33.f, 20.f},   {6144, true, 23.f, 23.f},    {8192, true, 25.f, 26.f},
+    {10240, false, 45.f, 36.f},  {12288, false, 48.f, 41.f},  {14336, false, 57.f, 53.f},
+    {16384, false, 60.f, 53.f},  {20480, false, 80.f, 79.f},  {24576, false, 84.f, 86.f},
     {28672, false, 107.f, 123.f}, {32768, false, 108.f, 122.f}};
+constexpr NttKernel kRaggedSide7 = {7168, true, 26.f, 27.f};
 
 int ntt_pick(int64_t na, int64_t nb, int64_t batch, double* us) {
   int best = -1;
@@ -209,16 +210,10 @@ int launch_mul_ntt(uint32_t* out, const uint32_t* a, int64_t na, const uint32_t*
       case 4096: NTT3(4);
       case 5120: NTT3(5);
       case 6144: NTT3(6);
-      case 7168: NTT3(7);
       case 8192: NTT3(8);
     }
   } else {
     switch (kNtt[pick].M) {
-      case 1280: NTT(64, 5, 4, 16);
-      case 1536: NTT(64, 6, 4, 16);
-      case 1792: NTT(64, 7, 4, 16);
-      case 2048: NTT(64, 8, 4, 16);
-      case 2560: NTT(128, 5, 8, 16);
       case 3072: NTT(128, 6, 8, 16);
       case 5120: NTT(256, 5, 16, 16);
       case 6144: NTT(256, 6, 16, 16);
@@ -335,11 +330,10 @@ NttRagged ntt_ragged(int64_t na, int64_t nb) {
   else r.kind = kRaggedSideSmall, r.q = std::max(2, (int)cdiv(need, 1024));
   r.lds = ragged_lds(r.kind, r.q);
   const int M = r.q * (r.kind == kRagged1024 ? 4096 : (r.kind == kRagged512 ? 2048 : 1024));
-  for (const NttKernel& k : kNtt)
-    if (k.M == M && k.side == (r.kind >= kRaggedSide)) {
-      r.load = k.load;
-      r.lat = k.lat;
-    }
+  const NttKernel* k = M == kRaggedSide7.M ? &kRaggedSide7 : kNtt;
+  while (k->M != M || k->side != (r.kind >= kRaggedSide)) ++k;   // (every ragged size is in the table)
+  r.load = k->load;
+  r.lat = k->lat;
   return r;
 }
 
