@@ -586,8 +586,6 @@ __device__ inline void wave_mul_lds(uint32_t* dst, const uint32_t* sa, int na, c
   wave_lds_sync();
   na = min(na, n);
   if (n <= 64) wave_cols<1>(dst, sa, na, sp, n);
-  else if (n <= 128 || kWaveGroups <= 2) wave_cols<2>(dst, sa, na, sp, n);
-  else if (n <= 192) wave_cols<3>(dst, sa, na, sp, n);
   else wave_cols<kWaveGroups>(dst, sa, na, sp, n);
   wave_lds_sync();
 }
