@@ -279,11 +279,27 @@ static bool split_forced() { return t_cfg_P || t_cfg_waves || t_cfg_dw || t_cfg_
 // 10 %, so the transform is taken where it is ahead by more than that.
 // Products mod B^n take half the first and 1.2e-3 of the second term (1024
 // limbs 3.7, 1536 6.2).
+// So few products that each has its bands split over as many work-groups as it
+// can take the same 9 us + 0.002 max + 0.0045 min (na, nb) for any such batch,
+// mod B^n 0.85 of that (one of 9000 limbs 68, 13000 92, 16384 113, 16384 by
+// 5461 65, 14000 mod B^n 87), and the transforms, without the quarters, what
+// their size takes alone (73, 110, 105, 82, 110).
 static double mfma_load(int64_t na, int64_t nb, bool low) {
   return (low ? 1.1e-6 : 2.2e-6) * (double)na * (double)nb + (low ? 1.2e-3 : 1.4e-3) * (double)(na + nb);
 }
 
 constexpr int kNttQuarters = 1000;   // ntt_choice: the quarters apart
+
+// the MFMA multiply's time for so few products, 0 for others
+static double mfma_few_us(int64_t na, int64_t nb, int64_t batch, bool low) {
+  if (4 * batch > num_cus()) return 0.0;
+  const int nout = (int)(low ? na : na + nb), dw = uniform_mfma_cfg((int)na, (int)nb, batch, low).dw;
+  int w = 0;
+  const int parts = mul_mfma_split_parts((int)na, (int)nb, nout, batch, dw, &w);
+  if (parts <= 1 || parts * batch > num_cus() || parts != mul_mfma_split_parts((int)na, (int)nb, nout, 1, dw, &w))
+    return 0.0;
+  return (low ? 0.85 : 1.0) * (9.0 + 0.002 * (double)std::max(na, nb) + 0.0045 * (double)std::min(na, nb));
+}
 
 static int ntt_choice(int64_t na, int64_t nb, int64_t batch, bool low, size_t ws_bytes) {
   if (split_forced() || na > BIGINT_MFMA_MAX_LIMBS || nb > BIGINT_MFMA_MAX_LIMBS || std::min(na, nb) < 64)
@@ -295,6 +311,8 @@ static int ntt_choice(int64_t na, int64_t nb, int64_t batch, bool low, size_t ws
   if (quarters < us && ws_bytes >= ntt_quarters_ws(na, nb, batch)) {
     pick = kNttQuarters;
     us = quarters;
+  } else if (const double few = mfma_few_us(na, nb, batch, low)) {
+    return 0.93 * ntt_alone_us(pick) <= few ? pick : -1;
   }
   const double load = mfma_load(na, nb, low);
   const double lat = 8.0 + 0.7 * std::min(load, 50.0) + std::max(load - 50.0, 0.0) / 6.0;

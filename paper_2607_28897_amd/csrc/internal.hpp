@@ -40,6 +40,7 @@ int launch_mul_mfma(uint32_t* out, int32_t* coef, const uint32_t* a, int64_t na,
 // kernel for this batch and its estimated time, -1 if the operands are too large
 int ntt_pick(int64_t na, int64_t nb, int64_t batch, double* us);
 int ntt_points(int pick, bool* side);
+double ntt_alone_us(int pick);   // one product on an idle device
 int launch_mul_ntt(uint32_t* out, const uint32_t* a, int64_t na, const uint32_t* b, int64_t nb, int64_t batch,
                    int nout, int pick, hipStream_t s);
 // few large products: every prime and quarter of a product its own work-group

@@ -198,6 +198,8 @@ int ntt_points(int pick, bool* side) {
   return kNtt[pick].M;
 }
 
+double ntt_alone_us(int pick) { return kNtt[pick].lat; }
+
 int launch_mul_ntt(uint32_t* out, const uint32_t* a, int64_t na, const uint32_t* b, int64_t nb, int64_t batch,
                    int nout, int pick, hipStream_t s) {
 #define NTT(T, Q, R1, R2) return launch_ntt_size<T, Q, R1, R2>(out, a, na, b, nb, batch, nout, s)

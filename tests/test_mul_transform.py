@@ -54,3 +54,16 @@ def test_workspace_is_for_the_quarters(bi, n, batch):
     t = bi.mul_transform(n, n, batch)
     assert (size.value > 0) == (t is not None and t[1] == "quarters")
     assert (bi.mul_transform(n, n, batch, workspace=False) or (0, ""))[1] != "quarters"
+
+
+# measured without a workspace: us by the MFMA multiply, by transforms
+@pytest.mark.parametrize("na,nb,batch,low,mfma,ntt", [
+    (13000, 13000, 1, False, 92, 110), (12500, 12500, 8, False, 94, 111), (16384, 10922, 4, False, 91, 113),
+    (16384, 5461, 8, False, 68, 82), (8192, 5461, 2, False, 50, 63), (9000, 9000, 1, False, 68, 73),
+    (14000, 14000, 2, True, 89, 111), (14336, 14336, 10, True, 93, 111),
+    (16384, 16384, 1, False, 113, 105), (10240, 10240, 4, False, 77, 72), (8192, 8192, 1, False, 62, 57),
+    (4096, 4096, 8, False, 36, 24), (13000, 13000, 40, False, 306, 111), (14000, 14000, 20, True, 151, 111),
+])
+def test_few_products_without_workspace(bi, na, nb, batch, low, mfma, ntt):
+    """So few that the MFMA multiply spreads each over the device: the faster one."""
+    assert (bi.mul_transform(na, nb, batch, low, False) is None) == (mfma < ntt)
