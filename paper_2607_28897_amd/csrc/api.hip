@@ -275,10 +275,12 @@ static bool split_forced() { return t_cfg_P || t_cfg_waves || t_cfg_dw || t_cfg_
 // for those sizes; the transform 11, 11, 15, 24, 60 and 108, with its
 // quarters apart 16 and 22 for the last two).  A last round of products that
 // leaves CUs idle counts half (4096 limbs: batch 256 60 us, 300 85, 512 106).
-// The estimates are good to some
-// 10 %, so the transform is taken where it is ahead by more than that.
-// Products mod B^n take half the first and 1.2e-3 of the second term (1024
-// limbs 3.7, 1536 6.2).
+// The estimates are good to some 5 %, so the transform is taken where it is
+// ahead by more than that (over 3592 shapes and batches, each timed both ways:
+// the choice 1.8 % slower than the faster one in the mean, 3.0 % before the
+// transforms' last round was counted).  Products mod B^n take half the first
+// and 1.2e-3 of the second term (1024 limbs 3.7, 1536 6.2), which is low by
+// those 5 %.
 // So few products that each has its bands split over as many work-groups as it
 // can take the same 9 us + 0.002 max + 0.0045 min (na, nb) for any such batch,
 // mod B^n 0.85 of that (one of 9000 limbs 68, 13000 92, 16384 113, 16384 by
@@ -317,7 +319,7 @@ static int ntt_choice(int64_t na, int64_t nb, int64_t batch, bool low, size_t ws
   const double load = mfma_load(na, nb, low);
   const double lat = 8.0 + 0.7 * std::min(load, 50.0) + std::max(load - 50.0, 0.0) / 6.0;
   const double x = (double)batch / num_cus();
-  return us <= 0.92 * std::max(lat, 9.0 + load * (x + std::ceil(x)) / 2) ? pick : -1;
+  return us <= (low ? 1.0 : 0.94) * std::max(lat, 9.0 + load * (x + std::ceil(x)) / 2) ? pick : -1;
 }
 
 static int mul_ntt(uint32_t* out, const uint32_t* a, int64_t na, const uint32_t* b, int64_t nb, int nout,

@@ -153,7 +153,8 @@ int launch_mul_ntt_quarters(uint32_t* out, const uint32_t* a, int64_t na, const 
 // of a CU in a large batch (us, measured on batches of 1 to 8192).  In
 // between, work-groups that fill a CU by themselves go in whole rounds, and of
 // the small ones several overlap (1536 limbs side by side: 256 14 us, 512 23,
-// 1024 40).  Side by side wins wherever waves are idle, and above 3072 points
+// 1024 40), though a CU with one more than the others sets the end (1024 limbs
+// side by side: 256 12 us, 257 18, 512 18).  Side by side wins wherever waves are idle, and above 3072 points
 // also in large batches except at 5120 and 6144 points, whose serial kernels
 // fit four work-groups a CU against one (2560-limb products, batch 1024: 73
 // against 88 us; batch 256: 35 against 25 us).  Serial kernels below 3072
@@ -183,7 +184,7 @@ int ntt_pick(int64_t na, int64_t nb, int64_t batch, double* us) {
     const NttKernel& k = kNtt[i];
     const double x = (double)batch / num_cus();
     const double t = k.M > (k.side ? 4096 : 8192) ? 1.1 * k.lat + k.load * std::max(0.0, std::ceil(x) - 1.0)
-                     : k.side                     ? std::max<double>(k.lat, 0.4 * k.lat + k.load * x)
+                     : k.side ? std::max<double>(k.lat, 0.4 * k.lat + k.load * (0.6 * x + 0.4 * std::ceil(x)))
                                                   : std::max(k.load * x, k.lat + 0.7 * k.load * x);
     if (best < 0 || t < *us) {
       best = i;

@@ -19,7 +19,7 @@ pytestmark = pytest.mark.gpu
 FULL = [
     (2048, "side", 1024, 1024, 100), (2048, "side", 1061, 986, 100), (2048, "side", 1280, 767, 150),
     (3072, "serial", 1536, 1536, 2000), (3072, "serial", 1920, 1151, 3000),
-    (3072, "side", 1536, 1536, 64), (3072, "side", 1573, 1498, 64), (3072, "side", 1025, 1024, 257),
+    (3072, "side", 1536, 1536, 64), (3072, "side", 1573, 1498, 64), (3072, "side", 1250, 1201, 200),
     (4096, "side", 2048, 2048, 64), (4096, "side", 2560, 1535, 64), (4096, "side", 1537, 1536, 150),
     (5120, "serial", 2560, 2560, 1000), (5120, "serial", 3200, 1919, 1000),
     (5120, "side", 2560, 2560, 200), (5120, "side", 2597, 2522, 200),
@@ -44,9 +44,9 @@ FULL = [
 
 # products mod B^n: points, way, n, batch
 LOW = [
-    (2048, "side", 1024, 257), (2048, "side", 1023, 257),
-    (3072, "side", 1536, 200), (3072, "side", 1535, 200), (3072, "side", 1281, 257),
-    (4096, "side", 2048, 150), (4096, "side", 2047, 150), (4096, "side", 1537, 257),
+    (2048, "side", 1024, 100), (2048, "side", 1023, 100),
+    (3072, "side", 1536, 200), (3072, "side", 1535, 200), (3072, "side", 1351, 200),
+    (4096, "side", 2048, 150), (4096, "side", 2047, 150), (4096, "side", 1793, 150),
     (8192, "side", 4096, 150), (8192, "side", 4095, 150), (8192, "side", 3585, 220),
     (10240, "serial", 5120, 1000), (10240, "serial", 5119, 1000),
     (12288, "serial", 6144, 200), (12288, "serial", 6143, 200), (12288, "serial", 5633, 512),

@@ -67,3 +67,16 @@ def test_workspace_is_for_the_quarters(bi, n, batch):
 def test_few_products_without_workspace(bi, na, nb, batch, low, mfma, ntt):
     """So few that the MFMA multiply spreads each over the device: the faster one."""
     assert (bi.mul_transform(na, nb, batch, low, False) is None) == (mfma < ntt)
+
+
+# us by the MFMA multiply, by transforms
+@pytest.mark.parametrize("na,nb,batch,low,mfma,ntt", [
+    (1700, 212, 257, False, 11.3, 17.8), (1300, 433, 257, False, 12.7, 17.7), (3000, 375, 300, False, 18.3, 23.8),
+    (1536, 1024, 513, False, 24.5, 29.4), (2300, 766, 800, False, 33.1, 40.7), (1024, 1024, 257, True, 12.4, 17.3),
+    (1024, 1024, 1024, False, 27.7, 33.2), (2048, 2048, 300, False, 34.2, 23.2), (1900, 1266, 400, False, 26.6, 23.2),
+    (1536, 1536, 280, False, 25.2, 21.4), (2048, 2048, 280, True, 26.0, 22.5), (1900, 1900, 230, True, 16.8, 14.6),
+    (1536, 1536, 256, True, 16.5, 13.6),
+])
+def test_rounds_of_small_transforms(bi, na, nb, batch, low, mfma, ntt):
+    """Just above one or two products per CU the transforms take a round more."""
+    assert (bi.mul_transform(na, nb, batch, low) is None) == (mfma < ntt)
