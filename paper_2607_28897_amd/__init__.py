@@ -209,26 +209,27 @@ def _addsub(fn, a, b, out, what):
     return _back(out, wd), carry
 
 
-def _workspace(query, what, device, *sizes):
-    """The workspace that C function `query` asks for, from torch's allocator
-    (ordered on the current stream like every tensor), else None, and its
-    size.  With no memory left for it the call runs without."""
+def _workspace(query, what, *sizes):
+    """The workspace that C function `query` asks for, else None, and its size.
+    From torch's allocator on the current device, whose current stream the
+    call runs on: it may go back to the allocator as soon as the call has been
+    enqueued.  With no memory left for it the call runs without."""
     n = ctypes.c_size_t()
     _check(query(*sizes, ctypes.byref(n)), what)
     if n.value == 0:
         return None, 0
     torch = _torch()
     try:
-        return torch.empty(n.value, dtype=torch.uint8, device=device), n.value
+        return torch.empty(n.value, dtype=torch.uint8, device="cuda"), n.value
     except torch.cuda.OutOfMemoryError:
         return None, 0
 
 
-def _mul_ws(na, nb, batch, device):
+def _mul_ws(na, nb, batch):
     """The workspace of products that take one (none do up to 8192 limbs)."""
     if na + nb <= 8192:
         return None, 0
-    return _workspace(lib().bigint_mul_workspace_size, "bigint_mul_workspace_size", device, na, nb, batch)
+    return _workspace(lib().bigint_mul_workspace_size, "bigint_mul_workspace_size", na, nb, batch)
 
 
 def mul(a, b, algo: int = MUL_AUTO):
@@ -241,7 +242,7 @@ def mul(a, b, algo: int = MUL_AUTO):
     if ba != bb:
         raise ValueError("batch mismatch")
     out = torch.empty((ba, na + nb), dtype=a.dtype, device=a.device)
-    ws, size = _mul_ws(na, nb, ba, a.device) if algo == MUL_AUTO else (None, 0)
+    ws, size = _mul_ws(na, nb, ba) if algo == MUL_AUTO else (None, 0)
     if ws is not None:
         _check(lib().bigint_mul_ws(_p(out), _p(a), na, _p(b), nb, ba, algo, _p(ws), size, _stream()), "bigint_mul")
     else:
@@ -263,7 +264,7 @@ def divmod(u, v):
     st = torch.empty(bu, dtype=torch.int32, device=u.device)
     ws, size = None, 0
     if 0 < nu <= DIV_MAX_LIMBS and 0 < nv <= DIV_MAX_LIMBS and bu > 0:
-        ws, size = _workspace(lib().bigint_divmod_workspace_size, "bigint_divmod", u.device, nu, nv, bu)
+        ws, size = _workspace(lib().bigint_divmod_workspace_size, "bigint_divmod", nu, nv, bu)
     if ws is not None:
         _check(lib().bigint_divmod_ws(_p(q), _p(r), _p(st), _p(u), nu, _p(v), nv, bu, _p(ws), size, _stream()),
                "bigint_divmod")
@@ -320,7 +321,7 @@ def mullo(a, b):
     if ba != bb or n != nb:
         raise ValueError("shape mismatch")
     out = torch.empty((ba, n), dtype=a.dtype, device=a.device)
-    ws, size = _mul_ws(n, n, ba, a.device)
+    ws, size = _mul_ws(n, n, ba)
     if ws is not None:
         _check(lib().bigint_mullo_ws(_p(out), _p(a), _p(b), n, ba, _p(ws), size, _stream()), "bigint_mullo")
     else:
