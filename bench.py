@@ -324,7 +324,7 @@ def small_batch_leg(torch, bi, a, b, ref, n, args):
     """The first 1 and 16 pairs of the same 2^19-bit batch alone: each
     product's bands split over several work-groups (k_mul_mfma_part, then
     k_mul_mfma_close); both equal the batch's products.  (One work-group per
-    product takes about 0.52 ms for either, the headline kernel's time.)"""
+    product takes about 0.5 ms for either, the headline kernel's time.)"""
     out = []
     steps = max(10, args.steps // 2)
     for k in (x for x in (1, 16) if x <= a.shape[0]):

@@ -122,10 +122,9 @@ int bigint_sub(uint32_t* out, uint32_t* borrow_out, const uint32_t* a,
  *     int8 MFMA tiles with int32 accumulation, recombined in 64-bit columns
  *     and resolved by the same carry scan.  The digit width is a tuned
  *     parameter: 7-bit digits (exact: every coefficient is at most
- *     min(Na,Nb)*127^2 < 2^31) or 8-bit digits fed as alpha - 128 (signed
- *     int8; every MFMA sum is at most min(Na,Nb)*2^14 < 2^31) with the
- *     offset terms 128 (window sums of the digits) + 2^14 (pair counts)
- *     added per coefficient in 64-bit arithmetic.  Both give the same bytes.
+ *     min(Na,Nb)*127^2 < 2^31) or signed 8-bit digits (the bytes of a + C less
+ *     128 each, C = sum 128 256^i; every coefficient is at most
+ *     min(Na,Nb)*2^14 < 2^31 in magnitude).  Both give the same bytes.
  *   BIGINT_MUL_KARATSUBA (na == nb >= 2): one level of Karatsuba's method
  *     over the MFMA-split multiply, with h = ceil(n/2) and s = sign(a0 - a1)
  *     sign(b1 - b0): a b = p2 B^(2h) + (p0 + p2 + s pm) B^h + p0 with
@@ -144,11 +143,14 @@ int bigint_sub(uint32_t* out, uint32_t* borrow_out, const uint32_t* a,
  * `stream` (stream-ordered); a second launch resolves each instance's strip
  * carries.  Same bytes as one work-group per instance
  * (bigint_mfma_split_parts reports the split).
- * AUTO multiplies large operands (from about 640 limbs each in large batches,
- * 2560 limbs in small ones, na + nb <= 32768) by number-theoretic transforms
- * of the limbs modulo three 27-bit primes, whose residues determine every
- * C_k < 2^78 exactly (integers only, no workspace, same bytes), unless a
- * configuration is forced on the thread.
+ * AUTO multiplies large operands (na + nb <= 32768; equal ones from about 1400
+ * to 1700 limbs, in batches of 100 to 256 from 840 to 1250; short of the next
+ * transform size up to 2900) by number-theoretic transforms of the limbs
+ * modulo three 27-bit primes, whose residues determine every C_k < 2^78
+ * exactly (integers only, same bytes), unless a configuration is forced on the
+ * thread (bigint_mul_transform reports the choice).  It is made by estimated
+ * times, those of the MFMA multiply with the built-in tuning table: a loaded
+ * table decides how the MFMA multiply runs where AUTO takes it.
  * a: batch*na limbs, b: batch*nb limbs, out: batch*(na+nb) limbs.
  * na, nb >= 1.  MFMA needs na, nb <= BIGINT_MFMA_MAX_LIMBS (else
  * BIGINT_EUNSUPPORTED); PLAIN needs na+nb <= 32768; AUTO picks the transform
@@ -355,9 +357,9 @@ int bigint_divmod_ragged(uint32_t* q, const int64_t* q_off, uint32_t* r,
  * bigint_autotune_load replaces it); a file that does not parse leaves the
  * built-in table (bigint_autotune_load on the same path reports why).
  * BIGINT_DEBUG=1 prints one line on stderr per configuration the library
- * picks: each MFMA-split, plain or Karatsuba multiply call (digit width,
- * tile, strips per band, waves, work-groups per product), each segment of a
- * ragged multiply plan and each division plan. */
+ * picks: each multiply call (by transforms; or MFMA-split, plain or Karatsuba
+ * with digit width, tile, strips per band, waves, work-groups per product),
+ * each segment of a ragged multiply plan and each division plan. */
 int bigint_autotune(const char* cache_path, int flags);
 int bigint_autotune_load(const char* cache_path);
 
@@ -438,14 +440,16 @@ int bigint_set_mfma_config(int strips_per_band, int waves, int digit_bits);
  * zero padding is wider: 18,432-limb operands on 8 waves do not); every other
  * configuration (and the ragged, Karatsuba, Poly and division kernels) runs
  * 16x16 tiles.  Both tiles give the same bytes.  Other values return
- * BIGINT_EINVAL.  bigint_mfma_tile returns the tile bigint_mul would use for
- * an na x nb product on this thread (16 or 32), or a negative status. */
+ * BIGINT_EINVAL.  bigint_mfma_tile returns the tile bigint_mul's MFMA multiply
+ * would use for an na x nb product on this thread (16 or 32), or a negative
+ * status. */
 int bigint_set_mfma_tile(int tile);
 int bigint_mfma_tile(int64_t na, int64_t nb);
 
-/* The tile configuration bigint_mul would use on this thread for an na x nb
- * product (tuned table, then this thread's overrides), written to the three
- * host ints.  Where the table gives one wave per instance, bigint_mul runs
+/* The tile configuration bigint_mul's MFMA multiply would use on this thread for
+ * an na x nb product (tuned table, then this thread's overrides), written to
+ * the three host ints (AUTO may take the transforms instead:
+ * bigint_mul_transform).  Where the table gives one wave per instance, bigint_mul runs
  * it only for batches of at least na*nb/64 instances, bigint_mullo for at
  * least n*n/256, bigint_poly for at least n*n/16, and 4 waves per instance
  * below that (one

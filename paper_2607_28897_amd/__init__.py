@@ -363,7 +363,7 @@ def set_mfma_tile(tile: int = 0):
 
 
 def mfma_tile(na: int, nb: int) -> int:
-    """The MFMA tile (16 or 32) bigint_mul uses for an na x nb product."""
+    """The MFMA tile (16 or 32) of mul's MFMA multiply for an na x nb product."""
     t = lib().bigint_mfma_tile(na, nb)
     if t < 0:
         raise BigIntError(t, "bigint_mfma_tile")
@@ -371,7 +371,7 @@ def mfma_tile(na: int, nb: int) -> int:
 
 
 def mfma_config(na: int, nb: int):
-    """(strips_per_band, waves, digit_bits) that bigint_mul uses for na x nb."""
+    """(strips_per_band, waves, digit_bits) of mul's MFMA multiply for na x nb."""
     import ctypes
     p, w, d = ctypes.c_int(), ctypes.c_int(), ctypes.c_int()
     _check(lib().bigint_mfma_config(na, nb, ctypes.byref(p), ctypes.byref(w), ctypes.byref(d)),

@@ -46,8 +46,8 @@ static std::mutex g_tune_mu;
 // (waves 1: one wave per instance, four instances per work-group).  8
 // strips on 8 waves run up to 8,676 limbs, the largest size whose LDS fits
 // two such work-groups on a CU; above it, with one work-group per CU either
-// way, 16 strips win (1024 products of 9,000 / 10,000 limbs: 0.599 / 0.615
-// of the int8 peak against 0.583 / 0.600).
+// way, 16 strips win (1024 products of 9,000 / 10,000 limbs: 0.617 / 0.629
+// of the int8 peak against 0.605 / 0.611).
 static const std::vector<TuneEntry> kBuiltinTune = {
     {512, 4, 1, 8}, {1448, 8, 1, 8}, {2896, 8, 4, 8}, {5792, 8, 8, 8}, {8676, 8, 8, 8},
     {BIGINT_MFMA_MAX_LIMBS, 16, 8, 8}};
@@ -117,13 +117,15 @@ MfmaCfg current_mfma_cfg(int na, int nb) {
 // One wave per instance pays only once the batch keeps every CU busy with
 // several instances, since the latency of one instance on one wave grows
 // with na*nb.  Measured crossovers on MI355X (128..1024 limbs), in instances:
-// about na*nb/64 for full products (256 at 128 limbs, 1024 at 256, 4096 at
-// 512, 16384 at 1024), n*n/256 for products mod B^n (half the strips), and
-// n*n/16 for Poly (its four products and three additions per wave).  Smaller
-// uniform batches run 4 waves per instance: full products with the table's
-// strips per band, products mod B^n and Poly with 4 strips per band, so that
-// their fewer bands still reach all four waves.  At 64 pairs of 1024 limbs
-// that is 2.5x faster.  Settings of bigint_set_mfma_config are kept.
+// about na*nb/64 for full products (us with 1 / 4 waves: 128 limbs, 256
+// instances 8.1 / 8.2; 256, 1024 11.4 / 12.5; 512, 4096 39.4 / 40.9; at 1024
+// limbs they are level, 16384 311 / 306), n*n/256 for products mod B^n (half
+// the strips: 256 limbs, 256 instances 8.0 / 8.5; 512, 1024 13.7 / 14.5; 1024,
+// 4096 52.8 / 54.1), and n*n/16 for Poly (its four products and three additions
+// per wave).  Smaller uniform batches run 4 waves per instance: full products
+// with the table's strips per band, products mod B^n and Poly with 4 strips
+// per band, so that their fewer bands still reach all four waves (64 pairs of
+// 1024 limbs 42 / 14).  Settings of bigint_set_mfma_config are kept.
 constexpr int kWaveFull = 64, kWaveLow = 256, kWavePoly = 16;
 
 static bool wave_batch(int64_t na, int64_t nb, int64_t batch, int per) {
@@ -141,9 +143,9 @@ static MfmaCfg uniform_mfma_cfg(int na, int nb, int64_t batch, bool low) {
   // Fewer instances than CUs: every work-group has a CU to itself, and 8
   // waves (two per SIMD) hide more MFMA and LDS latency than 4.  Measured
   // (call times through the Python binding): full products of 64 x 1024 limbs
-  // 26.3 -> 22.6 us (4 strips per band), 64 x 2048 limbs 39.7 -> 34.4 us (the
-  // table's 8 strips); products mod B^n of 64 x 2048 limbs 31.2 -> 27.0 us
-  // (4 strips per band; 8 strips gain nothing there).
+  // 14.4 -> 12.5 us (4 strips per band), 64 x 2048 limbs 25.5 -> 23.7 us (the
+  // table's 8 strips); products mod B^n of 64 x 2048 limbs 19.2 -> 17.1 us
+  // (4 strips per band; 8 strips 20.7).
   if (c.waves == 4 && t_cfg_waves == 0 && batch < num_cus()) {
     MfmaCfg w = c;
     w.waves = 8;

@@ -274,8 +274,9 @@ constexpr int kLinRounds = 16;
 // the carries of a round are one 64-bit scalar addition of its ballots, and
 // the result's length and its order against z (nullable, nz limbs) fall out of
 // two more ballots, so that no further pass and no second barrier is needed
-// for them.  (Runs of 16 limbs a thread, with a length and a comparison pass
-// of their own, took TIMES.)
+// for them.  (With runs of 16 limbs a thread, and a length and a comparison
+// pass of their own, one division of 2048 by 1024 limbs took 168 us against
+// 150 and 4096 of them 502 against 446.)
 __device__ __noinline__ LinResult wg_lin(uint32_t* dst, int n, Operand x, int at, Operand y, int sub, uint32_t c,
                                          uint32_t low, const uint32_t* z, int nz, Shared* sh) {
   n = __builtin_amdgcn_readfirstlane(n);

@@ -44,7 +44,7 @@
 // each, C = sum_i 128 256^i, in [-128, 127], and the carry out of that sum
 // as one more digit: their sum is a (|alpha beta| <= 2^14, so int32 is exact
 // up to 131,071 digits).  A strip's 256 coefficients are 64 limbs; limb j
-// takes X_j = sum_t c_{4j+t} 2^(8t), |X_j| < 2^56, and the spill of limb 63
+// takes X_j = sum_t c_{4j+t} 2^(8t), |X_j| < 2^55, and the spill of limb 63
 // is the strip's carry word.
 #pragma once
 
@@ -491,9 +491,14 @@ __device__ __forceinline__ LastDigits stage_signed(const Lds& s, const Geo& g, c
   return last;
 }
 
+// the largest |X_j|: four coefficients of at most kMaxDigits products each
+constexpr int64_t kMaxDigits = 4 * BIGINT_MFMA_MAX_LIMBS + 1;
+static_assert(kMaxDigits << 14 < (int64_t)1 << 31, "int32 coefficients");
+static_assert((kMaxDigits << 14) * 0x01010101 < (int64_t)1 << 55, "X_j, and with it signed 32-bit carry words");
+
 // Strip w from signed digits: its 64 limbs and signed carry word (32 bits, and
 // the tail flag in bit 63).  With X_j the sum of limb j's four
-// coefficients (|X_j| < 2^52), limb j takes L_j + H_(j-1) - 1 + B, whose carry
+// coefficients (|X_j| < 2^55), limb j takes L_j + H_(j-1) - 1 + B, whose carry
 // is 0, 1 or 2; after that carry has moved up, what is left is a sum of
 // 32-bit words with carries 0 or 1.  One unit is added
 // at limb bump.

@@ -15,10 +15,11 @@
 // (the root whose exponent is the bit-reversed fraction of i), so one table
 // of 2048 roots per prime serves every level of every size, and no twisting,
 // reordering or scaling pass is needed.  The splitting stops at leaves
-// x^Q - r of Q = 5..8 coefficients, whose products are formed directly
-// (64-bit multiply-adds): that costs less than three more levels in three
-// transforms, and it makes M = Q 2^k available in steps of 12 to 25% without
-// any radix-5 or radix-7 pass.
+// x^Q - r of Q = 5..8 coefficients (2..4 in the smallest transforms), whose
+// products are formed directly (64-bit multiply-adds): that costs less than
+// three more levels in three transforms, and it makes M = Q 2^k available in
+// steps of 14 to 25% (20 to 50% below 8192 points) without any radix-5 or
+// radix-7 pass.
 //
 // Arithmetic.  Montgomery products of signed 32-bit words, R = 2^32:
 // mont(b, wR) = b w mod p in (-3p/4, 3p/4) for any 32-bit b: one 32x32->64

@@ -402,11 +402,11 @@ __global__ __launch_bounds__(1024) void k_mul_mfma_close(uint32_t* out, int na, 
 // no split): enough work-groups for every CU once, at least four bands per
 // part, at least four parts and at least 32 bands (128 strips): with two
 // parts, or four thin ones, the parts' 4-strip bands on 4 waves lose more
-// than the extra CUs gain (128 products of 2^19 bits 0.54 -> 0.70 ms, 64 of
-// 2^15 bits 17 -> 31 us, one 4096-limb product mod B^n 36 -> 37 us); with
-// four or more, 2^19 bits: 1 or 4 products 0.52 -> 0.127 ms, 16 products
-// 0.52 -> 0.19, 64 products 0.53 -> 0.39; 2^17 bits, 1 or 16 products
-// 0.053 -> 0.041; products mod B^n of 2^19 bits, 1 or 16: 0.29 -> 0.115);
+// than the extra CUs gain (with digits offset by 128, before they were signed:
+// 128 products of 2^19 bits 0.54 -> 0.70 ms, 64 of 2^15 bits 17 -> 31 us, one
+// 4096-limb product mod B^n 36 -> 37 us); with four or more, 2^19 bits: 1 or 4
+// products 0.49 -> 0.115 ms, 16 products 0.49 -> 0.175, 64 products 0.50 ->
+// 0.37; 2^17 bits, 1 or 16 products 0.046 -> 0.037;
 // *wstride = strips per instance (carry words of workspace each).
 int mul_mfma_split_parts(int na, int nb, int nout, int64_t batch, int dw, int* wstride) {
   const int W = dw == 8 ? mfma::make_geo<8>(na, nb, nout).W : mfma::make_geo<7>(na, nb, nout).W;
