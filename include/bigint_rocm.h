@@ -143,9 +143,9 @@ int bigint_sub(uint32_t* out, uint32_t* borrow_out, const uint32_t* a,
  * `stream` (stream-ordered); a second launch resolves each instance's strip
  * carries.  Same bytes as one work-group per instance
  * (bigint_mfma_split_parts reports the split).
- * AUTO multiplies large operands (na + nb <= 32768; equal ones from about 1400
- * to 1700 limbs, in batches of 100 to 256 from 840 to 1250; short of the next
- * transform size up to 2900) by number-theoretic transforms of the limbs
+ * AUTO multiplies large operands (na + nb <= 32768; equal ones from about 1270
+ * to 1530 limbs, in batches of 100 to 256 from 840 to 950, but not where the
+ * next transform size is half empty) by number-theoretic transforms of the limbs
  * modulo three 27-bit primes, whose residues determine every C_k < 2^78
  * exactly (integers only, same bytes), unless a configuration is forced on the
  * thread (bigint_mul_transform reports the choice).  It is made by estimated

@@ -278,7 +278,7 @@ static bool split_forced() { return t_cfg_P || t_cfg_waves || t_cfg_dw || t_cfg_
 // quarters apart 16 and 22 for the last two).  A last round of products that
 // leaves CUs idle counts half (4096 limbs: batch 256 60 us, 300 85, 512 106).
 // The estimates are good to some 5 %, so the transform is taken where it is
-// ahead by more than that (over 3592 shapes and batches, each timed both ways:
+// ahead by more than that (over 3502 shapes and batches, each timed both ways:
 // the choice 1.8 % slower than the faster one in the mean, 3.0 % before the
 // transforms' last round was counted).  Products mod B^n take half the first
 // and 1.2e-3 of the second term (1024 limbs 3.7, 1536 6.2), which is low by
