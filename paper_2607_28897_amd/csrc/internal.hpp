@@ -141,7 +141,9 @@ size_t div_ws_bytes(int cap_u, int cap_v, int slots);
 // division, divisions resident per CU (0: they do not fit)
 struct DivCfg { int cap_u, cap_v, prod, threads, per_cu; };
 int64_t div_product_limbs(int64_t nu, int64_t nv);
-double div_size(int64_t nu, int64_t nv);
+// what a division costs grows like this (limb products)
+inline int64_t div_work(int64_t nu, int64_t nv) { return std::max<int64_t>(nu - nv + 1, 1) * (nu + 4 * nv); }
+double div_size(int64_t work);
 DivCfg div_cfg(int cap_u, int cap_v, int64_t prod, double size, double count);
 int div_chunk(const DivCfg& c, int64_t batch);
 // The allocation-free division's device workspace on the current device:

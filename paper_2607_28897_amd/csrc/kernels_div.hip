@@ -76,9 +76,7 @@ static size_t div_lds_bytes(const DivCfg& c) {
 }
 
 // Dividend limbs of the division by half as many limbs that does as much work.
-double div_size(int64_t nu, int64_t nv) {
-  return std::sqrt((double)std::max<int64_t>(nu - nv + 1, 1) * (double)(nu + 4 * nv) / 1.5);
-}
+double div_size(int64_t work) { return std::sqrt((double)work / 1.5); }
 
 // A division is mostly a chain of short passes that wait on memory and on one
 // another, and more of them on a CU hardly slow one another down (2048 / 1024
